@@ -311,7 +311,8 @@ dem_status dem_sim_status(const dem_sim* sim);
 
 /* Launch-shape tuning of one system, set before dem_add_aggregates (the
  * buffers are sized from it).  gravity_tile: spheres per gravity tile, one of
- * the sizes dem_gravity_tiles lists for the system's precision (0: default);
+ * the sizes dem_gravity_tiles lists for the system's precision (0: chosen by
+ * the number of spheres);
  * cell_scale >= 1 multiplies the contact cell side (at least the largest
  * sphere diameter).  Results do not depend on cell_scale; gravity_tile changes
  * the summation order of gravity (rounding only).  An engine may hold systems
@@ -338,16 +339,17 @@ typedef struct {
                                   are summed in another order (spin-up, stop rule). */
     int32_t gravity_form;      /* form of the exact softened sum (Eq. 4): 0 automatic --
                                   pairs unless their partial sums would exceed 64 GiB;
-                                  1 pairs: each unordered pair once, on super-tiles of
-                                  ceil(tiles / 256) tiles, one partial sum per sphere and
-                                  super-tile (at most 256 x 3 values per sphere); 2 per
+                                  1 pairs: each unordered pair once, one partial sum per
+                                  sphere and tile or source segment of a tile, past 256
+                                  tiles on super-tiles of ceil(tiles / 256) tiles, one per
+                                  super-tile (at most 352 x 3 values per sphere); 2 per
                                   target: each ordered pair from its target's side, one
                                   partial per sphere and source split (16 splits), about
                                   1.7x the time.  Same sum in another order (rounding). */
 } dem_tuning;
 dem_status dem_set_tuning(dem_sim* sim, const dem_tuning* tuning);
 /* Gravity tile sizes supported for a precision: writes up to n_max of them
- * to tiles (default first) and returns how many there are. */
+ * to tiles (the large systems' default first) and returns how many there are. */
 int32_t dem_gravity_tiles(int32_t precision, int32_t* tiles, int32_t n_max);
 
 /* Per-kernel timing (measurement aid for benchmarks).  enabled = 1: dem_step

@@ -58,6 +58,7 @@ int ceil_log2(uint64_t v) {
 // Device footprint of one system, byte for byte what alloc_pile allocates.
 struct Sizes {
   int64_t na, ns, cap, cells, g_tile, g_nt, g_np, n_rblk;
+  int64_t g_m0, g_segs, g_seg;   // see PileDev
   int g_form;                // 1 super-tile pairs, 2 per-target
   bool grav;
   bool tree;
@@ -130,16 +131,33 @@ Sizes pile_sizes(const dem_params& p, int64_t na, int64_t ns, int c_max, int til
   z.tree = z.grav && p.gravity_tree;
   z.tree_nodes = z.tree ? ((z.cells << 3) - 1) / 7 : 0;
   z.precision = p.precision;
-  z.g_tile = tile > 0 ? tile : default_tile(p.precision);
+  // the exact sum's form: pairs (one partial per tile, source segment or
+  // super-tile) unless asked otherwise or their partials would exceed
+  // kSymPartialMax
+  const GravPlan plan = gravity_plan(p.precision, ns, tile);
+  z.g_tile = plan.tile;
   z.g_nt = (ns + z.g_tile - 1) / z.g_tile;
-  // the exact sum's form: super-tile pairs (one partial per super-tile)
-  // unless asked otherwise or their partials would exceed kSymPartialMax
-  const int64_t pair_span = (z.g_nt + kGravSlots - 1) / kGravSlots;
-  const int64_t pair_np = (z.g_nt + pair_span - 1) / pair_span;
+  z.g_seg = plan.seg;
+  z.g_segs = z.g_tile / z.g_seg;
+  int64_t pair_np;
+  if (z.g_nt > kGravSlots) {
+    const int64_t span = (z.g_nt + kGravSlots - 1) / kGravSlots;
+    z.g_m0 = -1;
+    pair_np = (z.g_nt + span - 1) / span;
+  } else {
+    z.g_m0 = std::min<int64_t>(plan.m0, z.g_nt);
+    const int64_t last = ns - (z.g_nt - 1) * z.g_tile;       // slots of the last tile
+    pair_np = z.g_m0 == z.g_nt ? z.g_nt
+                               : z.g_m0 + (z.g_nt - z.g_m0 - 1) * z.g_segs +
+                                     (last + z.g_seg - 1) / z.g_seg;
+  }
   const int64_t part_bytes = pair_np * 3 * ns * (p.precision == 1 ? 4 : 8);
   z.g_form = form != 0 ? form : (part_bytes > kSymPartialMax ? 2 : 1);
   if (z.g_form == 2) {
+    if (tile <= 0) z.g_tile = default_tile(p.precision);
+    z.g_nt = (ns + z.g_tile - 1) / z.g_tile;
     const int64_t span = (z.g_nt + kGravSplits - 1) / kGravSplits;
+    z.g_m0 = -1;
     z.g_np = (z.g_nt + span - 1) / span;
   } else {
     z.g_np = pair_np;
@@ -189,7 +207,6 @@ void plan_pile(PileDev& h, const Sizes& z, BufList& L) {
   L.add(&h.sidx, ns);
   L.add(&h.sidx_raw, ns);
   L.add(&h.slot, ns);
-  L.add(&h.xs, 4 * ns);
   L.add(&h.xg, ns);
   L.add(&h.sid, ns);
   if (z.grav) {
@@ -203,12 +220,15 @@ void plan_pile(PileDev& h, const Sizes& z, BufList& L) {
     } else {
       // partials: g_np x 3 x ns values (FP64, or FP32 in the FP32-force form)
       const int64_t part_vals = z.g_np * 3 * ns;
-      L.add(&h.ganchor, 4 * z.g_nt);
+      if (z.g_form == 2 && z.precision == 1) {
+        L.add(reinterpret_cast<double**>(&h.jrec32), 4 * ns);
+        L.add(&h.ganchor, 4 * z.g_nt);
+      }
       L.add(reinterpret_cast<double**>(&h.gpart), z.precision == 1 ? (part_vals + 1) / 2 : part_vals);
     }
   }
   L.add(&h.bpart, kBbox * z.n_rblk);
-  L.add(&h.ppart, 3 * z.n_rblk);
+  L.add(&h.ppart, 3 * ((ns + 63) / 64));
   L.add(&h.grid, 1);
   L.add(&h.cell_cnt, z.cells + 1);          // + the cell of the big spheres
   L.add(&h.cell_start, z.cells + 2);
@@ -252,19 +272,19 @@ struct Batch {
   bool tree_order[2] = {false, false};       // some tree pile of order 2, 4
   unsigned tree_leaf_levels = 0;             // bit l: level l is some tree pile's finest
   int n_sph_blk = 0;
-  // gravity super-tile pairs, grouped by tile size (one launch per group)
-  GravItem* gl[3] = {nullptr, nullptr, nullptr};
-  int n_grav[3] = {0, 0, 0};
+  // gravity pair blocks, grouped by tile size (one launch per group)
+  GravPair* gl[kGravTileSizes] = {};
+  int n_grav[kGravTileSizes] = {};
   // super-tile pairs of piles with more than kGravSlots tiles, same grouping
-  GravItem* gm[3] = {nullptr, nullptr, nullptr};
-  int n_gmulti[3] = {0, 0, 0};
-  // per-target form: (target tile, source split) items, same grouping
-  GravItem* gs[3] = {nullptr, nullptr, nullptr};
-  int n_gsplit[3] = {0, 0, 0};
-  int grav_tile[3] = {0, 0, 0};
+  GravItem* gm[kGravTileSizes] = {};
+  int n_gmulti[kGravTileSizes] = {};
+  // per-target form: (target group, source split) items, same grouping
+  GravItem* gs[kGravTileSizes] = {};
+  int n_gsplit[kGravTileSizes] = {};
+  int grav_tile[kGravTileSizes] = {};
+  bool any_rec32 = false;                    // some FP32 pile in the per-target form
   int n_grav_groups = 0;
   bool any_grav = false;
-  bool any_direct = false;                   // some pile with the exact sum
   bool reduce_stage = false;                 // member reduction through LDS
   // piles whose whole step runs in one workgroup (k_fused): with gravity
   // (parts 1 and 2 around the gravity kernels) and without (part 3)
@@ -394,14 +414,15 @@ dem_status rebuild(Batch& b, hipStream_t st, dem_sim* errsim) {
   free_meta(b);
   std::vector<WorkItem> wa, wsph, wbig, wtree[11], wgrav, wall;
   std::vector<int32_t> pfg, pfng;
-  std::vector<GravItem> glg[3], gmg[3], gsg[3];
-  std::vector<std::pair<int64_t, GravItem>> gmw[3];
-  int tiles[3] = {0, 0, 0};
+  std::vector<GravItem> gmg[kGravTileSizes], gsg[kGravTileSizes];
+  std::vector<std::pair<int64_t, GravItem>> gmw[kGravTileSizes];
+  std::vector<GravPair> glg[kGravTileSizes];
+  int tiles[kGravTileSizes] = {};
   int n_groups = 0;
   std::vector<ScanSeg> sc, sp;
   std::vector<ScanItem> ic, ip;
   b.any_grav = false;
-  b.any_direct = false;
+  b.any_rec32 = false;
   b.any_tree = false;
   b.tree_order[0] = b.tree_order[1] = false;
   b.tree_leaf_levels = 0;
@@ -435,22 +456,31 @@ dem_status rebuild(Batch& b, hipStream_t st, dem_sim* errsim) {
           wtree[l].push_back({p, (int32_t)q});
     } else if (h.G != 0.0) {
       b.any_grav = true;
-      b.any_direct = true;
       if (!(h.soft_frac > 0.0)) b.all_soft = false;
-      // every super-tile pair (si <= sj) of the pile: each unordered pair
-      // once; or every (target tile, source split) of the per-target form
+      // every (target tile, source tile or segment) and every super-tile pair
+      // (si <= sj) of the pile: each unordered pair once; or every (target
+      // group, source split) of the per-target form
       int g = 0;
       while (g < n_groups && tiles[g] != h.g_tile) ++g;
       if (g == n_groups) tiles[n_groups++] = h.g_tile;
       if (h.g_form == 2) {
+        if (b.precision == 1) b.any_rec32 = true;
         const int grp = 64 * gravity_split_ipt(b.precision, h.g_tile);
         const int n_grp = (h.ns + grp - 1) / grp;
         for (int tg = 0; tg < n_grp; ++tg)
           for (int sp = 0; sp < h.g_np; ++sp) gsg[g].push_back({p, tg, sp, 0});
       } else {
-        if (h.g_np == h.g_nt) {
-          for (int si = 0; si < h.g_np; ++si)
-            for (int sj = si; sj < h.g_np; ++sj) glg[g].push_back({p, si, sj, 0});
+        if (h.g_m0 >= 0) {
+          auto row0 = [&](int t) { return t < h.g_m0 ? t : h.g_m0 + (t - h.g_m0) * h.g_segs; };
+          for (int i = 0; i < h.g_nt; ++i)
+            for (int j = i; j < h.g_nt; ++j) {
+              const int j1 = std::min((j + 1) * h.g_tile, h.ns);
+              const int seg = j < h.g_m0 ? h.g_tile : h.g_seg;
+              int row = row0(j);
+              for (int s = j * h.g_tile; s < j1; s += seg)
+                glg[g].push_back({p, i * h.g_tile, s, std::min(s + seg, j1), row++,
+                                  i == j ? -1 : row0(i), {0, 0}});
+            }
         } else {
           // super-tiles of several tiles: items weighted by their tile pairs
           const int span = (h.g_nt + kGravSlots - 1) / kGravSlots;
@@ -499,11 +529,14 @@ dem_status rebuild(Batch& b, hipStream_t st, dem_sim* errsim) {
     b.wl_tree[l] = nullptr;
     if (!wtree[l].empty()) HIPCHK(errsim, upload(b, &b.wl_tree[l], wtree[l], st));
   }
-  for (int g = 0; g < 3; ++g) {
-    HIPCHK(errsim, upload(b, &b.gl[g], glg[g], st));
-    b.n_grav[g] = (int)glg[g].size();
+  for (int g = 0; g < kGravTileSizes; ++g) {
     // largest items first: the blocks are handed out in launch order, so
     // the launch ends on the smallest ones
+    std::stable_sort(glg[g].begin(), glg[g].end(), [](const GravPair& a, const GravPair& c) {
+      return a.j1 - a.j0 > c.j1 - c.j0;
+    });
+    HIPCHK(errsim, upload(b, &b.gl[g], glg[g], st));
+    b.n_grav[g] = (int)glg[g].size();
     std::stable_sort(gmw[g].begin(), gmw[g].end(),
                      [](const auto& a, const auto& c) { return a.first > c.first; });
     for (const auto& e : gmw[g]) gmg[g].push_back(e.second);
@@ -603,18 +636,18 @@ void enqueue_pass_marked(Batch& b, hipStream_t st, int mode, Mark mark, bool ove
   });
   const bool fork = overlap && b.any_grav && b.side && staged;
   auto gravity = [&](hipStream_t s) {
-    launch_gravity_records(s, b.d_table, b.wl_grav, b.n_grav_blk, b.precision);
+    if (b.any_rec32) launch_gravity_records(s, b.d_table, b.wl_grav, b.n_grav_blk);
     for (int g = 0; g < b.n_grav_groups; ++g) {
-      launch_gravity_tiles(s, b.d_table, b.gl[g], b.n_grav[g], b.precision, b.all_soft,
-                           b.grav_tile[g], false);
+      launch_gravity_pairs(s, b.d_table, b.gl[g], b.n_grav[g], b.precision, b.all_soft,
+                           b.grav_tile[g]);
       launch_gravity_tiles(s, b.d_table, b.gm[g], b.n_gmulti[g], b.precision, b.all_soft,
-                           b.grav_tile[g], true);
+                           b.grav_tile[g]);
       launch_gravity_split(s, b.d_table, b.gs[g], b.n_gsplit[g], b.precision, b.all_soft,
                            b.grav_tile[g]);
     }
-    if (b.any_direct) launch_gravity_combine(s, b.d_table, b.wl_grav, b.n_grav_blk, b.precision);
     if (b.any_tree) launch_tree(s, b.d_table, b.wl_tree, b.n_tree, b.tree_leaf_levels, b.wl_sph,
                                b.n_sph_blk, b.tree_order);
+    launch_gravity_combine(s, b.d_table, b.wl_grav, b.n_grav_blk, b.precision);
   };
   if (fork) {
     (void)hipEventRecord(b.fork_ev, st);
@@ -835,6 +868,9 @@ dem_status alloc_pile(dem_sim* s, int64_t na, int64_t ns) {
   h.g_nt = (int32_t)s->sz.g_nt;
   h.g_form = s->sz.g_form;
   h.g_np = (int32_t)s->sz.g_np;
+  h.g_m0 = (int32_t)s->sz.g_m0;
+  h.g_segs = (int32_t)s->sz.g_segs;
+  h.g_seg = (int32_t)s->sz.g_seg;
   h.n_rblk = (int32_t)s->sz.n_rblk;
   h.box = s->prm.box[0];
   h.G = s->prm.G;
@@ -1078,7 +1114,6 @@ NoAllocPlan plan_noalloc(char* base, int64_t n, PileDev& h) {
   h.sidx = L.take<uint32_t>(n);
   h.sidx_raw = L.take<uint32_t>(n);
   h.slot = L.take<uint32_t>(n);
-  h.xs = L.take<double>(4 * n);
   h.xg = L.take<SortedGeom>(n);
   h.sid = L.take<SortedId>(n);
   h.bpart = L.take<double>(kBbox * q.n_blk);

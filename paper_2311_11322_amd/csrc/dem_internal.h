@@ -72,6 +72,11 @@ struct alignas(8) SortedId {
   uint32_t id;
 };
 
+// Source record of gravity: centre, mass, softening half-length.
+struct alignas(64) Rec64 {
+  double x, y, z, m, e, p0, p1, p2;
+};
+
 struct PileDev {
   // sizes (host-set)
   int32_t na, ns;
@@ -81,7 +86,11 @@ struct PileDev {
   int32_t g_tile;            // gravity tile (slots per tile)
   int32_t g_nt;              // gravity tiles
   int32_t g_form;            // 1: symmetric super-tile pairs; 2: per-target
-  int32_t g_np;              // partial-sum rows per sphere: super-tiles, or source splits
+  int32_t g_np;              // partial-sum rows: tiles and source segments, super-tiles, or splits
+  int32_t g_m0;              // pairs of single tiles: tiles from g_m0 on are cut into segments
+  int32_t g_segs;            // source segments of such a tile (rows g_m0 + (J - g_m0) g_segs + s)
+  int32_t g_seg;             // sources per segment
+  int32_t pad7;
   int32_t n_rblk;            // reconstruct blocks (bbox partials)
   int32_t n_periodic;        // cells per axis of a periodic pile
   int32_t member_scan;       // 1: reduction finds members by scanning all spheres
@@ -133,7 +142,7 @@ struct PileDev {
   int32_t pad1;
   double pert_M;
   double pert_r[2][3], pert_v[2][3], pert_a[2][3];
-  double* ppart;             // [n_rblk][3] block sums of the perturber's pull
+  double* ppart;             // [ceil(ns / 64)][3] sums of the perturber's pull over 64 slots
 
   // aggregate constants (written once by the set-up kernel)
   int32_t* first;            // [na] first member sphere
@@ -164,11 +173,11 @@ struct PileDev {
   uint32_t* sidx;            // [ns] sphere at sorted slot
   uint32_t* sidx_raw;        // [ns] sphere at slot, in atomic arrival order
   uint32_t* slot;            // [ns] sorted slot of sphere
-  double* xs;                // [4][ns] sorted x, y, z, radius (gravity)
   SortedGeom* xg;            // [ns] sorted x, y, z, radius (search)
   SortedId* sid;             // [ns] sorted aggregate id and sphere id
-  void* jrec;                // gravity records in sorted order (64 B FP64 / 32 B FP32)
-  double* ganchor;           // [g_nt][4] FP64 anchor of each tile (relative coordinates)
+  void* jrec;                // gravity records in sorted order (64 B, FP64)
+  void* jrec32;              // FP32 per-target form: 32 B records relative to their tile's anchor
+  double* ganchor;           // [g_nt][4] that form's FP64 anchor of each tile
   void* gpart;               // [g_np][3][ns] partial sums (sorted slots)
   double* gacc;              // [3][ns] gravity force G m_i sum_j (by sphere id)
   double* bpart;             // [n_rblk][kBbox] bbox min/max + mass moments
@@ -191,8 +200,19 @@ struct WorkItem {
   int32_t base;
 };
 
-// One block of the gravity kernel: the super-tile pair (ti, tj), ti <= tj,
-// of a pile; in the per-target form, target tile ti and source split tj.
+// One block of the pair kernel: the targets from slot i0 on (one tile) against
+// the sources in slots [j0, j1) of the same or a later tile.  The targets' sums
+// go to row row_t of the partial sums, the sources' reactions to row row_r
+// (row_r < 0: sources of the targets' own tile, ordered pairs one way).
+struct GravPair {
+  int32_t pile;
+  int32_t i0, j0, j1;
+  int32_t row_t, row_r;
+  int32_t pad[2];
+};
+
+// One block of the super-tile kernel: the super-tile pair (ti, tj), ti <= tj,
+// of a pile; in the per-target form, target group ti and source split tj.
 struct GravItem {
   int32_t pile;
   int32_t ti, tj;
@@ -234,14 +254,15 @@ void launch_search_big(hipStream_t st, const PileDev* piles, const WorkItem* wl,
                        int write);
 void launch_forces(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk,
                    ContactParams cp, int precision);
-// Gravity: records and the per-slot combine cover every pile; the pair and
-// per-target kernels run once per tile size present in the batch.
-void launch_gravity_records(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk,
-                            int precision);
-// multi: the items' piles have more tiles than kGravSlots (super-tiles of
-// several tiles); otherwise every item is one tile pair.
+// Gravity: the per-slot combine covers every pile (the tree's included); the
+// pair, super-tile and per-target kernels run once per tile size present in
+// the batch.  records: the FP32 records of the piles in the per-target form.
+void launch_gravity_records(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk);
+void launch_gravity_pairs(hipStream_t st, const PileDev* piles, const GravPair* gp, int nitems,
+                          int precision, bool softened, int tile);
+// Piles of more than kGravSlots tiles: super-tiles of several tiles.
 void launch_gravity_tiles(hipStream_t st, const PileDev* piles, const GravItem* gl, int nitems,
-                          int precision, bool softened, int tile, bool multi);
+                          int precision, bool softened, int tile);
 void launch_gravity_split(hipStream_t st, const PileDev* piles, const GravItem* gl, int nitems,
                           int precision, bool softened, int tile);
 // Targets per lane of the per-target kernel for a precision and tile size
@@ -249,8 +270,19 @@ void launch_gravity_split(hipStream_t st, const PileDev* piles, const GravItem* 
 int gravity_split_ipt(int precision, int tile);
 void launch_gravity_combine(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk,
                             int precision);
-// Supported tile sizes for a precision (default first); returns the count.
+// Supported tile sizes for a precision (the large piles' default first);
+// returns the count.
 int gravity_tiles(int precision, int* tiles);
+// How the exact sum of a pile in the pair form is cut into blocks: its tile
+// (the given one, or chosen by the number of spheres when tile is 0) and, for
+// piles of at most kGravSlots tiles, which tiles are cut into segments of how
+// many sources.
+struct GravPlan {
+  int tile, seg, m0;
+};
+GravPlan gravity_plan(int precision, int64_t ns, int tile);
+// Tile sizes the pair kernel is built for: the supported ones and smaller.
+constexpr int kGravTileSizes = 5;
 // Aggregates in one launch from which the member reduction stages its
 // members through LDS (below it, direct member reads are faster: few waves,
 // and the members stay in L2 between a wave's member iterations).

@@ -8,12 +8,12 @@ namespace dem {
 
 namespace {
 
-struct alignas(64) Rec64 {
-  double x, y, z, m, e, p0, p1, p2;
-};
 struct alignas(32) Rec32 {
   float x, y, z, m, e, p0, p1, p2;
 };
+
+constexpr int kTreeSplit = 2;      // a group's walk is split over the 8^2 subtrees of level 2
+constexpr int kTreeParts = 1 << (3 * kTreeSplit);   // partial sums per slot of a tree pile
 
 // Records are read through the constant address space: with a uniform index
 // these become scalar loads into SGPRs.

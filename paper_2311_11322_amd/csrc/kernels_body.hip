@@ -347,15 +347,13 @@ __global__ __launch_bounds__(kBlock) void k_reduce(const PileDev* __restrict__ p
   reduce_tail(P, A, R, FA, NA, cp, mode);
 }
 
-// One thread per pile: commit the step (flip the ping-pong halves) unless
-// the pile failed during it, in which case its state stays at the failing
-// step's start and the step index is recorded.
-__global__ void k_finish(PileDev* __restrict__ piles, int n_piles, int mode, double dt) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= n_piles) return;
-  PileDev& P = piles[p];
+// One wave per pile: commit the step (flip the ping-pong halves) unless the
+// pile failed during it, in which case its state stays at the failing step's
+// start and the step index is recorded.
+__global__ __launch_bounds__(64) void k_finish(PileDev* __restrict__ piles, int mode, double dt) {
+  PileDev& P = piles[blockIdx.x];
   if (P.fused) return;                       // k_fused finishes it
-  finish_one(P, mode, dt);
+  finish_one(P, threadIdx.x, mode, dt);
 }
 
 __global__ void k_fill_u32(uint32_t* __restrict__ p, uint32_t value, int64_t n) {
@@ -391,8 +389,7 @@ void launch_reduce(hipStream_t st, const PileDev* piles, const WorkItem* wl, int
 }
 
 void launch_finish(hipStream_t st, PileDev* piles, int n_piles, int mode, double dt) {
-  hipLaunchKernelGGL(k_finish, dim3((n_piles + 63) / 64), dim3(64), 0, st, piles, n_piles, mode,
-                     dt);
+  hipLaunchKernelGGL(k_finish, dim3(n_piles), dim3(64), 0, st, piles, mode, dt);
 }
 
 void launch_fill_u32(hipStream_t st, uint32_t* p, uint32_t value, int64_t n) {

@@ -177,7 +177,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_fused(PileDev* __restrict__ p
       }
       stage_sync();
     }
-    if (tid == 0) finish_one(P, mode, cp.dt);
+    if (tid < 64) finish_one(P, tid, mode, cp.dt);
   }
 }
 

@@ -2,253 +2,263 @@
 // paper, with Plummer softening eps_ij = soft_frac (s_i + s_j) / 2).
 //
 // Spheres are taken in cell-sorted (Morton) order and cut into tiles of B
-// slots, and the tiles into at most kGravSlots super-tiles of `span`
-// consecutive tiles.  One wave computes one super-tile pair (SI, SJ),
-// SI <= SJ, tile pair by tile pair (I, J), I <= J, so every unordered pair
-// of spheres is evaluated once (Newton's third law):
-//  * each lane holds IPT targets of tile I in registers, and their sums
-//    over all J of SJ;
-//  * the sources of tile J enter 64 at a time, one per lane, together with
-//    a reaction accumulator, and rotate one lane per step (DPP wave_ror:1)
-//    so that after 64 steps every source has met every target of the wave
-//    and is back in its own lane holding its complete reaction sum, which
-//    that lane adds to the source's running sum over the tiles of SI;
-//  * a diagonal pair (I, I) evaluates the ordered pairs i != j one way only,
-//    with the sources walked by a uniform index (scalar loads).
-// Each sphere receives exactly one partial sum per super-tile (as a target
-// of SJ's row or a source of SI's column), summed in a fixed order and
-// stored per super-tile; the combine kernel adds them in super-tile order,
-// so the result is deterministic and independent of other piles, and the
-// partial sums take at most kGravSlots x 3 values per sphere.  With no more
-// tiles than kGravSlots a super-tile is one tile.
+// slots.  A pile of at most kGravSlots tiles runs k_grav_pairs: one wave per
+// (target tile I, sources of tile J >= I or of a segment of it), so every
+// unordered pair of spheres is evaluated once (Newton's third law):
+//  * each lane holds IPT = B / 64 targets in registers, with their sums;
+//  * the sources enter 64 at a time, one per lane, together with a reaction
+//    accumulator, and rotate one lane per step (DPP wave_ror:1), so that after
+//    64 steps every source has met every target of the wave and is back in
+//    its own lane holding its complete reaction sum;
+//  * sources of the targets' own tile rotate without a reaction (ordered
+//    pairs, one way).
+// Each block stores its targets' sums in the row of its sources (tile or
+// segment) and its sources' reactions in the row of its targets' tile; the
+// combine kernel adds a sphere's rows in a fixed order, so the result is
+// deterministic and independent of other piles.
+//
+// A larger pile runs k_grav_tiles: its tiles are grouped into at most
+// kGravSlots super-tiles of `span` consecutive tiles and one wave takes one
+// super-tile pair (SI, SJ), SI <= SJ, tile pair by tile pair: the targets of
+// I keep their sums over all J of SJ, and a source's lane adds its reaction to
+// the source's running sum over the tiles of SI.  The partial sums take at
+// most kGravSlots x 3 values per sphere.
 //
 // FP64 form: rsqrt from the hardware estimate y0 and one first-order
 // correction folded into the cube: r^-3 = y0^3 (1 + 3e/2), e = 1 - r^2 y0^2.
-// FP32-force form: coordinates relative to an FP64 anchor per tile (the
-// first sphere of the tile); the anchor offset of a tile pair, formed in
-// FP64, moves one tile into the other's frame; FP32 partial sums per
-// super-tile, FP64 across them.
+// FP32-force form: coordinates relative to an FP64 anchor, the first sphere of
+// the target tile, subtracted in FP64 from the FP64 records as a block loads
+// them; FP32 partial sums, FP64 across them.  (The per-target form reads FP32
+// records relative to their own tile's anchor instead.)
 #include "gravity_common.h"
+
+#include <algorithm>
 
 namespace dem {
 
 namespace {
 
-// One thread per sorted slot: the source record of the sphere in that slot.
+// FP32 per-target form, one thread per sorted slot: the sphere's record
+// relative to its tile's anchor (the tile's first sphere).
 __global__ __launch_bounds__(kBlock) void k_grav_records(const PileDev* __restrict__ piles,
-                                                         const WorkItem* __restrict__ wl,
-                                                         int precision) {
+                                                         const WorkItem* __restrict__ wl) {
   const WorkItem w = wl[blockIdx.x];
   const PileDev& P = piles[w.pile];
   const int k = w.base + threadIdx.x;
-  if (k >= P.ns || P.status != 0 || P.G == 0.0) return;
-  const int ns = P.ns;
-  const double x = P.xs[k], y = P.xs[ns + k], z = P.xs[2 * ns + k];
-  const double e = 0.5 * P.soft_frac * P.xs[3 * ns + k];
-  const double m = P.m[P.sidx[k]];
-  if (precision == 1 && !P.tree) {
-    const int a = (k / P.g_tile) * P.g_tile;
-    const double ax = P.xs[a], ay = P.xs[ns + a], az = P.xs[2 * ns + a];
-    Rec32 r;
-    r.x = (float)(x - ax);
-    r.y = (float)(y - ay);
-    r.z = (float)(z - az);
-    r.m = (float)m;
-    r.e = (float)e;
-    r.p0 = r.p1 = r.p2 = 0.f;
-    ((Rec32*)P.jrec)[k] = r;
-    if (k == a) {
-      double* an = P.ganchor + (size_t)(k / P.g_tile) * 4;
-      an[0] = ax;
-      an[1] = ay;
-      an[2] = az;
-      an[3] = 0.0;
-    }
-  } else {
-    Rec64 r;
-    r.x = x;
-    r.y = y;
-    r.z = z;
-    r.m = m;
-    r.e = e;
-    r.p0 = r.p1 = r.p2 = 0.0;
-    ((Rec64*)P.jrec)[k] = r;
+  if (k >= P.ns || P.status != 0 || P.g_form != 2 || P.tree) return;
+  const int a = (k / P.g_tile) * P.g_tile;
+  const Rec64 f = ((const Rec64*)P.jrec)[k], o = ((const Rec64*)P.jrec)[a];
+  ((Rec32*)P.jrec32)[k] = Rec32{(float)(f.x - o.x), (float)(f.y - o.y), (float)(f.z - o.z),
+                                (float)f.m, (float)f.e, 0.f, 0.f, 0.f};
+  if (k == a) {
+    double* an = P.ganchor + (size_t)(k / P.g_tile) * 4;
+    an[0] = o.x;
+    an[1] = o.y;
+    an[2] = o.z;
+    an[3] = 0.0;
   }
 }
 
-// FP64 with 8 targets per lane runs at two waves per SIMD whatever the
-// schedule; saying so lets the compiler issue the eight inverse square roots
-// together (measured 1.5 % faster at 125k spheres than its three-wave
-// schedule).
-template <typename T, int IPT, bool SOFT, bool MULTI>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(
-    1, (sizeof(T) == 8 && IPT == 8) ? 2 : 8))) void k_grav_tiles(const PileDev* __restrict__ piles,
-                                                   const GravItem* __restrict__ gl) {
+// A source or target of the pair kernels: the record's centre less the
+// anchor (FP32 form; the FP64 form takes the centre as it is), its softening
+// half-length and its mass.
+template <typename T>
+struct Src {
+  T x, y, z, m, e;
+};
+template <typename T>
+__device__ __forceinline__ Src<T> relative(const Rec64& r, const double an[3]) {
+  if (sizeof(T) == 4)
+    return Src<T>{(T)(r.x - an[0]), (T)(r.y - an[1]), (T)(r.z - an[2]), (T)r.m, (T)r.e};
+  return Src<T>{(T)r.x, (T)r.y, (T)r.z, (T)r.m, (T)r.e};
+}
+
+// 64 sources, one per lane, led once around the wave past every lane's IPT
+// targets; with REACT each source's reaction sum comes back in (bx, by, bz).
+template <typename T, int IPT, bool SOFT, bool REACT>
+__device__ __forceinline__ void ring(Src<T> s, const T (&xi)[IPT], const T (&yi)[IPT],
+                                     const T (&zi)[IPT], const T (&ei)[IPT], const T (&mi)[IPT],
+                                     T (&ax)[IPT], T (&ay)[IPT], T (&az)[IPT], double c15, T& bx,
+                                     T& by, T& bz) {
+  bx = by = bz = 0;
+  for (int step = 0; step < 64; ++step) {
+#pragma unroll
+    for (int u = 0; u < IPT; ++u) {
+      // a sphere met by itself (own tile) contributes nothing: d = 0, and
+      // r^-3 = 0 when unsoftened
+      const T dx = s.x - xi[u], dy = s.y - yi[u], dz = s.z - zi[u];
+      const T t = ei[u] + s.e;
+      const T r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, t * t)));
+      const T c3 = inv_cube<SOFT>(r2, c15);
+      const T wi = s.m * c3;
+      ax[u] = fma(wi, dx, ax[u]);
+      ay[u] = fma(wi, dy, ay[u]);
+      az[u] = fma(wi, dz, az[u]);
+      if (REACT) {
+        const T wj = mi[u] * c3;
+        bx = fma(wj, dx, bx);
+        by = fma(wj, dy, by);
+        bz = fma(wj, dz, bz);
+      }
+    }
+    s.x = ror1(s.x);
+    s.y = ror1(s.y);
+    s.z = ror1(s.z);
+    s.m = ror1(s.m);
+    s.e = ror1(s.e);
+    if (REACT) {
+      bx = ror1(bx);
+      by = ror1(by);
+      bz = ror1(bz);
+    }
+  }
+}
+
+// Waves per SIMD the compiler may plan for.  FP64 with 8 targets per lane runs
+// at two waves per SIMD whatever the schedule; saying so lets the compiler
+// issue the eight inverse square roots together (measured 1.5 % faster at 125k
+// spheres than its three-wave schedule).
+#define GRAV_WAVES(T, IPT) \
+  __attribute__((amdgpu_waves_per_eu(1, (sizeof(T) == 8 && IPT == 8) ? 2 : 8)))
+
+template <typename T, int IPT, bool SOFT>
+__global__ __launch_bounds__(64) GRAV_WAVES(T, IPT) void k_grav_pairs(
+    const PileDev* __restrict__ piles, const GravPair* __restrict__ gp) {
+  const GravPair it = gp[blockIdx.x];
+  const PileDev& P = piles[it.pile];
+  if (P.status != 0) return;
+  const int ns = P.ns, lane = threadIdx.x;
+  const Rec64* __restrict__ rec = (const Rec64*)P.jrec;
+  double c15;
+  series_coeffs(c15);
+  T* __restrict__ part = (T*)P.gpart;
+  double an[3] = {0.0, 0.0, 0.0};
+  if (sizeof(T) == 4) {
+    const ConstRec64 cr = (ConstRec64)P.jrec;
+    an[0] = cr[it.i0].x;
+    an[1] = cr[it.i0].y;
+    an[2] = cr[it.i0].z;
+  }
+  T xi[IPT], yi[IPT], zi[IPT], ei[IPT], mi[IPT], ax[IPT], ay[IPT], az[IPT];
+#pragma unroll
+  for (int u = 0; u < IPT; ++u) {
+    const int k = it.i0 + u * 64 + lane;
+    const Src<T> r = relative<T>(rec[min(k, ns - 1)], an);
+    xi[u] = r.x;
+    yi[u] = r.y;
+    zi[u] = r.z;
+    ei[u] = r.e;
+    mi[u] = k < ns ? r.m : (T)0;
+    ax[u] = ay[u] = az[u] = (T)0;
+  }
+  // with few targets per lane a round of 64 sources is short, so the next 64
+  // are loaded while the current ones go round
+  constexpr bool kAhead = IPT < 8;
+  Rec64 next = rec[min(it.j0 + lane, it.j1 - 1)];
+  for (int jc = it.j0; jc < it.j1; jc += 64) {
+    const int jx = jc + lane;
+    Src<T> s = relative<T>(next, an);
+    if (jx >= it.j1) s.m = (T)0;
+    if (kAhead) next = rec[min(jx + 64, it.j1 - 1)];
+    T bx, by, bz;
+    if (it.row_r < 0) {
+      ring<T, IPT, SOFT, false>(s, xi, yi, zi, ei, mi, ax, ay, az, c15, bx, by, bz);
+    } else {
+      ring<T, IPT, SOFT, true>(s, xi, yi, zi, ei, mi, ax, ay, az, c15, bx, by, bz);
+      if (jx < it.j1) {
+        T* q = part + (size_t)it.row_r * 3 * ns + jx;
+        q[0] = -bx;
+        q[ns] = -by;
+        q[2 * (size_t)ns] = -bz;
+      }
+    }
+    if (!kAhead) next = rec[min(jx + 64, it.j1 - 1)];
+  }
+#pragma unroll
+  for (int u = 0; u < IPT; ++u) {
+    const int k = it.i0 + u * 64 + lane;
+    if (k < ns) {
+      T* q = part + (size_t)it.row_t * 3 * ns + k;
+      q[0] = ax[u];
+      q[ns] = ay[u];
+      q[2 * (size_t)ns] = az[u];
+    }
+  }
+}
+
+template <typename T, int IPT, bool SOFT>
+__global__ __launch_bounds__(64) GRAV_WAVES(T, IPT) void k_grav_tiles(
+    const PileDev* __restrict__ piles, const GravItem* __restrict__ gl) {
   constexpr int B = 64 * IPT;
-  constexpr bool F32 = sizeof(T) == 4;
   const GravItem it = gl[blockIdx.x];
   const PileDev& P = piles[it.pile];
   if (P.status != 0) return;
   const int ns = P.ns, nt = P.g_nt, lane = threadIdx.x;
-  // tiles per super-tile (the launch for piles of at most kGravSlots tiles
-  // takes one, fixed at compile time)
-  const int span = MULTI ? (nt + kGravSlots - 1) / kGravSlots : 1;
+  const int span = (nt + kGravSlots - 1) / kGravSlots;     // tiles per super-tile
   const int si = it.ti, sj = it.tj;
-  const int I0 = si * span, I1 = MULTI ? min(I0 + span, nt) : I0 + 1;
-  const int J0 = sj * span, J1 = MULTI ? min(J0 + span, nt) : J0 + 1;
+  const int I0 = si * span, I1 = min(I0 + span, nt);
+  const int J0 = sj * span, J1 = min(J0 + span, nt);
   const bool diag_item = si == sj;
+  const Rec64* __restrict__ rec = (const Rec64*)P.jrec;
   double c15;
   series_coeffs(c15);
   T* __restrict__ part = (T*)P.gpart;
 
   for (int I = I0; I < I1; ++I) {
     const int i0 = I * B;
+    double an[3] = {0.0, 0.0, 0.0};
+    if (sizeof(T) == 4) {
+      const ConstRec64 cr = (ConstRec64)P.jrec;
+      an[0] = cr[i0].x;
+      an[1] = cr[i0].y;
+      an[2] = cr[i0].z;
+    }
     T xi[IPT], yi[IPT], zi[IPT], ei[IPT], mi[IPT], ax[IPT], ay[IPT], az[IPT];
 #pragma unroll
-    for (int u = 0; u < IPT; ++u) ax[u] = ay[u] = az[u] = (T)0;
-    // targets of tile I, in the FP32 form less an anchor offset
-    auto load_targets = [&](T tx, T ty, T tz) {
-#pragma unroll
-      for (int u = 0; u < IPT; ++u) {
-        const int k = i0 + u * 64 + lane;
-        const int kk = k < ns ? k : ns - 1;
-        if (F32) {
-          const Rec32 r = ((const Rec32*)P.jrec)[kk];
-          xi[u] = (T)r.x - tx;
-          yi[u] = (T)r.y - ty;
-          zi[u] = (T)r.z - tz;
-          ei[u] = (T)r.e;
-          mi[u] = k < ns ? (T)r.m : (T)0;
-        } else {
-          const Rec64 r = ((const Rec64*)P.jrec)[kk];
-          xi[u] = (T)r.x;
-          yi[u] = (T)r.y;
-          zi[u] = (T)r.z;
-          ei[u] = (T)r.e;
-          mi[u] = k < ns ? (T)r.m : (T)0;
-        }
-      }
-    };
-    if (MULTI) load_targets((T)0, (T)0, (T)0);
+    for (int u = 0; u < IPT; ++u) {
+      const int k = i0 + u * 64 + lane;
+      const Src<T> r = relative<T>(rec[min(k, ns - 1)], an);
+      xi[u] = r.x;
+      yi[u] = r.y;
+      zi[u] = r.z;
+      ei[u] = r.e;
+      mi[u] = k < ns ? r.m : (T)0;
+      ax[u] = ay[u] = az[u] = (T)0;
+    }
     for (int J = diag_item ? I : J0; J < J1; ++J) {
-      // FP32 form: anchor offset A_J - A_I, formed in FP64; it moves the
-      // targets into J's frame when an item is one tile pair, and the
-      // sources into I's frame when the targets stay for several J
-      T sx = 0, sy = 0, sz = 0;
-      if (F32) {
-        const double* aI = P.ganchor + (size_t)I * 4;
-        const double* aJ = P.ganchor + (size_t)J * 4;
-        sx = (T)(aJ[0] - aI[0]);
-        sy = (T)(aJ[1] - aI[1]);
-        sz = (T)(aJ[2] - aI[2]);
-      }
-      if (!MULTI) load_targets(sx, sy, sz);
       const int j0 = J * B, j1 = min(j0 + B, ns);
-      if (J == I) {
-        // ordered pairs inside one tile, one way only; sources via scalar loads
-        for (int j = j0; j < j1; ++j) {
-          T xj, yj, zj, mj, ej;
-          if (F32) {
-            const ConstRec32 cr = (ConstRec32)P.jrec;
-            xj = cr[j].x;
-            yj = cr[j].y;
-            zj = cr[j].z;
-            mj = cr[j].m;
-            ej = cr[j].e;
-          } else {
-            const ConstRec64 cr = (ConstRec64)P.jrec;
-            xj = (T)cr[j].x;
-            yj = (T)cr[j].y;
-            zj = (T)cr[j].z;
-            mj = (T)cr[j].m;
-            ej = (T)cr[j].e;
-          }
-#pragma unroll
-          for (int u = 0; u < IPT; ++u) {
-            // j == i gives d = 0 and contributes nothing (r^-3 = 0 when unsoftened)
-            const T dx = xj - xi[u], dy = yj - yi[u], dz = zj - zi[u];
-            const T t = ei[u] + ej;
-            const T r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, t * t)));
-            const T w = mj * inv_cube<SOFT>(r2, c15);
-            ax[u] = fma(w, dx, ax[u]);
-            ay[u] = fma(w, dy, ay[u]);
-            az[u] = fma(w, dz, az[u]);
-          }
-        }
-        continue;
-      }
-      // sources of tile J travel around the wave 64 at a time, each carrying
-      // its own reaction sum; after 64 one-lane rotations it is back home
       for (int jc = j0; jc < j1; jc += 64) {
         const int jx = jc + lane;
-        const int jk = jx < j1 ? jx : j1 - 1;
-        T xj, yj, zj, mj, ej;
-        if (F32) {
-          const Rec32 r = ((const Rec32*)P.jrec)[jk];
-          xj = MULTI ? r.x + sx : r.x;
-          yj = MULTI ? r.y + sy : r.y;
-          zj = MULTI ? r.z + sz : r.z;
-          mj = jx < j1 ? r.m : 0.f;
-          ej = r.e;
-        } else {
-          const Rec64 r = ((const Rec64*)P.jrec)[jk];
-          xj = (T)r.x;
-          yj = (T)r.y;
-          zj = (T)r.z;
-          mj = jx < j1 ? (T)r.m : (T)0;
-          ej = (T)r.e;
+        Src<T> s = relative<T>(rec[min(jx, j1 - 1)], an);
+        if (jx >= j1) s.m = (T)0;
+        T bx, by, bz;
+        if (J == I) {
+          ring<T, IPT, SOFT, false>(s, xi, yi, zi, ei, mi, ax, ay, az, c15, bx, by, bz);
+          continue;
         }
-        T bx = 0, by = 0, bz = 0;
-        for (int step = 0; step < 64; ++step) {
-#pragma unroll
-          for (int u = 0; u < IPT; ++u) {
-            const T dx = xj - xi[u], dy = yj - yi[u], dz = zj - zi[u];
-            const T t = ei[u] + ej;
-            const T r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, t * t)));
-            const T c3 = inv_cube<SOFT>(r2, c15);
-            const T wi = mj * c3, wj = mi[u] * c3;
-            ax[u] = fma(wi, dx, ax[u]);
-            ay[u] = fma(wi, dy, ay[u]);
-            az[u] = fma(wi, dz, az[u]);
-            bx = fma(wj, dx, bx);
-            by = fma(wj, dy, by);
-            bz = fma(wj, dz, bz);
-          }
-          xj = ror1(xj);
-          yj = ror1(yj);
-          zj = ror1(zj);
-          mj = ror1(mj);
-          ej = ror1(ej);
-          bx = ror1(bx);
-          by = ror1(by);
-          bz = ror1(bz);
-        }
+        ring<T, IPT, SOFT, true>(s, xi, yi, zi, ei, mi, ax, ay, az, c15, bx, by, bz);
         // add to the source's reaction sum over the tiles of SI so far (which
         // this same lane stored)
         if (jx < j1) {
-          T* qx = part + ((size_t)si * 3 + 0) * ns + jx;
-          T* qy = part + ((size_t)si * 3 + 1) * ns + jx;
-          T* qz = part + ((size_t)si * 3 + 2) * ns + jx;
-          const bool first = !MULTI || I == I0;
-          *qx = first ? -bx : *qx - bx;
-          *qy = first ? -by : *qy - by;
-          *qz = first ? -bz : *qz - bz;
+          T* q = part + (size_t)si * 3 * ns + jx;
+          const bool first = I == I0;
+          q[0] = first ? -bx : q[0] - bx;
+          q[ns] = first ? -by : q[ns] - by;
+          q[2 * (size_t)ns] = first ? -bz : q[2 * (size_t)ns] - bz;
         }
       }
     }
     // targets of tile I store under super-tile sj; on a diagonal item that
     // slot already holds the reactions from the tiles before I
-    const bool add = MULTI && diag_item && I > I0;
+    const bool add = diag_item && I > I0;
 #pragma unroll
     for (int u = 0; u < IPT; ++u) {
       const int k = i0 + u * 64 + lane;
       if (k < ns) {
-        T* px = part + ((size_t)sj * 3 + 0) * ns + k;
-        T* py = part + ((size_t)sj * 3 + 1) * ns + k;
-        T* pz = part + ((size_t)sj * 3 + 2) * ns + k;
-        *px = add ? *px + ax[u] : ax[u];
-        *py = add ? *py + ay[u] : ay[u];
-        *pz = add ? *pz + az[u] : az[u];
+        T* q = part + (size_t)sj * 3 * ns + k;
+        q[0] = add ? q[0] + ax[u] : ax[u];
+        q[ns] = add ? q[ns] + ay[u] : ay[u];
+        q[2 * (size_t)ns] = add ? q[2 * (size_t)ns] + az[u] : az[u];
       }
     }
   }
@@ -285,7 +295,7 @@ __global__ __launch_bounds__(64) void k_grav_split(const PileDev* __restrict__ p
     const int k = i0 + u * 64 + lane;
     const int kk = k < ns ? k : ns - 1;
     if (F32) {
-      const Rec32 r = ((const Rec32*)P.jrec)[kk];
+      const Rec32 r = ((const Rec32*)P.jrec32)[kk];
       xi[u] = (T)r.x;
       yi[u] = (T)r.y;
       zi[u] = (T)r.z;
@@ -321,7 +331,7 @@ __global__ __launch_bounds__(64) void k_grav_split(const PileDev* __restrict__ p
     for (int j = j0; j < j1; ++j) {
       T xj, yj, zj, mj, ej;
       if (F32) {
-        const ConstRec32 cr = (ConstRec32)P.jrec;
+        const ConstRec32 cr = (ConstRec32)P.jrec32;
         xj = cr[j].x;
         yj = cr[j].y;
         zj = cr[j].z;
@@ -361,33 +371,85 @@ __global__ __launch_bounds__(64) void k_grav_split(const PileDev* __restrict__ p
   }
 }
 
-// One thread per sorted slot: add the partials in order -- per super-tile
-// (pair form) or per source split (per-target form) -- in FP64, and store the
-// gravity force G m_i sum under the sphere's id.  With a
-// perturber, its unsoftened pull G m_i M d/|d|^3 is added (FP64) and each
-// block stores the sum of its spheres' pulls (the reaction, reduced in block
-// order at the end of the step).
+// Sum of the partials of slot k over its rows q0 <= q < q1, in row order, FP64.
+// The rows a slot of tile T receives are: every row below m0 (a tile each), the
+// first row of each cut tile before T (the reaction of its targets), and from
+// tile T on every row.  Eight rows' loads are in flight.
 template <typename T>
+__device__ __forceinline__ void sum_rows(const T* __restrict__ part, size_t ns, int k, int q0,
+                                         int q1, int m0, int b, int segs, double g[3]) {
+  // rows of tile T and after start at m0 + b * segs, where b cut tiles precede T
+  auto row = [&](int q) {
+    return q < m0 ? q : (q < m0 + b ? m0 + (q - m0) * segs : m0 + b * segs + (q - m0 - b));
+  };
+  int q = q0;
+  for (; q + 8 <= q1; q += 8) {
+    T v[8][3];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) v[u][c] = part[((size_t)row(q + u) * 3 + c) * ns + k];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) g[c] += (double)v[u][c];
+  }
+  for (; q < q1; ++q)
+    for (int c = 0; c < 3; ++c) g[c] += (double)part[((size_t)row(q) * 3 + c) * ns + k];
+}
+
+// 64 sorted slots per block, four threads per slot: each adds a quarter of the
+// slot's rows -- per tile, source segment, super-tile, source split, or
+// level-2 subtree of the tree -- and the four sums are added in order, FP64.
+// (One thread per slot with three loads in flight took 5.3 us for 3 rows of
+// 3,000 spheres and 11.5 us for 26 rows of 13,001, a chain of memory
+// latencies.)  The gravity force G m_i sum is stored under the sphere's id.  With a
+// perturber, its unsoftened pull G m_i M d/|d|^3 is added and each block
+// stores the sum of its spheres' pulls (the reaction, reduced in a fixed order
+// at the end of the step).
 __global__ __launch_bounds__(kBlock) void k_grav_combine(const PileDev* __restrict__ piles,
-                                                         const WorkItem* __restrict__ wl) {
-  const WorkItem w = wl[blockIdx.x];
+                                                         const WorkItem* __restrict__ wl,
+                                                         int precision) {
+  __shared__ double red[4][3][64];
+  const WorkItem w = wl[blockIdx.x >> 2];
+  const int base = w.base + (int)(blockIdx.x & 3) * 64;
   const PileDev& P = piles[w.pile];
-  if (P.status != 0 || P.G == 0.0 || P.tree) return;
-  const int k = w.base + threadIdx.x;
-  const int ns = P.ns, nt = P.g_np;
+  const int ns = P.ns;
+  if (P.status != 0 || P.G == 0.0 || base >= ns) return;   // uniform over the block
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int k = base + lane;
+  double g[3] = {0.0, 0.0, 0.0};
+  if (k < ns) {
+    if (P.tree) {
+      constexpr int per = kTreeParts / 4;
+      sum_rows<double>(P.tpart, ns, k, wv * per, (wv + 1) * per, kTreeParts, 0, 1, g);
+    } else {
+      // super-tiles and source splits (g_m0 < 0): every row
+      const int m0 = P.g_m0 < 0 ? P.g_np : P.g_m0;
+      const int b = P.g_m0 < 0 ? 0 : max(0, k / P.g_tile - m0);
+      // the rows from the slot's own tile on are contiguous up to the last
+      const int n = m0 + b + (P.g_np - (m0 + b * P.g_segs));
+      const int q0 = (int)((int64_t)n * wv / 4), q1 = (int)((int64_t)n * (wv + 1) / 4);
+      if (precision == 1)
+        sum_rows<float>((const float*)P.gpart, ns, k, q0, q1, m0, b, P.g_segs, g);
+      else
+        sum_rows<double>((const double*)P.gpart, ns, k, q0, q1, m0, b, P.g_segs, g);
+    }
+  }
+  for (int c = 0; c < 3; ++c) red[wv][c][lane] = g[c];
+  __syncthreads();
+  if (wv != 0) return;
   double pull[3] = {0.0, 0.0, 0.0};
   if (k < ns) {
-    const T* __restrict__ part = (const T*)P.gpart;
-    double g[3] = {0.0, 0.0, 0.0};
-    for (int t = 0; t < nt; ++t)
-      for (int c = 0; c < 3; ++c) g[c] += (double)part[((size_t)t * 3 + c) * ns + k];
+    for (int c = 0; c < 3; ++c)
+      g[c] = ((red[0][c][lane] + red[1][c][lane]) + red[2][c][lane]) + red[3][c][lane];
     const uint32_t i = P.sidx[k];
-    const double gm = P.G * P.m[i];
+    const Rec64 r = ((const Rec64*)P.jrec)[k];
+    const double gm = P.G * r.m;
     for (int c = 0; c < 3; ++c) g[c] *= gm;
     if (P.pert_on) {
       const int nxt = P.parity ^ 1;
-      const double d[3] = {P.pert_r[nxt][0] - P.xs[k], P.pert_r[nxt][1] - P.xs[ns + k],
-                           P.pert_r[nxt][2] - P.xs[2 * ns + k]};
+      const double d[3] = {P.pert_r[nxt][0] - r.x, P.pert_r[nxt][1] - r.y, P.pert_r[nxt][2] - r.z};
       const double r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
       const double f = gm * P.pert_M / (r2 * sqrt(r2));
       for (int c = 0; c < 3; ++c) {
@@ -398,19 +460,11 @@ __global__ __launch_bounds__(kBlock) void k_grav_combine(const PileDev* __restri
     for (int c = 0; c < 3; ++c) P.gacc[c * ns + i] = g[c];
   }
   if (!P.pert_on) return;
-  // block sum of the pulls (fixed order: wave butterflies, then waves 0..3)
   for (int off = 32; off > 0; off >>= 1)
     for (int c = 0; c < 3; ++c) pull[c] += __shfl_xor(pull[c], off);
-  __shared__ double red[4][3];
-  const int wave = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0)
-    for (int c = 0; c < 3; ++c) red[wave][c] = pull[c];
-  __syncthreads();
-  if (threadIdx.x == 0)
-    for (int c = 0; c < 3; ++c)
-      P.ppart[(w.base / kBlock) * 3 + c] = ((red[0][c] + red[1][c]) + red[2][c]) + red[3][c];
+  if (lane == 0)
+    for (int c = 0; c < 3; ++c) P.ppart[(base / 64) * 3 + c] = pull[c];
 }
-
 
 }  // namespace
 
@@ -428,39 +482,96 @@ int gravity_tiles(int precision, int* tiles) {
   return 3;
 }
 
-void launch_gravity_records(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk,
-                            int precision) {
-  hipLaunchKernelGGL(k_grav_records, dim3(nblk), dim3(kBlock), 0, st, piles, wl, precision);
+// A block is one wave, so a small pile needs small tiles and short segments to
+// reach every SIMD, and a large one needs its last blocks short: with whole
+// tiles only, the launch ends on a few waves working alone.  Targets per lane
+// amortise the sources' rotation, so the tile grows with the pile.  Gravity
+// stage in us on one MI355X, whole default tiles (512 FP64, 1024 FP32) ->
+// the plan's, FP64 / FP32: 1,000 spheres 212 -> 14 / 475 -> 13; 3,000
+// 212 -> 20 / 617 -> 17; 6,000 214 -> 45 / 617 -> 34; 13,001 222 -> 96 /
+// 623 -> 70; 20,000 243 -> 201 / 626 -> 133; 32,000 480 -> 418 / 627 -> 266;
+// 50,000 1032 -> 967 / 1014 -> 582; 124,958 6402 -> 6305 / 3669 -> 3354;
+// 180,001 FP32 7185 -> 6769.  Neighbouring choices (half or twice the tile or
+// the segment) were within 5 % of these or slower.  A given tile keeps its
+// size and is cut by the same rule.
+GravPlan gravity_plan(int precision, int64_t ns, int tile) {
+  GravPlan p;
+  if (tile > 0) {
+    p.tile = tile;
+  } else if (ns <= 1500) {
+    p.tile = 64;
+  } else if (ns <= 4500) {
+    p.tile = 128;
+  } else if (ns <= 24000) {
+    p.tile = 256;
+  } else {
+    // FP32 tiles of 512 up to the largest pile that has kGravSlots of them
+    p.tile = precision == 1 && ns > 512 * kGravSlots ? 1024 : 512;
+  }
+  if (ns <= 40000) {
+    // every tile is cut
+    p.seg = std::min(p.tile, ns <= 8000 ? 64 : (ns <= 24000 ? 128 : 256));
+    p.m0 = p.seg < p.tile ? 0 : INT32_MAX;
+  } else {
+    // the last 8,192 slots' tiles are cut, and their blocks issued last
+    p.seg = std::max(64, p.tile / 4);
+    p.m0 = (int)std::max<int64_t>(0, (ns + p.tile - 1) / p.tile - 8192 / p.tile);
+  }
+  return p;
+}
+
+void launch_gravity_records(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk) {
+  hipLaunchKernelGGL(k_grav_records, dim3(nblk), dim3(kBlock), 0, st, piles, wl);
 }
 
 template <typename T, int IPT>
-static void tiles_launch(hipStream_t st, const PileDev* piles, const GravItem* gl, int n, bool soft,
-                         bool multi) {
-  if (multi) {
-    if (soft)
-      hipLaunchKernelGGL((k_grav_tiles<T, IPT, true, true>), dim3(n), dim3(64), 0, st, piles, gl);
-    else
-      hipLaunchKernelGGL((k_grav_tiles<T, IPT, false, true>), dim3(n), dim3(64), 0, st, piles, gl);
-  } else {
-    if (soft)
-      hipLaunchKernelGGL((k_grav_tiles<T, IPT, true, false>), dim3(n), dim3(64), 0, st, piles, gl);
-    else
-      hipLaunchKernelGGL((k_grav_tiles<T, IPT, false, false>), dim3(n), dim3(64), 0, st, piles, gl);
-  }
+static void pairs_launch(hipStream_t st, const PileDev* piles, const GravPair* gp, int n,
+                         bool soft) {
+  if (soft)
+    hipLaunchKernelGGL((k_grav_pairs<T, IPT, true>), dim3(n), dim3(64), 0, st, piles, gp);
+  else
+    hipLaunchKernelGGL((k_grav_pairs<T, IPT, false>), dim3(n), dim3(64), 0, st, piles, gp);
 }
 
-void launch_gravity_tiles(hipStream_t st, const PileDev* piles, const GravItem* gl, int nitems,
-                          int precision, bool softened, int tile, bool multi) {
+void launch_gravity_pairs(hipStream_t st, const PileDev* piles, const GravPair* gp, int nitems,
+                          int precision, bool softened, int tile) {
   if (nitems <= 0) return;
   const int ipt = tile / 64;
   if (precision == 1) {
-    if (ipt == 4) tiles_launch<float, 4>(st, piles, gl, nitems, softened, multi);
-    else if (ipt == 16) tiles_launch<float, 16>(st, piles, gl, nitems, softened, multi);
-    else tiles_launch<float, 8>(st, piles, gl, nitems, softened, multi);
+    if (ipt == 1) pairs_launch<float, 1>(st, piles, gp, nitems, softened);
+    else if (ipt == 2) pairs_launch<float, 2>(st, piles, gp, nitems, softened);
+    else if (ipt == 4) pairs_launch<float, 4>(st, piles, gp, nitems, softened);
+    else if (ipt == 8) pairs_launch<float, 8>(st, piles, gp, nitems, softened);
+    else pairs_launch<float, 16>(st, piles, gp, nitems, softened);
   } else {
-    if (ipt == 2) tiles_launch<double, 2>(st, piles, gl, nitems, softened, multi);
-    else if (ipt == 8) tiles_launch<double, 8>(st, piles, gl, nitems, softened, multi);
-    else tiles_launch<double, 4>(st, piles, gl, nitems, softened, multi);
+    if (ipt == 1) pairs_launch<double, 1>(st, piles, gp, nitems, softened);
+    else if (ipt == 2) pairs_launch<double, 2>(st, piles, gp, nitems, softened);
+    else if (ipt == 4) pairs_launch<double, 4>(st, piles, gp, nitems, softened);
+    else pairs_launch<double, 8>(st, piles, gp, nitems, softened);
+  }
+}
+
+template <typename T, int IPT>
+static void tiles_launch(hipStream_t st, const PileDev* piles, const GravItem* gl, int n,
+                         bool soft) {
+  if (soft)
+    hipLaunchKernelGGL((k_grav_tiles<T, IPT, true>), dim3(n), dim3(64), 0, st, piles, gl);
+  else
+    hipLaunchKernelGGL((k_grav_tiles<T, IPT, false>), dim3(n), dim3(64), 0, st, piles, gl);
+}
+
+void launch_gravity_tiles(hipStream_t st, const PileDev* piles, const GravItem* gl, int nitems,
+                          int precision, bool softened, int tile) {
+  if (nitems <= 0) return;
+  const int ipt = tile / 64;
+  if (precision == 1) {
+    if (ipt == 4) tiles_launch<float, 4>(st, piles, gl, nitems, softened);
+    else if (ipt == 16) tiles_launch<float, 16>(st, piles, gl, nitems, softened);
+    else tiles_launch<float, 8>(st, piles, gl, nitems, softened);
+  } else {
+    if (ipt == 2) tiles_launch<double, 2>(st, piles, gl, nitems, softened);
+    else if (ipt == 8) tiles_launch<double, 8>(st, piles, gl, nitems, softened);
+    else tiles_launch<double, 4>(st, piles, gl, nitems, softened);
   }
 }
 
@@ -496,10 +607,7 @@ void launch_gravity_split(hipStream_t st, const PileDev* piles, const GravItem* 
 
 void launch_gravity_combine(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk,
                             int precision) {
-  if (precision == 1)
-    hipLaunchKernelGGL(k_grav_combine<float>, dim3(nblk), dim3(kBlock), 0, st, piles, wl);
-  else
-    hipLaunchKernelGGL(k_grav_combine<double>, dim3(nblk), dim3(kBlock), 0, st, piles, wl);
+  hipLaunchKernelGGL(k_grav_combine, dim3(nblk * 4), dim3(kBlock), 0, st, piles, wl, precision);
 }
 
 }  // namespace dem

@@ -22,8 +22,6 @@ namespace {
 // ones and n - i - j twos sits at sym_index(n, i, j).
 // ---------------------------------------------------------------------------
 
-constexpr int kTreeSplit = 2;      // a group's walk is split over the 8^2 subtrees of level 2
-constexpr int kTreeParts = 1 << (3 * kTreeSplit);
 constexpr int kQ2 = 6, kQ3 = 12, kQ4 = 22;   // offsets of Q2, Q3, Q4 in a node's moments
 constexpr int kR2 = 0, kR3 = 6, kR4 = 16;    // offsets of M2, M3, M4 in a node's raw moments
 
@@ -604,48 +602,6 @@ __global__ __launch_bounds__(64) void k_tree_walk(const PileDev* __restrict__ pi
     for (int a = 0; a < 3; ++a) P.tpart[((size_t)part * 3 + a) * ns + k] = acc[a];
 }
 
-// One thread per sorted slot: the subtree parts in order, G m_i, and the
-// perturber's pull, exactly as the direct path's combine.
-__global__ __launch_bounds__(kBlock) void k_tree_combine(const PileDev* __restrict__ piles,
-                                                         const WorkItem* __restrict__ wl) {
-  const WorkItem w = wl[blockIdx.x];
-  const PileDev& P = piles[w.pile];
-  if (P.status != 0 || !P.tree || P.G == 0.0) return;
-  const int ns = P.ns;
-  const int k = w.base + threadIdx.x;
-  double pull[3] = {0.0, 0.0, 0.0};
-  if (k < ns) {
-    double acc[3] = {0.0, 0.0, 0.0};
-    for (int o = 0; o < kTreeParts; ++o)
-      for (int a = 0; a < 3; ++a) acc[a] += P.tpart[((size_t)o * 3 + a) * ns + k];
-    const uint32_t i = P.sidx[k];
-    const double gm = P.G * P.m[i];
-    for (int a = 0; a < 3; ++a) acc[a] *= gm;
-    if (P.pert_on) {
-      const int nxt = P.parity ^ 1;
-      const double d[3] = {P.pert_r[nxt][0] - P.xs[k], P.pert_r[nxt][1] - P.xs[ns + k],
-                           P.pert_r[nxt][2] - P.xs[2 * ns + k]};
-      const double r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
-      const double f = gm * P.pert_M / (r2 * sqrt(r2));
-      for (int a = 0; a < 3; ++a) {
-        pull[a] = f * d[a];
-        acc[a] += pull[a];
-      }
-    }
-    for (int a = 0; a < 3; ++a) P.gacc[a * ns + i] = acc[a];
-  }
-  if (!P.pert_on) return;
-  for (int off = 32; off > 0; off >>= 1)
-    for (int a = 0; a < 3; ++a) pull[a] += __shfl_xor(pull[a], off);
-  __shared__ double red[4][3];
-  const int wave = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0)
-    for (int a = 0; a < 3; ++a) red[wave][a] = pull[a];
-  __syncthreads();
-  if (threadIdx.x == 0)
-    for (int a = 0; a < 3; ++a)
-      P.ppart[(w.base / kBlock) * 3 + a] = ((red[0][a] + red[1][a]) + red[2][a]) + red[3][a];
-}
 }  // namespace
 
 void launch_tree(hipStream_t st, const PileDev* piles, WorkItem* const* wl_level,
@@ -669,7 +625,6 @@ void launch_tree(hipStream_t st, const PileDev* piles, WorkItem* const* wl_level
   if (any_order[1])
     hipLaunchKernelGGL(k_tree_walk<4>, dim3(walk_blocks), dim3(64), 0, st, piles, wl_sph,
                        n_sph_blk);
-  hipLaunchKernelGGL(k_tree_combine, dim3(n_sph_blk), dim3(kBlock), 0, st, piles, wl_sph);
 }
 
 }  // namespace dem

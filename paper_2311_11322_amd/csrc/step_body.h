@@ -415,21 +415,27 @@ __device__ __forceinline__ void reduce_tail(const PileDev& P, int A, const doubl
   }
 }
 
-// Per pile: commit the step (flip the ping-pong halves) unless the pile
-// failed during it, in which case its state stays at the failing step's
+// Per pile, by one wave: commit the step (flip the ping-pong halves) unless the
+// pile failed during it, in which case its state stays at the failing step's
 // start and the step index is recorded; the perturber's reaction and kick.
-__device__ __forceinline__ void finish_one(PileDev& P, int mode, double dt) {
+__device__ __forceinline__ void finish_one(PileDev& P, int lane, int mode, double dt) {
   if (P.status != 0) {
-    if (P.fail_step < 0) P.fail_step = P.step;
+    if (lane == 0 && P.fail_step < 0) P.fail_step = P.step;
     return;
   }
   const int nxt = P.parity ^ 1;
+  // reaction on the perturber: minus the pull on every sphere, each lane adding
+  // its share of the partials in order, then across the lanes
+  double f[3] = {0.0, 0.0, 0.0};
   if (P.pert_on) {
-    // reaction on the perturber: minus the pull on every sphere, summed over
-    // the per-block partials in block order; then its closing half kick
-    double f[3] = {0.0, 0.0, 0.0};
-    for (int b = 0; b < P.n_rblk; ++b)
+    for (int b = lane; b < (P.ns + 63) / 64; b += 64)
       for (int k = 0; k < 3; ++k) f[k] += P.ppart[b * 3 + k];
+    for (int off = 32; off > 0; off >>= 1)
+      for (int k = 0; k < 3; ++k) f[k] += __shfl_xor(f[k], off);
+  }
+  if (lane != 0) return;
+  if (P.pert_on) {
+    // its closing half kick
     for (int k = 0; k < 3; ++k) {
       const double a = -f[k] / P.pert_M;
       P.pert_a[nxt][k] = a;
