@@ -27,6 +27,7 @@ constexpr int kFusedThreads = 512;
 constexpr int kFusedWaves = kFusedThreads / 64;
 constexpr int kFusedLanes = kLanesSmall;          // lanes per sphere in the search
 constexpr int kFusedGroups = kFusedThreads / kFusedLanes;
+constexpr int kFusedSpheres = 128;                // spheres whose contacts are taken together
 
 // The pile's status as another thread of the workgroup may have set it.
 __device__ __forceinline__ int status_of(const PileDev& P) {
@@ -101,6 +102,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_fused(PileDev* __restrict__ p
   __shared__ uint32_t big_fill[2];
   __shared__ double red[kFusedWaves][kBbox];
   __shared__ uint32_t scan_sh[kFusedWaves + 1];
+  __shared__ ForceLds<kFusedThreads, kFusedSpheres> force_sh;
   PileDev& P = piles[plist[blockIdx.x]];
   const int tid = threadIdx.x;
   bool ok = status_of(P) == 0;            // a failed pile stays frozen
@@ -157,7 +159,8 @@ __global__ __launch_bounds__(kFusedThreads) void k_fused(PileDev* __restrict__ p
       // contact forces with the spring history
       const PairCtx<T> c = pair_ctx<T>(P, cp);
       bool bad = false;
-      for (int i = tid; i < P.ns; i += kFusedThreads) forces_one<T>(P, c, cp, (uint32_t)i, bad);
+      for (int i = 0; i < P.ns; i += kFusedSpheres)
+        forces_group<T, kFusedThreads, kFusedSpheres>(P, c, cp, i, force_sh, bad);
       if (bad) atomicOr(&P.status, kStUnstable);
       stage_sync();
       ok = status_of(P) == 0;
