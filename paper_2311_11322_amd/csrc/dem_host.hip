@@ -240,8 +240,8 @@ void plan_pile(PileDev& h, const Sizes& z, BufList& L) {
   L.add(&h.lo_off, ns + 1);
   L.add(&h.pair_j[0], cap);
   L.add(&h.pair_j[1], cap);
-  L.add(&h.hist[0], kHist * cap);
-  L.add(&h.hist[1], kHist * cap);
+  L.add(&h.hist[0], kHistRow * cap);
+  L.add(&h.hist[1], kHistRow * cap);
   L.add(&h.lo_nbr, cap);
 }
 
@@ -1350,6 +1350,14 @@ dem_status fetch_rows(dem_sim* s, const double* d, int k, int64_t n, double* hos
   return DEM_OK;
 }
 
+// The caller's history [n][kHist] as the device's rows.
+std::vector<double> hist_rows(const double* hist, int64_t n) {
+  std::vector<double> rows(size_t(kHistRow) * n, 0.0);
+  for (int64_t p = 0; p < n; ++p)
+    for (int c = 0; c < kHist; ++c) rows[p * kHistRow + c] = hist[p * kHist + c];
+  return rows;
+}
+
 dem_status store_rows(dem_sim* s, double* d, int k, int64_t n, const double* host, hipStream_t st) {
   std::vector<double> tmp(size_t(k) * n);
   for (int64_t i = 0; i < n; ++i)
@@ -1424,11 +1432,11 @@ dem_status dem_read_state(dem_sim* s, dem_state* out) {
         for (uint32_t p = off[i]; p < off[i + 1]; ++p)
           out->pair_keys[p] = (uint64_t(i) << 32) | pj[p];
     if (out->pair_hist && np) {
-      std::vector<double> hh(size_t(kHist) * h.cap_pairs);
+      std::vector<double> hh(size_t(kHistRow) * np);
       HIPCHK(s, hipMemcpyAsync(hh.data(), h.hist[cur], hh.size() * 8, hipMemcpyDeviceToHost, st));
       HIPCHK(s, hipStreamSynchronize(st));
       for (int64_t p = 0; p < np; ++p)
-        for (int c = 0; c < kHist; ++c) out->pair_hist[p * kHist + c] = hh[size_t(c) * h.cap_pairs + p];
+        for (int c = 0; c < kHist; ++c) out->pair_hist[p * kHist + c] = hh[p * kHistRow + c];
     }
   }
   return DEM_OK;
@@ -1472,13 +1480,9 @@ dem_status dem_restore_state(dem_sim* s, const dem_state* in) {
   HIPCHK(s, hipMemcpyAsync(h.up_off[cur], off.data(), (ns + 1) * 4, hipMemcpyHostToDevice, st));
   if (np) {
     HIPCHK(s, hipMemcpyAsync(h.pair_j[cur], pj.data(), np * 4, hipMemcpyHostToDevice, st));
-    std::vector<double> col(np);
-    for (int c = 0; c < kHist; ++c) {
-      for (int64_t p = 0; p < np; ++p) col[p] = in->pair_hist[p * kHist + c];
-      HIPCHK(s, hipMemcpyAsync(h.hist[cur] + size_t(c) * h.cap_pairs, col.data(), np * 8,
-                               hipMemcpyHostToDevice, st));
-      HIPCHK(s, hipStreamSynchronize(st));
-    }
+    const std::vector<double> rows = hist_rows(in->pair_hist, np);
+    HIPCHK(s, hipMemcpyAsync(h.hist[cur], rows.data(), rows.size() * 8, hipMemcpyHostToDevice, st));
+    HIPCHK(s, hipStreamSynchronize(st));
   }
   launch_fill_u32(st, h.cell_cnt, 0u, s->sz.cells + 1);
   h.status = 0;
@@ -1981,12 +1985,8 @@ dem_status dem_contact_forces(const dem_params* params, int64_t n, const double*
   HIPCHK(s, hipMemcpy(h.up_off[0], off.data(), (n + 1) * 4, hipMemcpyHostToDevice));
   if (n_old) {
     HIPCHK(s, hipMemcpy(h.pair_j[0], pj.data(), n_old * 4, hipMemcpyHostToDevice));
-    std::vector<double> col(n_old);
-    for (int c = 0; c < kHist; ++c) {
-      for (int64_t q = 0; q < n_old; ++q) col[q] = old_hist[q * kHist + c];
-      HIPCHK(s, hipMemcpy(h.hist[0] + size_t(c) * h.cap_pairs, col.data(), n_old * 8,
-                          hipMemcpyHostToDevice));
-    }
+    const std::vector<double> rows = hist_rows(old_hist, n_old);
+    HIPCHK(s, hipMemcpy(h.hist[0], rows.data(), rows.size() * 8, hipMemcpyHostToDevice));
   }
   launch_fill_u32(st, h.cell_cnt, 0u, s->sz.cells + 1);
   r = ensure_own_table(s);
@@ -2026,12 +2026,12 @@ dem_status dem_contact_forces(const dem_params* params, int64_t n, const double*
   if (cap > 0 && total > 0) {
     std::vector<uint32_t> pj1(total);
     HIPCHK(s, hipMemcpy(pj1.data(), h.pair_j[1], total * 4, hipMemcpyDeviceToHost));
-    std::vector<double> hh(size_t(kHist) * h.cap_pairs);
+    std::vector<double> hh(size_t(kHistRow) * total);
     HIPCHK(s, hipMemcpy(hh.data(), h.hist[1], hh.size() * 8, hipMemcpyDeviceToHost));
     for (int64_t i = 0; i < n; ++i)
       for (uint32_t q = off1[i]; q < off1[i + 1] && q < cap; ++q) {
         keys_out[q] = (uint64_t(i) << 32) | pj1[q];
-        for (int c = 0; c < kHist; ++c) hist_out[q * kHist + c] = hh[size_t(c) * h.cap_pairs + q];
+        for (int c = 0; c < kHist; ++c) hist_out[q * kHist + c] = hh[size_t(q) * kHistRow + c];
       }
   }
   return DEM_OK;

@@ -15,6 +15,7 @@ namespace dem {
 
 constexpr int kBlock = 256;        // threads per block (4 wave64)
 constexpr int kHist = 7;           // spring history per contact: xi_t[3], xi_r[3], xi_q
+constexpr int kHistRow = 8;        // doubles a contact's history takes: one 64 B row
 constexpr int kScanItems = 8;      // elements per thread in the batched scan
 constexpr int kScanChunk = kBlock * kScanItems;
 constexpr int kScanSingleItems = 4;   // segments of at most this many chunks: one-launch scan
@@ -190,7 +191,7 @@ struct PileDev {
   uint32_t* up_off[2];       // [ns + 1] CSR of contacts (i, j>i) by i
   uint32_t* lo_off;          // [ns + 1] CSR of contacts (j<i, i) by i
   uint32_t* pair_j[2];       // [cap]
-  double* hist[2];           // [kHist][cap]
+  double* hist[2];           // [cap][kHistRow]
   uint32_t* lo_nbr;          // [cap] lower neighbour ids
 };
 

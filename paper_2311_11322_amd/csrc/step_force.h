@@ -74,7 +74,7 @@ __device__ __forceinline__ V3<T> cap_spring(V3<T> xi, T k, T limit, bool* capped
 // What every contact of a pile's step reads from its table entry.
 template <typename T>
 struct PairCtx {
-  int ns, na, cap;
+  int ns, na;
   const uint32_t* __restrict__ up_off;
   const uint32_t* __restrict__ new_j;
   const uint32_t* __restrict__ old_off;
@@ -93,7 +93,6 @@ __device__ __forceinline__ PairCtx<T> pair_ctx(const PileDev& P, const ContactPa
   const int cur = P.parity, nxt = cur ^ 1;
   c.ns = P.ns;
   c.na = P.na;
-  c.cap = P.cap_pairs;
   c.up_off = P.up_off[nxt];
   c.new_j = P.pair_j[nxt];
   c.old_off = P.up_off[cur];
@@ -133,6 +132,26 @@ __device__ __forceinline__ Body<T> load_body(const PileDev& P, uint32_t i, int n
   return b;
 }
 
+// A contact's history is one aligned 64-byte row, moved as four 16-byte vectors:
+// the sphere that finds it in another sphere's run touches one line for it
+// instead of one per component.
+__device__ __forceinline__ void load_row(const double* __restrict__ h, uint32_t p,
+                                         double row[kHistRow]) {
+  const double2* __restrict__ s = reinterpret_cast<const double2*>(h + (size_t)p * kHistRow);
+#pragma unroll
+  for (int k = 0; k < kHistRow / 2; ++k) {
+    const double2 v = s[k];
+    row[2 * k] = v.x;
+    row[2 * k + 1] = v.y;
+  }
+}
+__device__ __forceinline__ void store_row(double* __restrict__ h, uint32_t p,
+                                          const double row[kHistRow]) {
+  double2* __restrict__ d = reinterpret_cast<double2*>(h + (size_t)p * kHistRow);
+#pragma unroll
+  for (int k = 0; k < kHistRow / 2; ++k) d[k] = make_double2(row[2 * k], row[2 * k + 1]);
+}
+
 // Spring history of contact (a, b) from the previous step, searched in a's
 // previous (sorted) upper run [o, o1); zero for a new contact.  The first four
 // keys are loaded together, so the usual short run costs one round of loads,
@@ -157,7 +176,9 @@ __device__ __forceinline__ void find_hist(const PairCtx<T>& c, uint32_t o, uint3
     p = o1;
   }
   if (p < o1) {
-    for (int k = 0; k < kHist; ++k) hs[k] = (T)c.old_h[(size_t)k * c.cap + p];
+    double row[kHistRow];
+    load_row(c.old_h, p, row);
+    for (int k = 0; k < kHist; ++k) hs[k] = (T)row[k];
   } else {
     for (int k = 0; k < kHist; ++k) hs[k] = (T)0;
   }
@@ -319,7 +340,7 @@ __device__ __forceinline__ void forces_group(const PileDev& P, const PairCtx<T>&
                                              const ContactParams& cp, int base,
                                              ForceLds<NT, S>& sh, bool& bad) {
   static_assert(S % 64 == 0 && 3 * S <= NT, "one thread per sphere and axis");
-  const int ns = c.ns, na = c.na, cap = c.cap, tid = threadIdx.x;
+  const int ns = c.ns, na = c.na, tid = threadIdx.x;
   const int n = min(S, ns - base);
   if (tid < 64) {
     // numbers of contacts, and their prefix sum (one wave)
@@ -375,7 +396,10 @@ __device__ __forceinline__ void forces_group(const PileDev& P, const PairCtx<T>&
         wall_contact<T>(P, c, cp, ba, (int)(b - (uint32_t)ns), hs, r);
       }
       if (!lower) {
-        for (int q = 0; q < kHist; ++q) c.new_h[(size_t)q * cap + p] = (double)r.hn[q];
+        double row[kHistRow];
+        for (int q = 0; q < kHist; ++q) row[q] = (double)r.hn[q];
+        row[kHist] = 0.0;
+        store_row(c.new_h, p, row);
         if (!isfinite((double)r.F.x) || !isfinite((double)r.F.y) || !isfinite((double)r.F.z))
           bad = true;
         if (cp.max_overlap_frac > 0.0 && r.delta > cp.max_overlap_frac * r.s_min) bad = true;
