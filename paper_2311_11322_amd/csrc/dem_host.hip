@@ -206,7 +206,6 @@ void plan_pile(PileDev& h, const Sizes& z, BufList& L) {
   L.add(&h.key, ns);
   L.add(&h.sidx, ns);
   L.add(&h.sidx_raw, ns);
-  L.add(&h.slot, ns);
   L.add(&h.xg, ns);
   L.add(&h.sid, ns);
   if (z.grav) {
@@ -232,12 +231,10 @@ void plan_pile(PileDev& h, const Sizes& z, BufList& L) {
   L.add(&h.grid, 1);
   L.add(&h.cell_cnt, z.cells + 1);          // + the cell of the big spheres
   L.add(&h.cell_start, z.cells + 2);
-  L.add(&h.run_cache, 2 * kRunCache * ns);
-  L.add(&h.cnt_up, ns);
-  L.add(&h.cnt_lo, ns);
-  L.add(&h.up_off[0], ns + 1);
-  L.add(&h.up_off[1], ns + 1);
-  L.add(&h.lo_off, ns + 1);
+  L.add(&h.runs, 16);
+  L.add(&h.up_run[0], ns);
+  L.add(&h.up_run[1], ns);
+  L.add(&h.lo_run, ns);
   L.add(&h.pair_j[0], cap);
   L.add(&h.pair_j[1], cap);
   L.add(&h.hist[0], kHistRow * cap);
@@ -302,10 +299,6 @@ struct Batch {
   ScanItem* item_cells = nullptr;
   uint32_t* sums_cells = nullptr;
   int n_seg_cells = 0, n_item_cells = 0, max_items_cells = 0;
-  ScanSeg* seg_pairs = nullptr;
-  ScanItem* item_pairs = nullptr;
-  uint32_t* sums_pairs = nullptr;
-  int n_seg_pairs = 0, n_item_pairs = 0, max_items_pairs = 0;
   hipGraphExec_t graph = nullptr;
   hipGraph_t graph_def = nullptr;
   // gravity runs on a second stream beside the contact search and forces
@@ -419,8 +412,8 @@ dem_status rebuild(Batch& b, hipStream_t st, dem_sim* errsim) {
   std::vector<GravPair> glg[kGravTileSizes];
   int tiles[kGravTileSizes] = {};
   int n_groups = 0;
-  std::vector<ScanSeg> sc, sp;
-  std::vector<ScanItem> ic, ip;
+  std::vector<ScanSeg> sc;
+  std::vector<ScanItem> ic;
   b.any_grav = false;
   b.any_rec32 = false;
   b.any_tree = false;
@@ -494,12 +487,10 @@ dem_status rebuild(Batch& b, hipStream_t st, dem_sim* errsim) {
     }
     // cell-count scan of this pile
     auto add_seg = [](std::vector<ScanSeg>& segs, std::vector<ScanItem>& items, const uint32_t* in,
-                      uint32_t* out0, uint32_t* out1, const int32_t* par, int64_t n) {
+                      uint32_t* out, int64_t n) {
       ScanSeg g{};
       g.in = in;
-      g.out_pp[0] = out0;
-      g.out_pp[1] = out1;
-      g.parity = par;
+      g.out = out;
       g.n = (int32_t)n;
       g.item0 = (int32_t)items.size();
       g.n_items = (int32_t)((n + kScanChunk - 1) / kScanChunk);
@@ -507,10 +498,7 @@ dem_status rebuild(Batch& b, hipStream_t st, dem_sim* errsim) {
       segs.push_back(g);
     };
     if (h.fused) continue;
-    PileDev* dentry = b.d_table + p;
-    add_seg(sc, ic, h.cell_cnt, h.cell_start, h.cell_start, nullptr, s->sz.cells + 1);
-    add_seg(sp, ip, h.cnt_up, h.up_off[0], h.up_off[1], &dentry->parity, h.ns);
-    add_seg(sp, ip, h.cnt_lo, h.lo_off, h.lo_off, nullptr, h.ns);
+    add_seg(sc, ic, h.cell_cnt, h.cell_start, s->sz.cells + 1);
   }
   HIPCHK(errsim, upload(b, &b.wl_agg, wa, st));
   HIPCHK(errsim, upload(b, &b.wl_grav, wgrav, st));
@@ -549,33 +537,27 @@ dem_status rebuild(Batch& b, hipStream_t st, dem_sim* errsim) {
   b.n_grav_groups = n_groups;
   HIPCHK(errsim, upload(b, &b.seg_cells, sc, st));
   HIPCHK(errsim, upload(b, &b.item_cells, ic, st));
-  HIPCHK(errsim, upload(b, &b.seg_pairs, sp, st));
-  HIPCHK(errsim, upload(b, &b.item_pairs, ip, st));
-  std::vector<uint32_t> zc(std::max<size_t>(ic.size(), 1), 0u), zp(std::max<size_t>(ip.size(), 1), 0u);
+  std::vector<uint32_t> zc(std::max<size_t>(ic.size(), 1), 0u);
   HIPCHK(errsim, upload(b, &b.sums_cells, zc, st));
-  HIPCHK(errsim, upload(b, &b.sums_pairs, zp, st));
   b.n_agg_blk = (int)wa.size();
   b.reduce_stage = tot_na >= kReduceStageMin;
   b.n_sph_blk = (int)wsph.size();
-  b.max_items_cells = b.max_items_pairs = 0;
+  b.max_items_cells = 0;
   for (const ScanSeg& g : sc) b.max_items_cells = std::max(b.max_items_cells, (int)g.n_items);
-  for (const ScanSeg& g : sp) b.max_items_pairs = std::max(b.max_items_pairs, (int)g.n_items);
   b.n_seg_cells = (int)sc.size();
   b.n_item_cells = (int)ic.size();
-  b.n_seg_pairs = (int)sp.size();
-  b.n_item_pairs = (int)ip.size();
   b.dirty = false;
   return DEM_OK;
 }
 
 // Kernel families of one step, in launch order (profiling names).
-constexpr int kNumStages = 16;
-constexpr int kStageGravity = 11;
-constexpr int kStageFusedA = 14;           // k_fused parts 1 and 3
-constexpr int kStageFusedB = 15;           // k_fused part 2
+constexpr int kNumStages = 14;
+constexpr int kStageGravity = 9;
+constexpr int kStageFusedA = 12;           // k_fused parts 1 and 3
+constexpr int kStageFusedB = 13;           // k_fused part 2
 const char* const kStageNames =
-    "integrate;reconstruct;grid;bin;scan_cells;scatter;cell_sort;search_count;"
-    "scan_pairs;search_write;forces;gravity;reduce;finish;fused_a;fused_b";
+    "integrate;reconstruct;grid;bin;scan_cells;scatter;cell_sort;search;"
+    "forces;gravity;reduce;finish;fused_a;fused_b";
 
 // Second stream and fork/join events of a batch (default priority).
 hipError_t ensure_side(Batch& b) {
@@ -656,18 +638,10 @@ void enqueue_pass_marked(Batch& b, hipStream_t st, int mode, Mark mark, bool ove
     (void)hipEventRecord(b.join_ev, b.side);
   }
   stage(7, st, staged, [&](hipStream_t s) {
-    launch_search(s, b.d_table, b.wl_sph, b.n_sph_blk, 0);
-    if (b.n_big_blk) launch_search_big(s, b.d_table, b.wl_big, b.n_big_blk, 0);
+    launch_search(s, b.d_table, b.wl_sph, b.n_sph_blk);
+    if (b.n_big_blk) launch_search_big(s, b.d_table, b.wl_big, b.n_big_blk);
   });
   stage(8, st, staged, [&](hipStream_t s) {
-    launch_scan(s, b.seg_pairs, b.n_seg_pairs, b.item_pairs, b.n_item_pairs, b.sums_pairs,
-                b.max_items_pairs);
-  });
-  stage(9, st, staged, [&](hipStream_t s) {
-    launch_search(s, b.d_table, b.wl_sph, b.n_sph_blk, 1);
-    if (b.n_big_blk) launch_search_big(s, b.d_table, b.wl_big, b.n_big_blk, 1);
-  });
-  stage(10, st, staged, [&](hipStream_t s) {
     launch_forces(s, b.d_table, b.wl_sph, b.n_sph_blk, b.cp, b.precision);
   });
   if (fork) (void)hipStreamWaitEvent(st, b.join_ev, 0);
@@ -675,10 +649,10 @@ void enqueue_pass_marked(Batch& b, hipStream_t st, int mode, Mark mark, bool ove
   stage(kStageFusedB, st, b.n_fused_g > 0, [&](hipStream_t s) {
     launch_fused(s, b.d_table, b.pl_fused_g, b.n_fused_g, b.cp, mode, 2, b.precision);
   });
-  stage(12, st, staged, [&](hipStream_t s) {
+  stage(10, st, staged, [&](hipStream_t s) {
     launch_reduce(s, b.d_table, b.wl_agg, b.n_agg_blk, b.cp, mode, b.reduce_stage);
   });
-  stage(13, st, staged, [&](hipStream_t s) { launch_finish(s, b.d_table, np, mode, b.cp.dt); });
+  stage(11, st, staged, [&](hipStream_t s) { launch_finish(s, b.d_table, np, mode, b.cp.dt); });
 }
 
 void enqueue_pass(Batch& b, hipStream_t st, int mode, bool overlap = false) {
@@ -861,6 +835,7 @@ dem_status alloc_pile(dem_sim* s, int64_t na, int64_t ns) {
   h.ns = (int32_t)ns;
   h.cap_pairs = (int32_t)s->sz.cap;
   h.bits = choose_bits(ns);
+  h.rows = s->sz.grav ? 0 : 1;
   h.periodic = s->prm.periodic ? 1 : 0;
   h.member_scan = s->tune.member_scan;
   h.member_read = s->tune.member_read;
@@ -908,6 +883,27 @@ dem_status alloc_pile(dem_sim* s, int64_t na, int64_t ns) {
   h.fail_step = -1;
   s->h = h;
   return DEM_OK;
+}
+
+// No contacts: empty runs of every sphere.
+void clear_runs(hipStream_t st, const PileDev& h, int64_t ns) {
+  for (int k = 0; k < 2; ++k)
+    launch_fill_u32(st, reinterpret_cast<uint32_t*>(h.up_run[k]), 0u, 2 * ns);
+  launch_fill_u32(st, reinterpret_cast<uint32_t*>(h.lo_run), 0u, 2 * ns);
+}
+
+// The runs of canonical keys listed sphere by sphere (first entry and length of
+// each sphere's contacts) and their partners.
+void runs_of_keys(const uint64_t* keys, int64_t np, int64_t ns, std::vector<uint2>& run,
+                  std::vector<uint32_t>& pj) {
+  run.assign(ns, make_uint2(0u, 0u));
+  pj.resize(std::max<int64_t>(np, 1));
+  for (int64_t p = 0; p < np; ++p) {
+    uint2& r = run[keys[p] >> 32];
+    if (r.y == 0) r.x = (uint32_t)p;
+    r.y++;
+    pj[p] = uint32_t(keys[p] & 0xffffffffu);
+  }
 }
 
 // Upload the host mirror into a batch table slot.
@@ -1034,12 +1030,14 @@ __global__ __launch_bounds__(kBlock) void k_noalloc_ingest(const double* __restr
 
 // One thread per sphere: its upper run as canonical keys, up to cap in all.
 __global__ __launch_bounds__(kBlock) void k_noalloc_keys(const uint32_t* __restrict__ off,
+                                                         const uint2* __restrict__ run,
                                                          const uint32_t* __restrict__ pj, int n,
                                                          uint64_t* __restrict__ out, int64_t cap) {
   const int i = blockIdx.x * kBlock + threadIdx.x;
   if (i >= n) return;
-  for (int64_t p = off[i], p1 = off[i + 1]; p < p1 && p < cap; ++p)
-    out[p] = (uint64_t(i) << 32) | pj[p];
+  const uint2 r = run[i];
+  for (int64_t e = 0, p = off[i]; e < r.y && p < cap; ++e, ++p)
+    out[p] = (uint64_t(i) << 32) | pj[r.x + e];
 }
 
 std::mutex g_scratch_mutex;
@@ -1084,6 +1082,7 @@ struct NoAllocPlan {
   ScanSeg* seg_pairs;
   ScanItem* item_pairs;
   uint32_t* sums_pairs;
+  uint32_t* key_off;                 // [n + 1] first key of each sphere's contacts
   int n_blk, n_item_cells, n_item_pairs, max_items_cells, max_items_pairs;
   int64_t cells;
   size_t bytes;
@@ -1099,35 +1098,32 @@ NoAllocPlan plan_noalloc(char* base, int64_t n, PileDev& h) {
   q.n_item_cells = (int)scan_items(q.cells + 1);
   q.max_items_cells = q.n_item_cells;
   q.max_items_pairs = (int)scan_items(n);
-  q.n_item_pairs = 2 * q.max_items_pairs;
+  q.n_item_pairs = q.max_items_pairs;
   q.hdr = L.take<NoAllocHdr>(1);
   q.entry = L.take<PileDev>(1);
   q.wl = L.take<WorkItem>(q.n_blk);
   q.seg_cells = L.take<ScanSeg>(1);
   q.item_cells = L.take<ScanItem>(q.n_item_cells);
   q.sums_cells = L.take<uint32_t>(q.n_item_cells);
-  q.seg_pairs = L.take<ScanSeg>(2);
+  q.seg_pairs = L.take<ScanSeg>(1);
   q.item_pairs = L.take<ScanItem>(q.n_item_pairs);
   q.sums_pairs = L.take<uint32_t>(q.n_item_pairs);
   h.r = L.take<double>(3 * n);
   h.key = L.take<uint32_t>(n);
   h.sidx = L.take<uint32_t>(n);
   h.sidx_raw = L.take<uint32_t>(n);
-  h.slot = L.take<uint32_t>(n);
   h.xg = L.take<SortedGeom>(n);
   h.sid = L.take<SortedId>(n);
   h.bpart = L.take<double>(kBbox * q.n_blk);
   h.grid = L.take<Grid>(1);
   h.cell_cnt = L.take<uint32_t>(q.cells + 1);
   h.cell_start = L.take<uint32_t>(q.cells + 2);
-  h.run_cache = L.take<uint32_t>(2 * kRunCache * n);
   h.cnt_up = L.take<uint32_t>(n);
-  h.cnt_lo = L.take<uint32_t>(n);
-  h.up_off[0] = L.take<uint32_t>(n + 1);
-  h.up_off[1] = L.take<uint32_t>(n + 1);
-  h.lo_off = L.take<uint32_t>(n + 1);
-  h.pair_j[0] = L.take<uint32_t>(kNoAllocMaxPairs);
-  h.pair_j[1] = L.take<uint32_t>(kNoAllocMaxPairs);
+  q.key_off = L.take<uint32_t>(n + 1);
+  h.runs = L.take<unsigned long long>(16);
+  h.up_run[0] = h.up_run[1] = L.take<uint2>(n);
+  h.lo_run = L.take<uint2>(n);
+  h.pair_j[0] = h.pair_j[1] = L.take<uint32_t>(kNoAllocMaxPairs);
   h.lo_nbr = L.take<uint32_t>(kNoAllocMaxPairs);
   q.bytes = L.off;
   return q;
@@ -1259,9 +1255,7 @@ dem_status dem_add_aggregates(dem_sim* s, int64_t n_agg, const int32_t* spa, con
     HIPCHK(s, hipMemcpyAsync(d_spin, agg_spin, n_agg * 24, hipMemcpyHostToDevice, str));
   }
   // zero the contact lists (empty history) and cell counts
-  launch_fill_u32(str, s->h.up_off[0], 0u, ns + 1);
-  launch_fill_u32(str, s->h.up_off[1], 0u, ns + 1);
-  launch_fill_u32(str, s->h.lo_off, 0u, ns + 1);
+  clear_runs(str, s->h, ns);
   launch_fill_u32(str, s->h.cell_cnt, 0u, s->sz.cells + 1);
   st = ensure_own_table(s);
   if (st != DEM_OK) return st;
@@ -1423,20 +1417,27 @@ dem_status dem_read_state(dem_sim* s, dem_state* out) {
   out->step = h.step;
   if (out->pair_keys || out->pair_hist) {
     const int64_t np = h.n_pairs;
-    std::vector<uint32_t> off(ns + 1), pj(std::max<int64_t>(np, 1));
-    HIPCHK(s, hipMemcpyAsync(off.data(), h.up_off[cur], (ns + 1) * 4, hipMemcpyDeviceToHost, st));
+    // the runs sphere by sphere are the canonical order
+    std::vector<uint2> run(ns);
+    std::vector<uint32_t> pj(std::max<int64_t>(np, 1));
+    HIPCHK(s, hipMemcpyAsync(run.data(), h.up_run[cur], ns * 8, hipMemcpyDeviceToHost, st));
     if (np) HIPCHK(s, hipMemcpyAsync(pj.data(), h.pair_j[cur], np * 4, hipMemcpyDeviceToHost, st));
     HIPCHK(s, hipStreamSynchronize(st));
-    if (out->pair_keys)
+    if (out->pair_keys) {
+      int64_t p = 0;
       for (int64_t i = 0; i < ns; ++i)
-        for (uint32_t p = off[i]; p < off[i + 1]; ++p)
-          out->pair_keys[p] = (uint64_t(i) << 32) | pj[p];
+        for (uint32_t e = run[i].x, e1 = e + run[i].y; e < e1; ++e)
+          out->pair_keys[p++] = (uint64_t(i) << 32) | pj[e];
+    }
     if (out->pair_hist && np) {
       std::vector<double> hh(size_t(kHistRow) * np);
       HIPCHK(s, hipMemcpyAsync(hh.data(), h.hist[cur], hh.size() * 8, hipMemcpyDeviceToHost, st));
       HIPCHK(s, hipStreamSynchronize(st));
-      for (int64_t p = 0; p < np; ++p)
-        for (int c = 0; c < kHist; ++c) out->pair_hist[p * kHist + c] = hh[p * kHistRow + c];
+      int64_t p = 0;
+      for (int64_t i = 0; i < ns; ++i)
+        for (uint32_t e = run[i].x, e1 = e + run[i].y; e < e1; ++e, ++p)
+          for (int c = 0; c < kHist; ++c)
+            out->pair_hist[p * kHist + c] = hh[(size_t)e * kHistRow + c];
     }
   }
   return DEM_OK;
@@ -1464,8 +1465,6 @@ dem_status dem_restore_state(dem_sim* s, const dem_state* in) {
   if (r == DEM_OK) r = store_rows(s, h.q[cur], 4, na, in->agg_quat, st);
   if (r == DEM_OK) r = store_rows(s, h.wb[cur], 3, na, in->agg_spin_body, st);
   if (r != DEM_OK) return r;
-  // contact list as CSR of the canonical keys
-  std::vector<uint32_t> off(ns + 1, 0), pj(std::max<int64_t>(np, 1));
   for (int64_t p = 0; p < np; ++p) {
     const uint64_t key = in->pair_keys[p];
     const int64_t i = int64_t(key >> 32), j = int64_t(key & 0xffffffffu);
@@ -1473,11 +1472,11 @@ dem_status dem_restore_state(dem_sim* s, const dem_state* in) {
     if (i < 0 || i >= ns || j <= i || j >= ns + h.n_walls ||
         (p > 0 && key <= in->pair_keys[p - 1]))
       return fail(s, DEM_ERR_INVALID_ARG, "pair keys must be canonical and sorted");
-    off[i + 1]++;
-    pj[p] = uint32_t(j);
   }
-  for (int64_t i = 0; i < ns; ++i) off[i + 1] += off[i];
-  HIPCHK(s, hipMemcpyAsync(h.up_off[cur], off.data(), (ns + 1) * 4, hipMemcpyHostToDevice, st));
+  std::vector<uint2> run;
+  std::vector<uint32_t> pj;
+  runs_of_keys(in->pair_keys, np, ns, run, pj);
+  HIPCHK(s, hipMemcpyAsync(h.up_run[cur], run.data(), ns * 8, hipMemcpyHostToDevice, st));
   if (np) {
     HIPCHK(s, hipMemcpyAsync(h.pair_j[cur], pj.data(), np * 4, hipMemcpyHostToDevice, st));
     const std::vector<double> rows = hist_rows(in->pair_hist, np);
@@ -1625,9 +1624,7 @@ dem_status dem_reserve_contacts(dem_sim* s, int32_t per_sphere) {
   copy(h.m, old.m, ns * 8);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) return fail(s, undo(DEM_ERR_DEVICE), hip_msg(e, "reserve copy"));
-  launch_fill_u32(st, h.up_off[0], 0u, ns + 1);
-  launch_fill_u32(st, h.up_off[1], 0u, ns + 1);
-  launch_fill_u32(st, h.lo_off, 0u, ns + 1);
+  clear_runs(st, h, ns);
   free_meta(s->own);
   e = put_entry(s, s->own.d_table, st);
   if (e != hipSuccess) return fail(s, undo(DEM_ERR_DEVICE), hip_msg(e, "reserve table"));
@@ -1766,25 +1763,25 @@ dem_status dem_find_contacts(const double* pos, const double* radius, const int3
               b.max_items_cells);
   launch_scatter(st, b.d_table, b.wl_sph, b.n_sph_blk);
   launch_cell_sort(st, b.d_table, b.wl_sph, b.n_sph_blk);
-  launch_search(st, b.d_table, b.wl_sph, b.n_sph_blk, 0);
-  launch_scan(st, b.seg_pairs, b.n_seg_pairs, b.item_pairs, b.n_item_pairs, b.sums_pairs,
-              b.max_items_pairs);
-  launch_search(st, b.d_table, b.wl_sph, b.n_sph_blk, 1);
+  launch_search(st, b.d_table, b.wl_sph, b.n_sph_blk);
   HIPCHK(s, hipGetLastError());
   PileDev tmp;
+  unsigned long long runs = 0;
   HIPCHK(s, hipMemcpyAsync(&tmp, b.d_table, sizeof(PileDev), hipMemcpyDeviceToHost, st));
-  std::vector<uint32_t> off(n + 1);
-  HIPCHK(s, hipMemcpyAsync(off.data(), h.up_off[1], (n + 1) * 4, hipMemcpyDeviceToHost, st));
+  HIPCHK(s, hipMemcpyAsync(&runs, h.runs, sizeof runs, hipMemcpyDeviceToHost, st));
+  std::vector<uint2> run(n);
+  HIPCHK(s, hipMemcpyAsync(run.data(), h.up_run[1], n * 8, hipMemcpyDeviceToHost, st));
   HIPCHK(s, hipStreamSynchronize(st));
-  const int64_t total = off[n];
+  const int64_t total = int64_t(runs >> 32);
   *n_out = total;
   if (tmp.status & kStCapacity) return fail(nullptr, DEM_ERR_CAPACITY, "more than 64 contacts per sphere");
   if (tmp.status != 0) return fail(nullptr, DEM_ERR_INVALID_ARG, "non-finite positions");
   std::vector<uint32_t> pj(std::max<int64_t>(total, 1));
   if (total) HIPCHK(s, hipMemcpy(pj.data(), h.pair_j[1], total * 4, hipMemcpyDeviceToHost));
-  for (int64_t i = 0; i < n; ++i)
-    for (uint32_t q = off[i]; q < off[i + 1] && q < cap; ++q)
-      pairs_out[q] = (uint64_t(i) << 32) | pj[q];
+  int64_t q = 0;
+  for (int64_t i = 0; i < n && q < cap; ++i)
+    for (uint32_t e = run[i].x, e1 = e + run[i].y; e < e1 && q < cap; ++e)
+      pairs_out[q++] = (uint64_t(i) << 32) | pj[e];
   return DEM_OK;
 }
 
@@ -1827,6 +1824,7 @@ dem_status dem_find_contacts_noalloc(const double* pos, const double* radius,
   h.ns = (int32_t)n;
   h.cap_pairs = (int32_t)kNoAllocMaxPairs;
   h.bits = choose_bits(n);
+  h.rows = 1;
   h.periodic = box ? 1 : 0;
   h.box = box ? box[0] : 0.0;
   h.n_rblk = q.n_blk;
@@ -1843,31 +1841,26 @@ dem_status dem_find_contacts_noalloc(const double* pos, const double* radius,
   for (int b = 0; b < q.n_blk; ++b) wl[b] = WorkItem{0, b * kBlock};
   ScanSeg sc{};
   sc.in = h.cell_cnt;
-  sc.out_pp[0] = sc.out_pp[1] = h.cell_start;
+  sc.out = h.cell_start;
   sc.n = (int32_t)(q.cells + 1);
   sc.n_items = q.n_item_cells;
   ScanItem ic[(((int64_t(1) << 18) + 1) + kScanChunk - 1) / kScanChunk];
   static_assert(sizeof(ic) / sizeof(ic[0]) >= (size_t)(((int64_t(1) << 18) + 1 + kScanChunk - 1) /
                                                         kScanChunk), "cell scan items");
   for (int c = 0; c < q.n_item_cells; ++c) ic[c] = ScanItem{0, c};
-  ScanSeg sp[2]{};
-  ScanItem ip[2 * ((kNoAllocMaxSpheres + kScanChunk - 1) / kScanChunk)];
-  const uint32_t* ins[2] = {h.cnt_up, h.cnt_lo};
-  uint32_t* outs[2] = {h.up_off[1], h.lo_off};
-  for (int g = 0; g < 2; ++g) {
-    sp[g].in = ins[g];
-    sp[g].out_pp[0] = sp[g].out_pp[1] = outs[g];
-    sp[g].n = (int32_t)n;
-    sp[g].item0 = g * q.max_items_pairs;
-    sp[g].n_items = q.max_items_pairs;
-    for (int c = 0; c < q.max_items_pairs; ++c) ip[g * q.max_items_pairs + c] = ScanItem{g, c};
-  }
+  ScanSeg sp{};
+  ScanItem ip[(kNoAllocMaxSpheres + kScanChunk - 1) / kScanChunk];
+  sp.in = h.cnt_up;
+  sp.out = q.key_off;
+  sp.n = (int32_t)n;
+  sp.n_items = q.max_items_pairs;
+  for (int c = 0; c < q.max_items_pairs; ++c) ip[c] = ScanItem{0, c};
   HIPCHK(nullptr, hipMemcpyAsync(q.entry, &h, sizeof h, hipMemcpyHostToDevice, st));
   HIPCHK(nullptr, hipMemcpyAsync(q.wl, wl, q.n_blk * sizeof(WorkItem), hipMemcpyHostToDevice, st));
   HIPCHK(nullptr, hipMemcpyAsync(q.seg_cells, &sc, sizeof sc, hipMemcpyHostToDevice, st));
   HIPCHK(nullptr, hipMemcpyAsync(q.item_cells, ic, q.n_item_cells * sizeof(ScanItem),
                                  hipMemcpyHostToDevice, st));
-  HIPCHK(nullptr, hipMemcpyAsync(q.seg_pairs, sp, sizeof sp, hipMemcpyHostToDevice, st));
+  HIPCHK(nullptr, hipMemcpyAsync(q.seg_pairs, &sp, sizeof sp, hipMemcpyHostToDevice, st));
   HIPCHK(nullptr, hipMemcpyAsync(q.item_pairs, ip, q.n_item_pairs * sizeof(ScanItem),
                                  hipMemcpyHostToDevice, st));
   // the cell counts start at zero (the scatter returns them to zero)
@@ -1879,22 +1872,22 @@ dem_status dem_find_contacts_noalloc(const double* pos, const double* radius,
   launch_scan(st, q.seg_cells, 1, q.item_cells, q.n_item_cells, q.sums_cells, q.max_items_cells);
   launch_scatter(st, t, q.wl, q.n_blk);
   launch_cell_sort(st, t, q.wl, q.n_blk);
-  launch_search(st, t, q.wl, q.n_blk, 0);
-  launch_scan(st, q.seg_pairs, 2, q.item_pairs, q.n_item_pairs, q.sums_pairs, q.max_items_pairs);
-  launch_search(st, t, q.wl, q.n_blk, 1);
+  launch_search(st, t, q.wl, q.n_blk);
   HIPCHK(nullptr, hipGetLastError());
   int32_t status = 0;
-  uint32_t total = 0;
+  unsigned long long runs = 0;
   HIPCHK(nullptr, hipMemcpyAsync(&status, &q.entry->status, sizeof status, hipMemcpyDeviceToHost, st));
-  HIPCHK(nullptr, hipMemcpyAsync(&total, h.up_off[1] + n, sizeof total, hipMemcpyDeviceToHost, st));
+  HIPCHK(nullptr, hipMemcpyAsync(&runs, h.runs, sizeof runs, hipMemcpyDeviceToHost, st));
   HIPCHK(nullptr, hipStreamSynchronize(st));
+  const int64_t total = int64_t(runs >> 32);
   *n_out = total;
   if (status & kStCapacity)
     return fail(nullptr, DEM_ERR_CAPACITY, "more contacts than the static scratch holds");
   if (status != 0) return fail(nullptr, DEM_ERR_INVALID_ARG, "non-finite positions");
   if (cap > 0 && total > 0) {
-    hipLaunchKernelGGL(k_noalloc_keys, dim3(q.n_blk), dim3(kBlock), 0, st, h.up_off[1], h.pair_j[1],
-                       (int)n, pairs_out, cap);
+    launch_scan(st, q.seg_pairs, 1, q.item_pairs, q.n_item_pairs, q.sums_pairs, q.max_items_pairs);
+    hipLaunchKernelGGL(k_noalloc_keys, dim3(q.n_blk), dim3(kBlock), 0, st, q.key_off, h.up_run[1],
+                       h.pair_j[1], (int)n, pairs_out, cap);
     HIPCHK(nullptr, hipGetLastError());
     HIPCHK(nullptr, hipStreamSynchronize(st));
   }
@@ -1976,13 +1969,10 @@ dem_status dem_contact_forces(const dem_params* params, int64_t n, const double*
   HIPCHK(s, hipMemcpy(h.agg, agg, n * 4, hipMemcpyHostToDevice));
   HIPCHK(s, hipMemcpy(h.M, agg_mass, n_agg * 8, hipMemcpyHostToDevice));
   // the previous contact list (parity 0) with its spring history
-  std::vector<uint32_t> off(n + 1, 0), pj(std::max<int64_t>(n_old, 1));
-  for (int64_t q = 0; q < n_old; ++q) {
-    off[(old_keys[q] >> 32) + 1]++;
-    pj[q] = uint32_t(old_keys[q] & 0xffffffffu);
-  }
-  for (int64_t i = 0; i < n; ++i) off[i + 1] += off[i];
-  HIPCHK(s, hipMemcpy(h.up_off[0], off.data(), (n + 1) * 4, hipMemcpyHostToDevice));
+  std::vector<uint2> run;
+  std::vector<uint32_t> pj;
+  runs_of_keys(old_keys, n_old, n, run, pj);
+  HIPCHK(s, hipMemcpy(h.up_run[0], run.data(), n * 8, hipMemcpyHostToDevice));
   if (n_old) {
     HIPCHK(s, hipMemcpy(h.pair_j[0], pj.data(), n_old * 4, hipMemcpyHostToDevice));
     const std::vector<double> rows = hist_rows(old_hist, n_old);
@@ -2003,20 +1993,18 @@ dem_status dem_contact_forces(const dem_params* params, int64_t n, const double*
               b.max_items_cells);
   launch_scatter(st, b.d_table, b.wl_sph, b.n_sph_blk);
   launch_cell_sort(st, b.d_table, b.wl_sph, b.n_sph_blk);
-  launch_search(st, b.d_table, b.wl_sph, b.n_sph_blk, 0);
-  if (b.n_big_blk) launch_search_big(st, b.d_table, b.wl_big, b.n_big_blk, 0);
-  launch_scan(st, b.seg_pairs, b.n_seg_pairs, b.item_pairs, b.n_item_pairs, b.sums_pairs,
-              b.max_items_pairs);
-  launch_search(st, b.d_table, b.wl_sph, b.n_sph_blk, 1);
-  if (b.n_big_blk) launch_search_big(st, b.d_table, b.wl_big, b.n_big_blk, 1);
+  launch_search(st, b.d_table, b.wl_sph, b.n_sph_blk);
+  if (b.n_big_blk) launch_search_big(st, b.d_table, b.wl_big, b.n_big_blk);
   launch_forces(st, b.d_table, b.wl_sph, b.n_sph_blk, b.cp, b.precision);
   HIPCHK(s, hipGetLastError());
   PileDev tmp;
   HIPCHK(s, hipMemcpyAsync(&tmp, b.d_table, sizeof(PileDev), hipMemcpyDeviceToHost, st));
-  std::vector<uint32_t> off1(n + 1);
-  HIPCHK(s, hipMemcpyAsync(off1.data(), h.up_off[1], (n + 1) * 4, hipMemcpyDeviceToHost, st));
+  std::vector<uint2> run1(n);
+  unsigned long long runs = 0;
+  HIPCHK(s, hipMemcpyAsync(run1.data(), h.up_run[1], n * 8, hipMemcpyDeviceToHost, st));
+  HIPCHK(s, hipMemcpyAsync(&runs, h.runs, sizeof runs, hipMemcpyDeviceToHost, st));
   HIPCHK(s, hipStreamSynchronize(st));
-  const int64_t total = off1[n];
+  const int64_t total = int64_t(runs >> 32);
   *n_out = total;
   if (tmp.status & kStCapacity) return fail(nullptr, DEM_ERR_CAPACITY, "contact capacity exceeded");
   if (tmp.status != 0) return fail(nullptr, DEM_ERR_UNSTABLE, "non-finite force or bad positions");
@@ -2028,10 +2016,11 @@ dem_status dem_contact_forces(const dem_params* params, int64_t n, const double*
     HIPCHK(s, hipMemcpy(pj1.data(), h.pair_j[1], total * 4, hipMemcpyDeviceToHost));
     std::vector<double> hh(size_t(kHistRow) * total);
     HIPCHK(s, hipMemcpy(hh.data(), h.hist[1], hh.size() * 8, hipMemcpyDeviceToHost));
-    for (int64_t i = 0; i < n; ++i)
-      for (uint32_t q = off1[i]; q < off1[i + 1] && q < cap; ++q) {
-        keys_out[q] = (uint64_t(i) << 32) | pj1[q];
-        for (int c = 0; c < kHist; ++c) hist_out[q * kHist + c] = hh[size_t(q) * kHistRow + c];
+    int64_t q = 0;
+    for (int64_t i = 0; i < n && q < cap; ++i)
+      for (uint32_t e = run1[i].x, e1 = e + run1[i].y; e < e1 && q < cap; ++e, ++q) {
+        keys_out[q] = (uint64_t(i) << 32) | pj1[e];
+        for (int c = 0; c < kHist; ++c) hist_out[q * kHist + c] = hh[size_t(e) * kHistRow + c];
       }
   }
   return DEM_OK;

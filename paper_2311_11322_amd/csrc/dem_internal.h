@@ -19,7 +19,7 @@ constexpr int kHistRow = 8;        // doubles a contact's history takes: one 64 
 constexpr int kScanItems = 8;      // elements per thread in the batched scan
 constexpr int kScanChunk = kBlock * kScanItems;
 constexpr int kScanSingleItems = 4;   // segments of at most this many chunks: one-launch scan
-constexpr int kRunCache = 16;      // contact ids per run kept by the search's find pass
+constexpr int kRunLds = 16;        // contact ids per sphere the search keeps in LDS
 constexpr int kMaxBig = 64;        // big spheres per pile searched separately
 constexpr int kBigRun = 2048;      // contacts per run of a big sphere (LDS sort)
 constexpr int kMom = 40;           // per tree node: M, c[3], sum m e, sum m e^2, traceless
@@ -82,7 +82,7 @@ struct PileDev {
   // sizes (host-set)
   int32_t na, ns;
   int32_t cap_pairs;         // capacity of each contact list (upper and lower)
-  int32_t bits;              // cell table is (1 << bits)^3 Morton codes
+  int32_t bits;              // cell table is (1 << bits)^3 cells
   int32_t periodic;
   int32_t g_tile;            // gravity tile (slots per tile)
   int32_t g_nt;              // gravity tiles
@@ -111,7 +111,7 @@ struct PileDev {
                              // to reconstruct them from; stateless test hooks)
   int32_t fused;             // 1: the whole step runs in one workgroup (k_fused); the staged
                              // kernels launched over every pile skip it
-  int32_t pad6;
+  int32_t rows;              // 1: cell keys are row-major (no gravity), 0: Morton
   // uniform field and container walls (host-set)
   int32_t n_walls;
   int32_t pad3;
@@ -171,9 +171,8 @@ struct PileDev {
   double* F;                 // [3][ns] contact force (gravity is added by the reduction)
   double* tau;               // [3][ns] contact torque about the centre
   uint32_t* key;             // [ns] Morton cell code
-  uint32_t* sidx;            // [ns] sphere at sorted slot
+  uint32_t* sidx;            // [ns] sphere at sorted slot (piles with gravity)
   uint32_t* sidx_raw;        // [ns] sphere at slot, in atomic arrival order
-  uint32_t* slot;            // [ns] sorted slot of sphere
   SortedGeom* xg;            // [ns] sorted x, y, z, radius (search)
   SortedId* sid;             // [ns] sorted aggregate id and sphere id
   void* jrec;                // gravity records in sorted order (64 B, FP64)
@@ -185,14 +184,16 @@ struct PileDev {
   Grid* grid;
   uint32_t* cell_cnt;        // [cells]
   uint32_t* cell_start;      // [cells + 1]
-  uint32_t* run_cache;       // [2][ns][kRunCache] sorted upper / lower runs by slot
-  uint32_t* cnt_up;          // [ns]
-  uint32_t* cnt_lo;          // [ns]
-  uint32_t* up_off[2];       // [ns + 1] CSR of contacts (i, j>i) by i
-  uint32_t* lo_off;          // [ns + 1] CSR of contacts (j<i, i) by i
-  uint32_t* pair_j[2];       // [cap]
-  double* hist[2];           // [cap][kHistRow]
-  uint32_t* lo_nbr;          // [cap] lower neighbour ids
+  // contacts listed so far by the search of this evaluation: upper in the
+  // high word, lower in the low (reset with the cell grid; on a line of its
+  // own, as every block of the search adds to it)
+  unsigned long long* runs;
+  uint2* up_run[2];          // [ns] first entry and length of sphere i's contacts (i, j > i)
+  uint2* lo_run;             // [ns] the same of its contacts (j, i), j < i
+  uint32_t* cnt_up;          // [ns] upper run lengths, or NULL (stateless searches only)
+  uint32_t* pair_j[2];       // [cap] partners j of the upper runs, each run sorted
+  double* hist[2];           // [cap][kHistRow] spring history beside pair_j
+  uint32_t* lo_nbr;          // [cap] lower neighbour ids, each run sorted
 };
 
 // One block of a per-element kernel: pile p, elements base .. base+255.
@@ -221,12 +222,9 @@ struct GravItem {
 };
 
 // One segment of the batched exclusive scan (out[n] receives the total).
-// When parity is set, the output is out_pp[*parity ^ 1] (the next half of a
-// ping-pong pair), else out_pp[0].
 struct ScanSeg {
   const uint32_t* in;
-  uint32_t* out_pp[2];
-  const int32_t* parity;
+  uint32_t* out;
   int32_t n;
   int32_t item0;             // first work item of this segment
   int32_t n_items;
@@ -250,9 +248,8 @@ void launch_grid(hipStream_t st, const PileDev* piles, int n_piles, int mode, do
 void launch_bin(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk);
 void launch_scatter(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk);
 void launch_cell_sort(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk);
-void launch_search(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk, int write);
-void launch_search_big(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk,
-                       int write);
+void launch_search(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk);
+void launch_search_big(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk);
 void launch_forces(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk,
                    ContactParams cp, int precision);
 // Gravity: the per-slot combine covers every pile (the tree's included); the
@@ -299,8 +296,8 @@ constexpr int kGravSplits = 16;
 // 6.7, 6.4 ms).
 constexpr int kSplitIpt64 = 2, kSplitIpt32 = 16;
 constexpr int64_t kSymPartialMax = int64_t(64) << 30;
-// Spheres in one search launch from which each sphere gets four lanes
-// instead of eight.
+// Spheres in one search launch from which each sphere gets one lane instead
+// of eight.
 constexpr int64_t kSearchLargeLaunch = 32768;
 void launch_reduce(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk,
                    ContactParams cp, int mode, bool stage);
@@ -381,11 +378,11 @@ __device__ __forceinline__ uint32_t morton3(uint32_t x, uint32_t y, uint32_t z) 
   return spread3(x) | (spread3(y) << 1) | (spread3(z) << 2);
 }
 
-// Cell key for per-axis bit counts b: with m = min(b), the Morton code of
+// Morton cell key for per-axis bit counts b: with m = min(b), the Morton code of
 // the low m bits of each coordinate (a block of 2^m cells per axis), then the
 // block's row-major index above it -- a bijection onto [0, 2^(bx+by+bz)),
 // and the plain Morton code when the counts are equal.
-__device__ __forceinline__ uint32_t cell_key(int cx, int cy, int cz, const int32_t nbits[3]) {
+__device__ __forceinline__ uint32_t morton_key(int cx, int cy, int cz, const int32_t nbits[3]) {
   const int m = min(nbits[0], min(nbits[1], nbits[2]));
   const uint32_t lo = (1u << m) - 1u;
   const uint32_t blk = ((uint32_t)cx >> m) + (((uint32_t)cy >> m) << (nbits[0] - m)) +

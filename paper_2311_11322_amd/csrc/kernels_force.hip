@@ -38,7 +38,6 @@ __global__ __launch_bounds__(kBlock) void k_forces(PileDev* __restrict__ piles,
   __syncthreads();
   if (base >= P.ns || failed) return;
   const PairCtx<T> c = pair_ctx<T>(P, cp);
-  if (c.n_pairs > (uint32_t)P.cap_pairs) return;
   bool bad = false;
   forces_group<T, kBlock, kForceSpheres>(P, c, cp, base, sh, bad);
   if (bad) atomicOr(&P.status, kStUnstable);

@@ -76,17 +76,33 @@ __device__ void block_scan(const uint32_t* __restrict__ in, uint32_t* __restrict
   __syncthreads();                        // sh is reused by the next scan
 }
 
-// The search of every sphere (find or write pass): lane groups over the
-// sorted slots, then the big spheres with the whole workgroup.
-__device__ void search_all(PileDev& P, int write, uint32_t (*buf_up)[kRunLds],
-                           uint32_t (*buf_lo)[kRunLds], uint32_t (*fill)[2], uint32_t* big_up,
-                           uint32_t* big_lo, uint32_t* big_fill) {
+// The search of every sphere: lane groups over the sorted slots, each taking
+// room for its runs from the workgroup's counter, then the big spheres with the
+// whole workgroup.  total: LDS, the number of contacts listed so far.
+__device__ void search_all(PileDev& P, SearchLds<kFusedLanes, kFusedThreads>& sh,
+                           unsigned long long* total, uint32_t* big_up, uint32_t* big_lo,
+                           uint32_t* big_fill) {
   const int tid = threadIdx.x, grp = tid / kFusedLanes, lane = tid % kFusedLanes;
-  for (int k = grp; k < P.ns; k += kFusedGroups)
-    search_slot<kFusedLanes>(P, k, lane, write, buf_up[grp], buf_lo[grp], fill[grp]);
+  const unsigned long long cap = (unsigned long long)P.cap_pairs;
+  for (int k = grp; k < P.ns - P.n_big; k += kFusedGroups) {
+    const uint32_t i = P.sid[k].id;
+    uint32_t nup, nlo;
+    find_slot(P, k, i, grp, lane, sh, nup, nlo);
+    unsigned long long at = 0;
+    if (lane == 0)
+      at = atomicAdd(total, ((unsigned long long)nup << 32) | (unsigned long long)nlo);
+    at = __shfl(at, (tid & 63) - lane);
+    if ((at >> 32) + nup <= cap && (at & 0xffffffffull) + nlo <= cap)
+      store_runs(P, k, i, grp, lane, sh, nup, nlo, (uint32_t)(at >> 32), (uint32_t)at);
+    else if (lane == 0)
+      atomicOr(&P.status, kStCapacity);
+  }
+  stage_sync();
+  if (tid == 0) *P.runs = *total;
+  stage_sync();
   for (int kb = 0; kb < P.n_big; ++kb) {
-    stage_sync();                         // runs written; the previous sphere's LDS read
-    search_big_one(P, kb, write, tid, kFusedThreads, big_up, big_lo, big_fill);
+    search_big_one(P, kb, tid, kFusedThreads, big_up, big_lo, big_fill);
+    stage_sync();                         // runs written, the LDS read
   }
 }
 
@@ -94,12 +110,11 @@ template <typename T>
 __global__ __launch_bounds__(kFusedThreads) void k_fused(PileDev* __restrict__ piles,
                                                          const int32_t* __restrict__ plist,
                                                          ContactParams cp, int mode, int part) {
-  __shared__ uint32_t buf_up[kFusedGroups][kRunLds];
-  __shared__ uint32_t buf_lo[kFusedGroups][kRunLds];
-  __shared__ uint32_t fill[kFusedGroups][2];
+  __shared__ SearchLds<kFusedLanes, kFusedThreads> search_sh;
   __shared__ uint32_t big_up[kBigRun];
   __shared__ uint32_t big_lo[kBigRun];
-  __shared__ uint32_t big_fill[2];
+  __shared__ uint32_t big_fill[4];
+  __shared__ unsigned long long run_total;
   __shared__ double red[kFusedWaves][kBbox];
   __shared__ uint32_t scan_sh[kFusedWaves + 1];
   __shared__ ForceLds<kFusedThreads, kFusedSpheres> force_sh;
@@ -136,6 +151,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_fused(PileDev* __restrict__ p
     }
     if (ok) {
       // counting sort of the cell keys
+      if (tid == 0) run_total = 0ull;
       for (int i = tid; i < P.ns; i += kFusedThreads) bin_one(P, i);
       stage_sync();
       block_scan(P.cell_cnt, P.cell_start, (1 << (3 * P.bits)) + 1, scan_sh);
@@ -144,15 +160,8 @@ __global__ __launch_bounds__(kFusedThreads) void k_fused(PileDev* __restrict__ p
       stage_sync();
       for (int k = tid; k < P.ns; k += kFusedThreads) cell_sort_one(P, k);
       stage_sync();
-      // contact search: counts, offsets, runs
-      search_all(P, 0, buf_up, buf_lo, fill, big_up, big_lo, big_fill);
-      stage_sync();
-      const int nxt = P.parity ^ 1;
-      block_scan(P.cnt_up, P.up_off[nxt], P.ns, scan_sh);
-      block_scan(P.cnt_lo, P.lo_off, P.ns, scan_sh);
-      stage_sync();
-      search_all(P, 1, buf_up, buf_lo, fill, big_up, big_lo, big_fill);
-      stage_sync();
+      // contact search (the counter was cleared before the last barriers)
+      search_all(P, search_sh, &run_total, big_up, big_lo, big_fill);
       ok = status_of(P) == 0;
     }
     if (ok) {

@@ -1,7 +1,6 @@
 // kernels_scan.hip -- batched exclusive prefix sum of uint32 arrays.
 //
-// Many independent segments (the cell counts and contact counts of every
-// pile) are scanned by the same two launches: per-chunk totals, then the
+// Many independent segments (the cell counts of every pile) are scanned by the same two launches: per-chunk totals, then the
 // chunk-local scans, each chunk adding up the totals before it in its
 // segment; or, when every segment is short, by one launch with a block per
 // segment.  out[n] of each segment receives its total.
@@ -103,7 +102,7 @@ __global__ __launch_bounds__(kBlock) void k_scan_down(const ScanSeg* __restrict_
                                                       const uint32_t* __restrict__ sums) {
   const ScanItem it = items[blockIdx.x];
   const ScanSeg sg = segs[it.seg];
-  uint32_t* __restrict__ out = sg.parity ? sg.out_pp[*sg.parity ^ 1] : sg.out_pp[0];
+  uint32_t* __restrict__ out = sg.out;
   // the chunk's elements and the earlier chunks' totals are loaded before
   // the first barrier, so the two loads are in flight together
   const int64_t base = (int64_t)it.chunk * kScanChunk + threadIdx.x * kScanItems;
@@ -126,7 +125,7 @@ __global__ __launch_bounds__(kBlock) void k_scan_down(const ScanSeg* __restrict_
 // running total (one launch; for batches whose segments are all short).
 __global__ __launch_bounds__(kBlock) void k_scan_single(const ScanSeg* __restrict__ segs) {
   const ScanSeg sg = segs[blockIdx.x];
-  uint32_t* __restrict__ out = sg.parity ? sg.out_pp[*sg.parity ^ 1] : sg.out_pp[0];
+  uint32_t* __restrict__ out = sg.out;
   uint32_t carry = 0;
   for (int c = 0; c < sg.n_items; ++c) {
     const int64_t base = (int64_t)c * kScanChunk + threadIdx.x * kScanItems;

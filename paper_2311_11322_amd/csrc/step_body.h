@@ -201,6 +201,7 @@ __device__ __forceinline__ void reconstruct_one(const PileDev& P, int i, const d
 // centre of mass when that is smaller.
 __device__ __forceinline__ void grid_from_vals(PileDev& P, double vals[kBbox], int mode,
                                                double dt) {
+  *P.runs = 0ull;                      // the search of this evaluation starts
   // written in place: a local Grid (its wall arrays indexed by a count
   // known only at run time) would live in scratch memory
   Grid& g = *P.grid;
@@ -442,7 +443,7 @@ __device__ __forceinline__ void finish_one(PileDev& P, int lane, int mode, doubl
       if (mode == kModeStep) P.pert_v[nxt][k] += 0.5 * dt * a;
     }
   }
-  P.n_pairs = P.up_off[nxt][P.ns];
+  P.n_pairs = (uint32_t)(__hip_atomic_load(P.runs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 32);
   P.parity = nxt;
   if (mode == kModeStep) P.step += 1;
 }

@@ -75,13 +75,12 @@ __device__ __forceinline__ V3<T> cap_spring(V3<T> xi, T k, T limit, bool* capped
 template <typename T>
 struct PairCtx {
   int ns, na;
-  const uint32_t* __restrict__ up_off;
+  const uint2* __restrict__ up_run;
   const uint32_t* __restrict__ new_j;
-  const uint32_t* __restrict__ old_off;
+  const uint2* __restrict__ old_run;
   const uint32_t* __restrict__ old_j;
   const double* __restrict__ old_h;
   double* __restrict__ new_h;
-  uint32_t n_pairs;
   int periodic;
   double L;
   T h, kn, kt, kr, kq;
@@ -93,13 +92,12 @@ __device__ __forceinline__ PairCtx<T> pair_ctx(const PileDev& P, const ContactPa
   const int cur = P.parity, nxt = cur ^ 1;
   c.ns = P.ns;
   c.na = P.na;
-  c.up_off = P.up_off[nxt];
+  c.up_run = P.up_run[nxt];
   c.new_j = P.pair_j[nxt];
-  c.old_off = P.up_off[cur];
+  c.old_run = P.up_run[cur];
   c.old_j = P.pair_j[cur];
   c.old_h = P.hist[cur];
   c.new_h = P.hist[nxt];
-  c.n_pairs = P.up_off[nxt][P.ns];
   c.periodic = P.periodic;
   c.L = P.box;
   c.h = (T)cp.dt;
@@ -153,13 +151,14 @@ __device__ __forceinline__ void store_row(double* __restrict__ h, uint32_t p,
 }
 
 // Spring history of contact (a, b) from the previous step, searched in a's
-// previous (sorted) upper run [o, o1); zero for a new contact.  The first four
+// previous (sorted) upper run; zero for a new contact.  The first four
 // keys are loaded together, so the usual short run costs one round of loads,
 // not a chain.
 template <typename T>
-__device__ __forceinline__ void find_hist(const PairCtx<T>& c, uint32_t o, uint32_t o1, uint32_t b,
+__device__ __forceinline__ void find_hist(const PairCtx<T>& c, uint32_t a, uint32_t b,
                                           T hs[kHist]) {
-  const uint32_t n = o1 - o;
+  const uint2 run = c.old_run[a];
+  const uint32_t o = run.x, n = run.y, o1 = o + n;
   uint32_t kk[4];
 #pragma unroll
   for (int u = 0; u < 4; ++u) kk[u] = (uint32_t)u < n ? c.old_j[o + u] : 0xffffffffu;
@@ -349,12 +348,11 @@ __device__ __forceinline__ void forces_group(const PileDev& P, const PairCtx<T>&
       const int l = q + tid, i = base + l;
       uint32_t nc = 0;
       if (l < n) {
-        const uint32_t l0 = P.lo_off[i], l1 = P.lo_off[i + 1];
-        const uint32_t u0 = c.up_off[i], u1 = c.up_off[i + 1];
-        sh.lo0[l] = l0;
-        sh.up0[l] = u0;
-        sh.nlo[l] = l1 - l0;
-        nc = (l1 - l0) + (u1 - u0);
+        const uint2 lo = P.lo_run[i], up = c.up_run[i];
+        sh.lo0[l] = lo.x;
+        sh.up0[l] = up.x;
+        sh.nlo[l] = lo.y;
+        nc = lo.y + up.y;
       }
       uint32_t x = nc;
       for (int off = 1; off < 64; off <<= 1) {
@@ -389,10 +387,10 @@ __device__ __forceinline__ void forces_group(const PileDev& P, const PairCtx<T>&
       const Body<T> ba = load_body<T>(P, a, ns, na);
       if (b < (uint32_t)ns) {
         const Body<T> bb = load_body<T>(P, b, ns, na);
-        find_hist<T>(c, c.old_off[a], c.old_off[a + 1], b, hs);
+        find_hist<T>(c, a, b, hs);
         sphere_contact<T>(c, cp, ba, bb, hs, r);
       } else {
-        find_hist<T>(c, c.old_off[a], c.old_off[a + 1], b, hs);
+        find_hist<T>(c, a, b, hs);
         wall_contact<T>(P, c, cp, ba, (int)(b - (uint32_t)ns), hs, r);
       }
       if (!lower) {
