@@ -194,7 +194,6 @@ void plan_pile(PileDev& h, const Sizes& z, BufList& L) {
     L.add(&h.wb[k], 3 * na);
   }
   L.add(&h.wA, 3 * na);
-  L.add(&h.vpred, 3 * na);
   L.add(&h.b, 3 * ns);
   L.add(&h.s, ns);
   L.add(&h.m, ns);
@@ -599,11 +598,9 @@ void enqueue_pass_marked(Batch& b, hipStream_t st, int mode, Mark mark, bool ove
     launch_fused(s, b.d_table, b.pl_fused_g, b.n_fused_g, b.cp, mode, 1, b.precision);
   });
   stage(0, st, staged, [&](hipStream_t s) {
-    launch_integrate(s, b.d_table, b.wl_agg, b.n_agg_blk, b.cp, mode);
+    launch_move(s, b.d_table, b.wl_sph, b.n_sph_blk, b.cp, mode);
   });
-  stage(1, st, staged, [&](hipStream_t s) {
-    launch_reconstruct(s, b.d_table, b.wl_sph, b.n_sph_blk);
-  });
+  stage(1, st, false, [](hipStream_t) {});       // part of move
   stage(2, st, staged, [&](hipStream_t s) { launch_grid(s, b.d_table, np, mode, b.cp.dt); });
   stage(3, st, staged, [&](hipStream_t s) { launch_bin(s, b.d_table, b.wl_sph, b.n_sph_blk); });
   stage(4, st, staged, [&](hipStream_t s) {
@@ -1756,7 +1753,7 @@ dem_status dem_find_contacts(const double* pos, const double* radius, const int3
   r = rebuild(s->own, st, s);
   if (r != DEM_OK) return fail(nullptr, r, s->err);
   Batch& b = s->own;
-  launch_reconstruct(st, b.d_table, b.wl_sph, b.n_sph_blk);
+  launch_move(st, b.d_table, b.wl_sph, b.n_sph_blk, b.cp, kModeInit);
   launch_grid(st, b.d_table, 1, kModeInit, 1.0);
   launch_bin(st, b.d_table, b.wl_sph, b.n_sph_blk);
   launch_scan(st, b.seg_cells, b.n_seg_cells, b.item_cells, b.n_item_cells, b.sums_cells,
@@ -1866,7 +1863,7 @@ dem_status dem_find_contacts_noalloc(const double* pos, const double* radius,
   // the cell counts start at zero (the scatter returns them to zero)
   launch_fill_u32(st, h.cell_cnt, 0u, q.cells + 1);
   const PileDev* t = q.entry;
-  launch_reconstruct(st, t, q.wl, q.n_blk);
+  launch_move(st, t, q.wl, q.n_blk, ContactParams{}, kModeInit);
   launch_grid(st, t, 1, kModeInit, 1.0);
   launch_bin(st, t, q.wl, q.n_blk);
   launch_scan(st, q.seg_cells, 1, q.item_cells, q.n_item_cells, q.sums_cells, q.max_items_cells);
@@ -1986,7 +1983,7 @@ dem_status dem_contact_forces(const dem_params* params, int64_t n, const double*
   if (r != DEM_OK) return fail(nullptr, r, s->err);
   // one evaluation pass without motion, gravity or the aggregate reduction
   Batch& b = s->own;
-  launch_reconstruct(st, b.d_table, b.wl_sph, b.n_sph_blk);
+  launch_move(st, b.d_table, b.wl_sph, b.n_sph_blk, b.cp, kModeInit);
   launch_grid(st, b.d_table, 1, kModeInit, p.dt);
   launch_bin(st, b.d_table, b.wl_sph, b.n_sph_blk);
   launch_scan(st, b.seg_cells, b.n_seg_cells, b.item_cells, b.n_item_cells, b.sums_cells,

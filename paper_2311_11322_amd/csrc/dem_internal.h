@@ -158,7 +158,6 @@ struct PileDev {
   double* q[2];              // [4][na]
   double* wb[2];             // [3][na]
   double* wA;                // [3][na] spin in space frame (this step)
-  double* vpred;             // [3][na] predicted COM velocity (Eq. 3, first bracket)
 
   // sphere constants (set-up)
   double* b;                 // [3][ns] body offsets
@@ -241,9 +240,8 @@ struct ScanItem {
 // ---------------------------------------------------------------------------
 void launch_setup(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk,
                   const double* pos_in, const double* vel_in, const double* spin_in);
-void launch_integrate(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk,
-                      ContactParams cp, int mode);
-void launch_reconstruct(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk);
+void launch_move(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk,
+                 ContactParams cp, int mode);
 void launch_grid(hipStream_t st, const PileDev* piles, int n_piles, int mode, double dt);
 void launch_bin(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk);
 void launch_scatter(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk);

@@ -156,41 +156,28 @@ __global__ __launch_bounds__(kBlock) void k_setup(const PileDev* __restrict__ pi
   for (int k = 0; k < 4; ++k) P.q[cur][k * P.na + A] = q[k];
 }
 
-// One thread per aggregate.  Step mode: v_A += h/2 a_A, r_A += h v_A (wrapped
-// in a periodic cube), one RK5 step of (q, w_b) with the last torque.  Writes
-// the next state, the space-frame spin w_A = R w_b and the predicted
-// centre-of-mass velocity v_A + h/2 a_A (first bracket of Eq. 3).  Init mode
-// copies the state unchanged (evaluation at t0).
-__global__ __launch_bounds__(kBlock) void k_integrate(PileDev* __restrict__ piles,
-                                                      const WorkItem* __restrict__ wl,
-                                                      ContactParams cp, int mode) {
+// ---------------------------------------------------------------------------
+// kick, drift, rotation and member reconstruction (SetSpacePos / SetSpaceSpin /
+// SetSpaceVel, Eq. 3)
+// ---------------------------------------------------------------------------
+
+// One thread per sphere, after the aggregates of the block's spheres have been
+// moved (move_block; as two launches, one thread per aggregate and one per
+// sphere, it took MOVE_BEFORE).
+// Each block also writes the bounding box and mass moments of its spheres for
+// the per-pile cell grid.
+__global__ __launch_bounds__(kBlock) void k_move(PileDev* __restrict__ piles,
+                                                 const WorkItem* __restrict__ wl, ContactParams cp,
+                                                 int mode) {
+  __shared__ MoveLds<kBlock> sh;
   const WorkItem w = wl[xcd_block(blockIdx.x, gridDim.x)];
   PileDev& P = piles[w.pile];
-  const int A = w.base + threadIdx.x;
-  if (A >= P.na || P.status != 0) return;
-  integrate_one(P, A, cp, mode);
-}
-
-// ---------------------------------------------------------------------------
-// member reconstruction (SetSpacePos / SetSpaceSpin / SetSpaceVel, Eq. 3)
-// ---------------------------------------------------------------------------
-
-// One thread per sphere: r_i = r_A + R b_i and v_i = vpred_A + w_A x (R b_i)
-// (a pile without aggregates, or with given sphere states, keeps the
-// positions and velocities it was given).  Each block
-// also writes the bounding box and mass moments of its spheres
-// for the per-pile cell grid.
-__global__ __launch_bounds__(kBlock) void k_reconstruct(const PileDev* __restrict__ piles,
-                                                        const WorkItem* __restrict__ wl) {
-  const WorkItem w = wl[xcd_block(blockIdx.x, gridDim.x)];
-  const PileDev& P = piles[w.pile];
   if (P.status != 0) return;
-  const int i = w.base + threadIdx.x;
   double vals[kBbox];
   bbox_identity(vals);
   double cref[3];
   bbox_ref(P, cref);
-  if (i < P.ns) reconstruct_one(P, i, cref, vals);
+  move_block<kBlock>(P, w.base, cp, mode, sh, cref, vals);
   // block reduction (wave shuffles, then across the 4 waves through LDS)
   __shared__ double red[4][kBbox];
   for (int off = 32; off > 0; off >>= 1) {
@@ -368,14 +355,10 @@ void launch_setup(hipStream_t st, const PileDev* piles, const WorkItem* wl, int 
   hipLaunchKernelGGL(k_setup, dim3(nblk), dim3(kBlock), 0, st, piles, wl, pos_in, vel_in, spin_in);
 }
 
-void launch_integrate(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk,
-                      ContactParams cp, int mode) {
-  hipLaunchKernelGGL(k_integrate, dim3(nblk), dim3(kBlock), 0, st, const_cast<PileDev*>(piles), wl,
-                     cp, mode);
-}
-
-void launch_reconstruct(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk) {
-  hipLaunchKernelGGL(k_reconstruct, dim3(nblk), dim3(kBlock), 0, st, piles, wl);
+void launch_move(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk,
+                 ContactParams cp, int mode) {
+  hipLaunchKernelGGL(k_move, dim3(nblk), dim3(kBlock), 0, st, const_cast<PileDev*>(piles), wl, cp,
+                     mode);
 }
 
 void launch_grid(hipStream_t st, const PileDev* piles, int n_piles, int mode, double dt) {

@@ -118,21 +118,23 @@ __global__ __launch_bounds__(kFusedThreads) void k_fused(PileDev* __restrict__ p
   __shared__ double red[kFusedWaves][kBbox];
   __shared__ uint32_t scan_sh[kFusedWaves + 1];
   __shared__ ForceLds<kFusedThreads, kFusedSpheres> force_sh;
+  __shared__ MoveLds<kFusedThreads> move_sh;
   PileDev& P = piles[plist[blockIdx.x]];
   const int tid = threadIdx.x;
   bool ok = status_of(P) == 0;            // a failed pile stays frozen
   if (part & 1) {
     if (ok) {
-      // kick, drift and rotate every aggregate
-      for (int A = tid; A < P.na; A += kFusedThreads) integrate_one(P, A, cp, mode);
-      stage_sync();
-      // members, and the bounding box and mass moments of the pile
-      double acc[kBbox], one[kBbox], cref[3];
+      // kick, drift and rotate every aggregate; members, and the bounding box
+      // and mass moments of the pile
+      double acc[kBbox], cref[3];
       bbox_identity(acc);
       bbox_ref(P, cref);
-      for (int i = tid; i < P.ns; i += kFusedThreads) {
-        reconstruct_one(P, i, cref, one);
+      for (int base = 0; base < P.ns; base += kFusedThreads) {
+        double one[kBbox];
+        bbox_identity(one);
+        move_block<kFusedThreads>(P, base, cp, mode, move_sh, cref, one);
         bbox_combine(acc, one);
+        if (base + kFusedThreads < P.ns) stage_sync();      // move_sh is written again
       }
       for (int off = 32; off > 0; off >>= 1) {
         double o[kBbox];

@@ -68,19 +68,26 @@ __device__ void rk5_rotate(double y[7], const double I[3], const double N[3], do
   for (int c = 0; c < 4; ++c) y[c] *= inv;
 }
 
+// What a member's reconstruction needs of its aggregate after the drift: the new
+// centre, orientation and space-frame spin, and the predicted centre velocity.
+struct Moved {
+  double r[3], q[4], w[3], vpred[3];
+};
+
 // One aggregate.  Step mode: v_A += h/2 a_A, r_A += h v_A (wrapped in a
-// periodic cube), one RK5 step of (q, w_b) with the last torque.  Writes the
-// next state, the space-frame spin w_A = R w_b and the predicted
-// centre-of-mass velocity v_A + h/2 a_A (first bracket of Eq. 3).  Init mode
-// copies the state unchanged (evaluation at t0).
-__device__ __forceinline__ void integrate_one(PileDev& P, int A, const ContactParams& cp,
-                                              int mode) {
+// periodic cube), one RK5 step of (q, w_b) with the last torque.  Returns the
+// new state with the space-frame spin w_A = R w_b and the predicted
+// centre-of-mass velocity v_A + h/2 a_A (first bracket of Eq. 3) and, with
+// store, writes it.  Init mode copies the state unchanged (evaluation at t0).
+__device__ __forceinline__ Moved move_one(PileDev& P, int A, const ContactParams& cp, int mode,
+                                          bool store) {
   const int na = P.na, cur = P.parity, nxt = cur ^ 1;
   const double h = cp.dt;
-  double v[3], r[3], a[3], y[7];
+  double v[3], a[3], y[7];
+  Moved m;
   for (int k = 0; k < 3; ++k) {
     v[k] = P.vA[cur][k * na + A];
-    r[k] = P.rA[cur][k * na + A];
+    m.r[k] = P.rA[cur][k * na + A];
     a[k] = P.aA[cur][k * na + A];
   }
   for (int k = 0; k < 4; ++k) y[k] = P.q[cur][k * na + A];
@@ -88,28 +95,30 @@ __device__ __forceinline__ void integrate_one(PileDev& P, int A, const ContactPa
   if (mode == kModeStep) {
     for (int k = 0; k < 3; ++k) {
       v[k] += 0.5 * h * a[k];
-      r[k] += h * v[k];
+      m.r[k] += h * v[k];
     }
     if (P.periodic) {
       const double L = P.box;
       for (int k = 0; k < 3; ++k) {
-        if (r[k] >= L) r[k] -= L;
-        if (r[k] < 0.0) r[k] += L;
+        if (m.r[k] >= L) m.r[k] -= L;
+        if (m.r[k] < 0.0) m.r[k] += L;
       }
     }
     const double I[3] = {P.I[A], P.I[na + A], P.I[2 * na + A]};
     const double N[3] = {P.NA[cur][A], P.NA[cur][na + A], P.NA[cur][2 * na + A]};
     rk5_rotate(y, I, N, h);
   }
-  double R[9], ws[3];
+  double R[9];
   quat_rot(y, R);
-  rot_apply(R, &y[4], ws);
+  rot_apply(R, &y[4], m.w);
   const double hh = (mode == kModeStep) ? 0.5 * h : 0.0;
+  for (int k = 0; k < 3; ++k) m.vpred[k] = v[k] + hh * a[k];
+  for (int k = 0; k < 4; ++k) m.q[k] = y[k];
+  if (!store) return m;
   for (int k = 0; k < 3; ++k) {
     P.vA[nxt][k * na + A] = v[k];
-    P.rA[nxt][k * na + A] = r[k];
-    P.wA[k * na + A] = ws[k];
-    P.vpred[k * na + A] = v[k] + hh * a[k];
+    P.rA[nxt][k * na + A] = m.r[k];
+    P.wA[k * na + A] = m.w[k];
     P.wb[nxt][k * na + A] = y[4 + k];
   }
   for (int k = 0; k < 4; ++k) P.q[nxt][k * na + A] = y[k];
@@ -125,6 +134,7 @@ __device__ __forceinline__ void integrate_one(PileDev& P, int A, const ContactPa
       P.pert_r[nxt][k] = pr;
     }
   }
+  return m;
 }
 
 // Partials of an empty set of spheres: bbox min / max and mass moments.
@@ -143,48 +153,45 @@ __device__ __forceinline__ void bbox_combine(double a[kBbox], const double b[kBb
   for (int k = 6; k < kBbox; ++k) a[k] += b[k];
 }
 
-// Reference point of the second moment: aggregate 0's new centre (the
-// origin for a pile of given positions).
+// Reference point of the second moment: aggregate 0's centre before the step
+// (the origin for a pile of given positions).
 __device__ __forceinline__ void bbox_ref(const PileDev& P, double cref[3]) {
-  const int na = P.na, nxt = P.parity ^ 1;
-  for (int k = 0; k < 3; ++k) cref[k] = (na > 0 && !P.given) ? P.rA[nxt][k * na] : 0.0;
+  const int na = P.na, cur = P.parity;
+  for (int k = 0; k < 3; ++k) cref[k] = (na > 0 && !P.given) ? P.rA[cur][k * na] : 0.0;
 }
 
-// Member reconstruction of sphere i (SetSpacePos / SetSpaceVel, Eq. 3):
-// r_i = r_A + R b_i, v_i = vpred_A + w_A x (R b_i); a pile without
-// aggregates, or with given sphere states, keeps the positions and
-// velocities it was given.  Its bounding-box and mass-moment contributions
-// (second moment about cref) go into vals.
-__device__ __forceinline__ void reconstruct_one(const PileDev& P, int i, const double cref[3],
-                                                double vals[kBbox]) {
-  const int ns = P.ns, na = P.na, nxt = P.parity ^ 1;
-  if (na == 0 || P.given) {
-    // positions given directly (stateless hooks): bbox only
-    for (int k = 0; k < 3; ++k) {
-      const double x = P.r[k * ns + i];
-      vals[k] = x;
-      vals[3 + k] = x;
-      vals[7 + k] = x;
-    }
-    vals[6] = 1.0;
-    vals[10] = 0.0;
-    return;
+// Bounding-box contribution of sphere i of a pile whose positions are given
+// (stateless hooks).
+__device__ __forceinline__ void given_one(const PileDev& P, int i, double vals[kBbox]) {
+  for (int k = 0; k < 3; ++k) {
+    const double x = P.r[k * P.ns + i];
+    vals[k] = x;
+    vals[3 + k] = x;
+    vals[7 + k] = x;
   }
-  const int A = P.agg[i];
-  double q[4], R[9];
-  for (int k = 0; k < 4; ++k) q[k] = P.q[nxt][k * na + A];
-  quat_rot(q, R);
+  vals[6] = 1.0;
+  vals[10] = 0.0;
+}
+
+// Member reconstruction of sphere i of the aggregate in state (rA, q, wa, vp)
+// (SetSpacePos / SetSpaceVel, Eq. 3): r_i = r_A + R b_i, v_i = vpred_A + w_A x
+// (R b_i).  Its bounding-box and mass-moment contributions (second moment
+// about cref) go into vals.
+__device__ __forceinline__ void reconstruct_one(const PileDev& P, int i, const Moved& m,
+                                                const double cref[3], double vals[kBbox]) {
+  const int ns = P.ns;
+  double R[9];
+  quat_rot(m.q, R);
   const double bb[3] = {P.b[i], P.b[ns + i], P.b[2 * ns + i]};
   double d[3], wxd[3];
   rot_apply(R, bb, d);
-  const double wa[3] = {P.wA[A], P.wA[na + A], P.wA[2 * na + A]};
-  cross3(wa, d, wxd);
+  cross3(m.w, d, wxd);
   const double mi = P.m[i];
   double d2 = 0.0;
   for (int k = 0; k < 3; ++k) {
-    const double x = P.rA[nxt][k * na + A] + d[k];
+    const double x = m.r[k] + d[k];
     P.r[k * ns + i] = x;
-    P.v[k * ns + i] = P.vpred[k * na + A] + wxd[k];
+    P.v[k * ns + i] = m.vpred[k] + wxd[k];
     vals[k] = x;
     vals[3 + k] = x;
     vals[7 + k] = mi * x;
@@ -192,6 +199,52 @@ __device__ __forceinline__ void reconstruct_one(const PileDev& P, int i, const d
   }
   vals[6] = mi;
   vals[10] = mi * d2;
+}
+
+// The new states of the aggregates of one block's NT spheres, in LDS.
+template <int NT>
+struct MoveLds {
+  double v[13][NT];
+};
+
+// Kick, drift and rotation of the aggregates that own spheres base .. base +
+// NT - 1, and the reconstruction of those spheres, by a block of NT threads.
+// The spheres are grouped by aggregate, so at most NT aggregates take part;
+// one whose members lie in several blocks is moved by each of them (the same
+// arithmetic) and stored by the block of its first member.  Every thread of the
+// block calls this; vals gets this thread's sphere's contribution.
+template <int NT>
+__device__ __forceinline__ void move_block(PileDev& P, int base, const ContactParams& cp, int mode,
+                                           MoveLds<NT>& sh, const double cref[3],
+                                           double vals[kBbox]) {
+  const int ns = P.ns, tid = threadIdx.x, i = base + tid;
+  if (P.na == 0 || P.given) {
+    if (i < ns) given_one(P, i, vals);
+    return;
+  }
+  const int a0 = P.agg[base], a1 = P.agg[min(base + NT, ns) - 1];
+  if (tid <= a1 - a0) {
+    const int A = a0 + tid;
+    const Moved m = move_one(P, A, cp, mode, P.first[A] >= base);
+    for (int k = 0; k < 3; ++k) {
+      sh.v[k][tid] = m.r[k];
+      sh.v[3 + k][tid] = m.w[k];
+      sh.v[6 + k][tid] = m.vpred[k];
+    }
+    for (int k = 0; k < 4; ++k) sh.v[9 + k][tid] = m.q[k];
+  }
+  __syncthreads();
+  if (i < ns) {
+    const int l = P.agg[i] - a0;
+    Moved m;
+    for (int k = 0; k < 3; ++k) {
+      m.r[k] = sh.v[k][l];
+      m.w[k] = sh.v[3 + k][l];
+      m.vpred[k] = sh.v[6 + k][l];
+    }
+    for (int k = 0; k < 4; ++k) m.q[k] = sh.v[9 + k][l];
+    reconstruct_one(P, i, m, cref, vals);
+  }
 }
 
 // The pile's cell grid, centre of mass, bulk radius and stop rule, wall
@@ -212,14 +265,12 @@ __device__ __forceinline__ void grid_from_vals(PileDev& P, double vals[kBbox], i
     return;
   }
   for (int k = 0; k < 3; ++k) g.com[k] = vals[7 + k] / vals[6];
-  // second moment about the centre of mass, from the one about aggregate 0's
-  // centre c: <|r - com|^2>_m = <|r - c|^2>_m - |com - c|^2
+  // second moment about the centre of mass, from the one about the reference
+  // point c: <|r - com|^2>_m = <|r - c|^2>_m - |com - c|^2
   double s2;
   {
-    double c[3] = {0.0, 0.0, 0.0};
-    const int na = P.na, nxt = P.parity ^ 1;
-    if (na > 0 && !P.given)
-      for (int k = 0; k < 3; ++k) c[k] = P.rA[nxt][k * na];
+    double c[3];
+    bbox_ref(P, c);
     s2 = vals[10] / vals[6];
     for (int k = 0; k < 3; ++k) s2 -= (g.com[k] - c[k]) * (g.com[k] - c[k]);
     s2 = fmax(s2, 0.0);
