@@ -203,11 +203,12 @@ void plan_pile(PileDev& h, const Sizes& z, BufList& L) {
   L.add(&h.F, 3 * ns);
   L.add(&h.tau, 3 * ns);
   L.add(&h.key, ns);
-  L.add(&h.sidx, ns);
-  L.add(&h.sidx_raw, ns);
+  L.add(&h.num, ns);
   L.add(&h.xg, ns);
   L.add(&h.sid, ns);
   if (z.grav) {
+    L.add(&h.sidx, ns);
+    L.add(&h.sidx_raw, ns);
     L.add(reinterpret_cast<double**>(&h.jrec), 8 * ns);
     L.add(&h.gacc, 3 * ns);
     if (z.tree) {
@@ -268,6 +269,18 @@ struct Batch {
   bool tree_order[2] = {false, false};       // some tree pile of order 2, 4
   unsigned tree_leaf_levels = 0;             // bit l: level l is some tree pile's finest
   int n_sph_blk = 0;
+  // the staged piles by how their spheres are sorted: with gravity on this
+  // evaluation's cells and in id order, without on carried cells (PileDev::rows)
+  int32_t* pl_staged = nullptr;              // every staged pile
+  int32_t* pl_grid = nullptr;
+  int n_grid = 0;
+  WorkItem* wl_bin = nullptr;
+  int n_bin_blk = 0;
+  int32_t* pl_carry = nullptr;
+  int n_carry = 0;
+  WorkItem* wl_place = nullptr;
+  int n_place_blk = 0;
+  bool finish_in_reduce = false;             // no staged pile has too many blocks for it
   // gravity pair blocks, grouped by tile size (one launch per group)
   GravPair* gl[kGravTileSizes] = {};
   int n_grav[kGravTileSizes] = {};
@@ -320,6 +333,7 @@ struct dem_sim {
   size_t bytes = 0;
   Sizes sz{};
   int c_max = kDefaultContacts;
+  bool regrid = false;               // restored: the carried cells do not suit the positions
   bool has_aggs = false;
   bool stepped = false;
   dem_forcing forcing{};
@@ -404,8 +418,9 @@ hipError_t upload(Batch& b, T** dst, const std::vector<T>& src, hipStream_t st) 
 // device table entries must already be in place at slots 0..n-1.
 dem_status rebuild(Batch& b, hipStream_t st, dem_sim* errsim) {
   free_meta(b);
-  std::vector<WorkItem> wa, wsph, wbig, wtree[11], wgrav, wall;
-  std::vector<int32_t> pfg, pfng;
+  std::vector<WorkItem> wa, wsph, wbin, wplace, wbig, wtree[11], wgrav, wall;
+  std::vector<int32_t> pfg, pfng, pstaged, pgrid, pcarry;
+  b.finish_in_reduce = true;
   std::vector<GravItem> gmg[kGravTileSizes], gsg[kGravTileSizes];
   std::vector<std::pair<int64_t, GravItem>> gmw[kGravTileSizes];
   std::vector<GravPair> glg[kGravTileSizes];
@@ -433,7 +448,13 @@ dem_status rebuild(Batch& b, hipStream_t st, dem_sim* errsim) {
       b.n_staged++;
       for (int a = 0; a < h.na; a += kBlock) wa.push_back({p, a});
       tot_na += h.na;
-      for (int i = 0; i < h.ns; i += kBlock) wsph.push_back({p, i});
+      if ((h.na + kBlock - 1) / kBlock > kFinishInReduce) b.finish_in_reduce = false;
+      pstaged.push_back(p);
+      (h.rows ? pcarry : pgrid).push_back(p);
+      for (int i = 0; i < h.ns; i += kBlock) {
+        wsph.push_back({p, i});
+        (h.rows ? wplace : wbin).push_back({p, i});
+      }
       for (int k = 0; k < h.n_big; ++k) wbig.push_back({p, k});
     }
     if (h.G != 0.0 && h.tree) {
@@ -485,7 +506,7 @@ dem_status rebuild(Batch& b, hipStream_t st, dem_sim* errsim) {
       }
     }
     // cell-count scan of this pile
-    auto add_seg = [](std::vector<ScanSeg>& segs, std::vector<ScanItem>& items, const uint32_t* in,
+    auto add_seg = [](std::vector<ScanSeg>& segs, std::vector<ScanItem>& items, uint32_t* in,
                       uint32_t* out, int64_t n) {
       ScanSeg g{};
       g.in = in;
@@ -509,6 +530,15 @@ dem_status rebuild(Batch& b, hipStream_t st, dem_sim* errsim) {
   HIPCHK(errsim, upload(b, &b.pl_fused_ng, pfng, st));
   b.n_fused_ng = (int)pfng.size();
   HIPCHK(errsim, upload(b, &b.wl_sph, wsph, st));
+  HIPCHK(errsim, upload(b, &b.wl_bin, wbin, st));
+  b.n_bin_blk = (int)wbin.size();
+  HIPCHK(errsim, upload(b, &b.wl_place, wplace, st));
+  b.n_place_blk = (int)wplace.size();
+  HIPCHK(errsim, upload(b, &b.pl_staged, pstaged, st));
+  HIPCHK(errsim, upload(b, &b.pl_grid, pgrid, st));
+  b.n_grid = (int)pgrid.size();
+  HIPCHK(errsim, upload(b, &b.pl_carry, pcarry, st));
+  b.n_carry = (int)pcarry.size();
   b.n_big_blk = (int)wbig.size();
   if (!wbig.empty()) HIPCHK(errsim, upload(b, &b.wl_big, wbig, st));
   for (int l = 0; l <= 10; ++l) {
@@ -550,13 +580,13 @@ dem_status rebuild(Batch& b, hipStream_t st, dem_sim* errsim) {
 }
 
 // Kernel families of one step, in launch order (profiling names).
-constexpr int kNumStages = 14;
-constexpr int kStageGravity = 9;
-constexpr int kStageFusedA = 12;           // k_fused parts 1 and 3
-constexpr int kStageFusedB = 13;           // k_fused part 2
+constexpr int kNumStages = 13;
+constexpr int kStageGravity = 8;
+constexpr int kStageFusedA = 11;           // k_fused parts 1 and 3
+constexpr int kStageFusedB = 12;           // k_fused part 2
 const char* const kStageNames =
-    "integrate;reconstruct;grid;bin;scan_cells;scatter;cell_sort;search;"
-    "forces;gravity;reduce;finish;fused_a;fused_b";
+    "move;grid;bin;scan_cells;place;cell_sort;search;forces;gravity;reduce;finish;"
+    "fused_a;fused_b";
 
 // Second stream and fork/join events of a batch (default priority).
 hipError_t ensure_side(Batch& b) {
@@ -582,9 +612,11 @@ void release_side(Batch& b) {
 // batch's second stream beside the search, scan and force kernels (the
 // captured step); without, every stage runs in order on one stream (the
 // t0 evaluation, the stateless hooks, and the profiled passes, whose event
-// spans then time each stage alone).
+// spans then time each stage alone).  fresh: piles that bin on carried cells
+// have none that suit their positions (the t0 evaluation, the step after a
+// restore), so the cells come first, as in a pile with gravity.
 template <typename Mark>
-void enqueue_pass_marked(Batch& b, hipStream_t st, int mode, Mark mark, bool overlap) {
+void enqueue_pass_marked(Batch& b, hipStream_t st, int mode, Mark mark, bool overlap, bool fresh) {
   const int np = (int)b.members.size();
   const bool staged = b.n_staged > 0;
   auto stage = [&](int k, hipStream_t s, bool run, auto&& launch) {
@@ -598,20 +630,26 @@ void enqueue_pass_marked(Batch& b, hipStream_t st, int mode, Mark mark, bool ove
     launch_fused(s, b.d_table, b.pl_fused_g, b.n_fused_g, b.cp, mode, 1, b.precision);
   });
   stage(0, st, staged, [&](hipStream_t s) {
-    launch_move(s, b.d_table, b.wl_sph, b.n_sph_blk, b.cp, mode);
+    launch_move(s, b.d_table, b.wl_sph, b.n_sph_blk, b.cp, mode, !fresh);
   });
-  stage(1, st, false, [](hipStream_t) {});       // part of move
-  stage(2, st, staged, [&](hipStream_t s) { launch_grid(s, b.d_table, np, mode, b.cp.dt); });
-  stage(3, st, staged, [&](hipStream_t s) { launch_bin(s, b.d_table, b.wl_sph, b.n_sph_blk); });
-  stage(4, st, staged, [&](hipStream_t s) {
+  stage(1, st, staged, [&](hipStream_t s) {
+    launch_grid(s, b.d_table, fresh ? b.pl_staged : b.pl_grid, fresh ? b.n_staged : b.n_grid, mode,
+                b.cp.dt);
+  });
+  stage(2, st, staged, [&](hipStream_t s) {
+    launch_bin(s, b.d_table, fresh ? b.wl_sph : b.wl_bin, fresh ? b.n_sph_blk : b.n_bin_blk);
+  });
+  stage(3, st, staged, [&](hipStream_t s) {
     launch_scan(s, b.seg_cells, b.n_seg_cells, b.item_cells, b.n_item_cells, b.sums_cells,
-                b.max_items_cells);
+                b.max_items_cells,
+                ScanGrids{b.d_table, b.pl_carry, fresh ? 0 : b.n_carry, mode, b.cp.dt});
+  });
+  stage(4, st, staged, [&](hipStream_t s) {
+    launch_place(s, b.d_table, b.wl_place, b.n_place_blk);
+    launch_scatter(s, b.d_table, b.wl_bin, b.n_bin_blk);
   });
   stage(5, st, staged, [&](hipStream_t s) {
-    launch_scatter(s, b.d_table, b.wl_sph, b.n_sph_blk);
-  });
-  stage(6, st, staged, [&](hipStream_t s) {
-    launch_cell_sort(s, b.d_table, b.wl_sph, b.n_sph_blk);
+    launch_cell_sort(s, b.d_table, b.wl_bin, b.n_bin_blk);
   });
   const bool fork = overlap && b.any_grav && b.side && staged;
   auto gravity = [&](hipStream_t s) {
@@ -634,11 +672,11 @@ void enqueue_pass_marked(Batch& b, hipStream_t st, int mode, Mark mark, bool ove
     stage(kStageGravity, b.side, true, gravity);
     (void)hipEventRecord(b.join_ev, b.side);
   }
-  stage(7, st, staged, [&](hipStream_t s) {
+  stage(6, st, staged, [&](hipStream_t s) {
     launch_search(s, b.d_table, b.wl_sph, b.n_sph_blk);
     if (b.n_big_blk) launch_search_big(s, b.d_table, b.wl_big, b.n_big_blk);
   });
-  stage(8, st, staged, [&](hipStream_t s) {
+  stage(7, st, staged, [&](hipStream_t s) {
     launch_forces(s, b.d_table, b.wl_sph, b.n_sph_blk, b.cp, b.precision);
   });
   if (fork) (void)hipStreamWaitEvent(st, b.join_ev, 0);
@@ -646,14 +684,27 @@ void enqueue_pass_marked(Batch& b, hipStream_t st, int mode, Mark mark, bool ove
   stage(kStageFusedB, st, b.n_fused_g > 0, [&](hipStream_t s) {
     launch_fused(s, b.d_table, b.pl_fused_g, b.n_fused_g, b.cp, mode, 2, b.precision);
   });
-  stage(10, st, staged, [&](hipStream_t s) {
-    launch_reduce(s, b.d_table, b.wl_agg, b.n_agg_blk, b.cp, mode, b.reduce_stage);
+  stage(9, st, staged, [&](hipStream_t s) {
+    launch_reduce(s, b.d_table, b.wl_agg, b.n_agg_blk, b.cp, mode, b.reduce_stage,
+                  b.finish_in_reduce);
   });
-  stage(11, st, staged, [&](hipStream_t s) { launch_finish(s, b.d_table, np, mode, b.cp.dt); });
+  stage(10, st, staged && !b.finish_in_reduce, [&](hipStream_t s) {
+    launch_finish(s, b.d_table, np, mode, b.cp.dt);
+  });
 }
 
-void enqueue_pass(Batch& b, hipStream_t st, int mode, bool overlap = false) {
-  enqueue_pass_marked(b, st, mode, [](int, hipStream_t, bool) {}, overlap);
+void enqueue_pass(Batch& b, hipStream_t st, int mode, bool overlap, bool fresh) {
+  enqueue_pass_marked(b, st, mode, [](int, hipStream_t, bool) {}, overlap, fresh);
+}
+
+// The sorted copies of a batch whose positions are given (stateless hooks).
+void sort_pass(Batch& b, hipStream_t st, double dt) {
+  launch_move(st, b.d_table, b.wl_sph, b.n_sph_blk, b.cp, kModeInit, false);
+  launch_grid(st, b.d_table, b.pl_staged, b.n_staged, kModeInit, dt);
+  launch_bin(st, b.d_table, b.wl_sph, b.n_sph_blk);
+  launch_scan(st, b.seg_cells, b.n_seg_cells, b.item_cells, b.n_item_cells, b.sums_cells,
+              b.max_items_cells, ScanGrids{});
+  launch_place(st, b.d_table, b.wl_place, b.n_place_blk);
 }
 
 dem_status ensure_graph(Batch& b, hipStream_t st, dem_sim* errsim) {
@@ -667,7 +718,7 @@ dem_status ensure_graph(Batch& b, hipStream_t st, dem_sim* errsim) {
     own_stream = true;
   }
   HIPCHK(errsim, hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
-  enqueue_pass(b, cap, kModeStep, true);
+  enqueue_pass(b, cap, kModeStep, true, false);
   hipGraph_t g = nullptr;
   hipError_t e = hipStreamEndCapture(cap, &g);
   if (own_stream) (void)hipStreamDestroy(cap);
@@ -694,7 +745,7 @@ dem_status profiled_passes(Batch& b, hipStream_t st, int64_t n_steps,
     hipEvent_t* ev = &events[size_t(k) * per_step];
     enqueue_pass_marked(b, st, kModeStep, [&](int m, hipStream_t s, bool begin) {
       if (rec == hipSuccess) rec = hipEventRecord(ev[2 * m + (begin ? 0 : 1)], s);
-    }, false);
+    }, false, false);
   }
   HIPCHK(errsim, rec);
   HIPCHK(errsim, hipStreamSynchronize(st));
@@ -730,7 +781,7 @@ dem_status gravity_timed_passes(Batch& b, hipStream_t st, int64_t n_steps,
     hipEvent_t* ev = &events[size_t(2) * k];
     enqueue_pass_marked(b, st, kModeStep, [&](int m, hipStream_t s, bool begin) {
       if (m == kStageGravity && rec == hipSuccess) rec = hipEventRecord(ev[begin ? 0 : 1], s);
-    }, true);
+    }, true, false);
   }
   HIPCHK(errsim, rec);
   HIPCHK(errsim, hipStreamSynchronize(st));
@@ -880,13 +931,6 @@ dem_status alloc_pile(dem_sim* s, int64_t na, int64_t ns) {
   h.fail_step = -1;
   s->h = h;
   return DEM_OK;
-}
-
-// No contacts: empty runs of every sphere.
-void clear_runs(hipStream_t st, const PileDev& h, int64_t ns) {
-  for (int k = 0; k < 2; ++k)
-    launch_fill_u32(st, reinterpret_cast<uint32_t*>(h.up_run[k]), 0u, 2 * ns);
-  launch_fill_u32(st, reinterpret_cast<uint32_t*>(h.lo_run), 0u, 2 * ns);
 }
 
 // The runs of canonical keys listed sphere by sphere (first entry and length of
@@ -1107,8 +1151,7 @@ NoAllocPlan plan_noalloc(char* base, int64_t n, PileDev& h) {
   q.sums_pairs = L.take<uint32_t>(q.n_item_pairs);
   h.r = L.take<double>(3 * n);
   h.key = L.take<uint32_t>(n);
-  h.sidx = L.take<uint32_t>(n);
-  h.sidx_raw = L.take<uint32_t>(n);
+  h.num = L.take<uint32_t>(n);
   h.xg = L.take<SortedGeom>(n);
   h.sid = L.take<SortedId>(n);
   h.bpart = L.take<double>(kBbox * q.n_blk);
@@ -1252,8 +1295,7 @@ dem_status dem_add_aggregates(dem_sim* s, int64_t n_agg, const int32_t* spa, con
     HIPCHK(s, hipMemcpyAsync(d_spin, agg_spin, n_agg * 24, hipMemcpyHostToDevice, str));
   }
   // zero the contact lists (empty history) and cell counts
-  clear_runs(str, s->h, ns);
-  launch_fill_u32(str, s->h.cell_cnt, 0u, s->sz.cells + 1);
+  launch_clear(str, s->h, s->sz.cells + 1);
   st = ensure_own_table(s);
   if (st != DEM_OK) return st;
   HIPCHK(s, put_entry(s, s->own.d_table, str));
@@ -1262,7 +1304,7 @@ dem_status dem_add_aggregates(dem_sim* s, int64_t n_agg, const int32_t* spa, con
   launch_setup(str, s->own.d_table, s->own.wl_agg_all, s->own.n_agg_all_blk, d_pos, d_vel,
                d_spin);
   // initial evaluation at t0 (forces, torques and accelerations)
-  enqueue_pass(s->own, str, kModeInit);
+  enqueue_pass(s->own, str, kModeInit, false, true);
   HIPCHK(s, hipGetLastError());
   HIPCHK(s, get_entry(s, s->own.d_table, str));
   (void)hipFree(d_pos);
@@ -1290,7 +1332,16 @@ dem_status dem_step(dem_sim* s, int64_t n_steps) {
   }
   s->stepped = true;
   if (n_steps == 0) return DEM_OK;
-  if (s->profiling == 1) {
+  if (s->regrid) {
+    // the first step after a restore works its cells out first
+    enqueue_pass(s->own, s->stream, kModeStep, false, true);
+    HIPCHK(s, hipGetLastError());
+    s->regrid = false;
+    --n_steps;
+  }
+  if (n_steps == 0) {
+    // that was the only step
+  } else if (s->profiling == 1) {
     dem_status st = profiled_passes(s->own, s->stream, n_steps, s->events, s->prof_ms,
                                     s->prof_steps, s);
     if (st != DEM_OK) return st;
@@ -1481,6 +1532,7 @@ dem_status dem_restore_state(dem_sim* s, const dem_state* in) {
     HIPCHK(s, hipStreamSynchronize(st));
   }
   launch_fill_u32(st, h.cell_cnt, 0u, s->sz.cells + 1);
+  s->regrid = true;
   h.status = 0;
   h.fail_step = -1;
   h.step = in->step;
@@ -1621,7 +1673,7 @@ dem_status dem_reserve_contacts(dem_sim* s, int32_t per_sphere) {
   copy(h.m, old.m, ns * 8);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) return fail(s, undo(DEM_ERR_DEVICE), hip_msg(e, "reserve copy"));
-  clear_runs(st, h, ns);
+  launch_clear(st, h, s->sz.cells + 1);
   free_meta(s->own);
   e = put_entry(s, s->own.d_table, st);
   if (e != hipSuccess) return fail(s, undo(DEM_ERR_DEVICE), hip_msg(e, "reserve table"));
@@ -1753,13 +1805,7 @@ dem_status dem_find_contacts(const double* pos, const double* radius, const int3
   r = rebuild(s->own, st, s);
   if (r != DEM_OK) return fail(nullptr, r, s->err);
   Batch& b = s->own;
-  launch_move(st, b.d_table, b.wl_sph, b.n_sph_blk, b.cp, kModeInit);
-  launch_grid(st, b.d_table, 1, kModeInit, 1.0);
-  launch_bin(st, b.d_table, b.wl_sph, b.n_sph_blk);
-  launch_scan(st, b.seg_cells, b.n_seg_cells, b.item_cells, b.n_item_cells, b.sums_cells,
-              b.max_items_cells);
-  launch_scatter(st, b.d_table, b.wl_sph, b.n_sph_blk);
-  launch_cell_sort(st, b.d_table, b.wl_sph, b.n_sph_blk);
+  sort_pass(b, st, 1.0);
   launch_search(st, b.d_table, b.wl_sph, b.n_sph_blk);
   HIPCHK(s, hipGetLastError());
   PileDev tmp;
@@ -1860,15 +1906,15 @@ dem_status dem_find_contacts_noalloc(const double* pos, const double* radius,
   HIPCHK(nullptr, hipMemcpyAsync(q.seg_pairs, &sp, sizeof sp, hipMemcpyHostToDevice, st));
   HIPCHK(nullptr, hipMemcpyAsync(q.item_pairs, ip, q.n_item_pairs * sizeof(ScanItem),
                                  hipMemcpyHostToDevice, st));
-  // the cell counts start at zero (the scatter returns them to zero)
+  // the cell counts start at zero (the scan returns them to zero)
   launch_fill_u32(st, h.cell_cnt, 0u, q.cells + 1);
   const PileDev* t = q.entry;
-  launch_move(st, t, q.wl, q.n_blk, ContactParams{}, kModeInit);
-  launch_grid(st, t, 1, kModeInit, 1.0);
+  launch_move(st, t, q.wl, q.n_blk, ContactParams{}, kModeInit, false);
+  launch_grid(st, t, nullptr, 1, kModeInit, 1.0);
   launch_bin(st, t, q.wl, q.n_blk);
-  launch_scan(st, q.seg_cells, 1, q.item_cells, q.n_item_cells, q.sums_cells, q.max_items_cells);
-  launch_scatter(st, t, q.wl, q.n_blk);
-  launch_cell_sort(st, t, q.wl, q.n_blk);
+  launch_scan(st, q.seg_cells, 1, q.item_cells, q.n_item_cells, q.sums_cells, q.max_items_cells,
+              ScanGrids{});
+  launch_place(st, t, q.wl, q.n_blk);
   launch_search(st, t, q.wl, q.n_blk);
   HIPCHK(nullptr, hipGetLastError());
   int32_t status = 0;
@@ -1882,7 +1928,8 @@ dem_status dem_find_contacts_noalloc(const double* pos, const double* radius,
     return fail(nullptr, DEM_ERR_CAPACITY, "more contacts than the static scratch holds");
   if (status != 0) return fail(nullptr, DEM_ERR_INVALID_ARG, "non-finite positions");
   if (cap > 0 && total > 0) {
-    launch_scan(st, q.seg_pairs, 1, q.item_pairs, q.n_item_pairs, q.sums_pairs, q.max_items_pairs);
+    launch_scan(st, q.seg_pairs, 1, q.item_pairs, q.n_item_pairs, q.sums_pairs, q.max_items_pairs,
+                ScanGrids{});
     hipLaunchKernelGGL(k_noalloc_keys, dim3(q.n_blk), dim3(kBlock), 0, st, q.key_off, h.up_run[1],
                        h.pair_j[1], (int)n, pairs_out, cap);
     HIPCHK(nullptr, hipGetLastError());
@@ -1983,13 +2030,7 @@ dem_status dem_contact_forces(const dem_params* params, int64_t n, const double*
   if (r != DEM_OK) return fail(nullptr, r, s->err);
   // one evaluation pass without motion, gravity or the aggregate reduction
   Batch& b = s->own;
-  launch_move(st, b.d_table, b.wl_sph, b.n_sph_blk, b.cp, kModeInit);
-  launch_grid(st, b.d_table, 1, kModeInit, p.dt);
-  launch_bin(st, b.d_table, b.wl_sph, b.n_sph_blk);
-  launch_scan(st, b.seg_cells, b.n_seg_cells, b.item_cells, b.n_item_cells, b.sums_cells,
-              b.max_items_cells);
-  launch_scatter(st, b.d_table, b.wl_sph, b.n_sph_blk);
-  launch_cell_sort(st, b.d_table, b.wl_sph, b.n_sph_blk);
+  sort_pass(b, st, p.dt);
   launch_search(st, b.d_table, b.wl_sph, b.n_sph_blk);
   if (b.n_big_blk) launch_search_big(st, b.d_table, b.wl_big, b.n_big_blk);
   launch_forces(st, b.d_table, b.wl_sph, b.n_sph_blk, b.cp, b.precision);
@@ -2128,7 +2169,19 @@ dem_status dem_engine_step(dem_engine* e, int64_t n_steps) {
     dem_status r = rebuild(b, e->stream, b.members[0]);
     if (r != DEM_OK) return r;
   }
-  if (e->profiling) {
+  bool regrid = false;
+  for (dem_sim* s : b.members) regrid = regrid || s->regrid;
+  if (regrid) {
+    // the first step after a restore works its cells out first
+    enqueue_pass(b, e->stream, kModeStep, false, true);
+    const hipError_t he = hipGetLastError();
+    if (he != hipSuccess) return fail(b.members[0], DEM_ERR_DEVICE, hip_msg(he, "step"));
+    for (dem_sim* s : b.members) s->regrid = false;
+    --n_steps;
+  }
+  if (n_steps == 0) {
+    // that was the only step
+  } else if (e->profiling) {
     dem_status r = profiled_passes(b, e->stream, n_steps, e->events, e->prof_ms, e->prof_steps,
                                    b.members[0]);
     if (r != DEM_OK) return r;

@@ -49,14 +49,20 @@ struct ContactParams {
   double max_overlap_frac;   // <= 0: no check
 };
 
-// Per-pile cell grid, written on the device every step.
-struct Grid {
+// Cells of a pile.
+struct CellGrid {
   double lo[3];              // origin of cell (0,0,0)
   double cell;               // cell side (>= largest sphere diameter)
   double inv_cell;
-  double com[3];             // centre of mass of the pile (spin-up forcing)
   int32_t nc[3];             // cells per axis
   int32_t nbits[3];          // key bits per axis (sum 3 * bits)
+};
+
+// What the spheres of an evaluation as a whole determine, and the cells of the
+// evaluations at both parities, written on the device every step.
+struct Grid {
+  CellGrid c[2];
+  double com[3];             // centre of mass of the pile (spin-up forcing)
   double t;                  // time of this evaluation
   double R_bulk;             // bulk radius sqrt(5/3 <|r - com|^2>_m) of this evaluation
   double wall_d[6];          // plane offset of each wall at time t
@@ -111,7 +117,11 @@ struct PileDev {
                              // to reconstruct them from; stateless test hooks)
   int32_t fused;             // 1: the whole step runs in one workgroup (k_fused); the staged
                              // kernels launched over every pile skip it
-  int32_t rows;              // 1: cell keys are row-major (no gravity), 0: Morton
+  // 1 (no gravity): cell keys are row-major and the spheres are binned on the
+  // cells of the evaluation before, so that moving and binning are one launch;
+  // no result depends on the cells or on the order inside them.  0: Morton keys
+  // on the cells of this evaluation, whose order gravity sums follow.
+  int32_t rows;
   // uniform field and container walls (host-set)
   int32_t n_walls;
   int32_t pad3;
@@ -171,7 +181,8 @@ struct PileDev {
   double* tau;               // [3][ns] contact torque about the centre
   uint32_t* key;             // [ns] Morton cell code
   uint32_t* sidx;            // [ns] sphere at sorted slot (piles with gravity)
-  uint32_t* sidx_raw;        // [ns] sphere at slot, in atomic arrival order
+  uint32_t* num;             // [ns] arrival number of sphere i in its cell
+  uint32_t* sidx_raw;        // [ns] sphere at slot, in arrival order (piles with gravity)
   SortedGeom* xg;            // [ns] sorted x, y, z, radius (search)
   SortedId* sid;             // [ns] sorted aggregate id and sphere id
   void* jrec;                // gravity records in sorted order (64 B, FP64)
@@ -186,6 +197,7 @@ struct PileDev {
   // contacts listed so far by the search of this evaluation: upper in the
   // high word, lower in the low (reset with the cell grid; on a line of its
   // own, as every block of the search adds to it)
+  // and, beside it, the blocks of the member reduction that are done
   unsigned long long* runs;
   uint2* up_run[2];          // [ns] first entry and length of sphere i's contacts (i, j > i)
   uint2* lo_run;             // [ns] the same of its contacts (j, i), j < i
@@ -222,7 +234,7 @@ struct GravItem {
 
 // One segment of the batched exclusive scan (out[n] receives the total).
 struct ScanSeg {
-  const uint32_t* in;
+  uint32_t* in;
   uint32_t* out;
   int32_t n;
   int32_t item0;             // first work item of this segment
@@ -240,10 +252,17 @@ struct ScanItem {
 // ---------------------------------------------------------------------------
 void launch_setup(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk,
                   const double* pos_in, const double* vel_in, const double* spin_in);
+// bin: piles of row-major cells are binned too, on the cells they carry
 void launch_move(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk,
-                 ContactParams cp, int mode);
-void launch_grid(hipStream_t st, const PileDev* piles, int n_piles, int mode, double dt);
+                 ContactParams cp, int mode, bool bin);
+// Cells of this evaluation (and, in piles that carry them, of the next) of the
+// listed piles (plist NULL: the first n).
+void launch_grid(hipStream_t st, const PileDev* piles, const int32_t* plist, int n, int mode,
+                 double dt);
 void launch_bin(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk);
+// Sorted copies of piles without gravity, in arrival order inside a cell.
+void launch_place(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk);
+// Piles with gravity: slots in arrival order, then ordered by id and copied.
 void launch_scatter(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk);
 void launch_cell_sort(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk);
 void launch_search(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk);
@@ -297,8 +316,11 @@ constexpr int64_t kSymPartialMax = int64_t(64) << 30;
 // Spheres in one search launch from which each sphere gets one lane instead
 // of eight.
 constexpr int64_t kSearchLargeLaunch = 32768;
-void launch_reduce(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk,
-                   ContactParams cp, int mode, bool stage);
+// finish: the last block of a pile ends its step (else launch_finish does)
+void launch_reduce(hipStream_t st, PileDev* piles, const WorkItem* wl, int nblk, ContactParams cp,
+                   int mode, bool stage, bool finish);
+// Blocks of one pile in the reduction up to which its last block ends the step.
+constexpr int kFinishInReduce = 64;
 void launch_finish(hipStream_t st, PileDev* piles, int n_piles, int mode, double dt);
 // any_order[0], [1]: some tree pile of multipole order 2, 4
 // leaf_levels: bit l set when level l is some pile's finest
@@ -306,6 +328,7 @@ void launch_tree(hipStream_t st, const PileDev* piles, WorkItem* const* wl_level
                  const int* n_level, unsigned leaf_levels, const WorkItem* wl_sph, int n_sph_blk,
                  const bool* any_order);
 void launch_fill_u32(hipStream_t st, uint32_t* p, uint32_t value, int64_t n);
+void launch_clear(hipStream_t st, const PileDev& h, int64_t cells);
 // The whole step of each listed pile in one workgroup: part 1 the stages
 // before gravity, part 2 those after it, part 3 all (no gravity).
 void launch_fused(hipStream_t st, const PileDev* piles, const int32_t* plist, int n,
@@ -315,8 +338,16 @@ void launch_fused(hipStream_t st, const PileDev* piles, const int32_t* plist, in
 // a few hundred spheres (measured on MI355X: 97 spheres 41 us vs 52 us
 // staged, 303 spheres 67 vs 58 us, 962 spheres 148 vs 65 us per step).
 constexpr int64_t kFusedAutoMax = 256;
+// Counts are returned to zero.  grids: that many listed piles get the cells of
+// their next evaluation from the same launch.
+struct ScanGrids {
+  PileDev* piles;
+  const int32_t* plist;
+  int n, mode;
+  double dt;
+};
 void launch_scan(hipStream_t st, const ScanSeg* segs, int n_segs, const ScanItem* items,
-                 int n_items, uint32_t* item_sums, int max_seg_items);
+                 int n_items, uint32_t* item_sums, int max_seg_items, ScanGrids grids);
 
 // ---------------------------------------------------------------------------
 // small device helpers

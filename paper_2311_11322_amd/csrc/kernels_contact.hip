@@ -3,9 +3,12 @@
 // history (Sec. 2.1, 2.2.4 and 2.2.5 of the paper; lever arm Eq. 8, contact-point
 // torque Eq. 9).
 //
-// Binning is a counting sort on Morton cell codes: integer atomics build the
-// per-cell counts, a batched exclusive scan turns them into cell ranges, and
-// ranking each sphere by id within its cell makes the order deterministic.
+// Binning is a counting sort on cell keys: integer atomics build the per-cell
+// counts, a batched exclusive scan turns them into cell ranges, and the spheres
+// are placed there.  Without gravity any order inside a cell will do, so the
+// number that its atomic returned places a sphere; with gravity the slots set
+// the order of the force sums, and ranking each sphere by id within its cell
+// makes it deterministic.
 // The search scans the 27 neighbouring cells of every sphere (a group of
 // lanes per sphere, blocks mapped to XCDs by region); each sphere lists
 // its contacts with higher ids (the canonical upper list) and with lower ids
@@ -27,8 +30,15 @@ __global__ __launch_bounds__(kBlock) void k_bin(const PileDev* __restrict__ pile
   bin_one(P, i);
 }
 
-// Place each sphere into its cell's range (in atomic arrival order); the
-// counts return to zero, ready for the next step.
+__global__ __launch_bounds__(kBlock) void k_place(const PileDev* __restrict__ piles,
+                                                  const WorkItem* __restrict__ wl) {
+  const WorkItem w = wl[xcd_block(blockIdx.x, gridDim.x)];
+  const PileDev& P = piles[w.pile];
+  const int i = w.base + threadIdx.x;
+  if (i >= P.ns || P.status != 0) return;
+  place_one(P, i);
+}
+
 __global__ __launch_bounds__(kBlock) void k_scatter(const PileDev* __restrict__ piles,
                                                     const WorkItem* __restrict__ wl) {
   const WorkItem w = wl[xcd_block(blockIdx.x, gridDim.x)];
@@ -57,7 +67,7 @@ __global__ __launch_bounds__(kBlock) void k_cell_sort(const PileDev* __restrict_
 // by id.  (As count, scan of the counts and write it took two launches more:
 // 21.8 -> 12.0 us for 6,400 spheres, 200 -> 131 us for a 1M-sphere lattice.)
 template <int L, int NT>
-__global__ __launch_bounds__(NT) void k_search(PileDev* __restrict__ piles,
+__global__ __launch_bounds__(NT, 5) void k_search(PileDev* __restrict__ piles,
                                                const WorkItem* __restrict__ wl) {
   constexpr int kGroups = NT / L;                // spheres per block
   constexpr int kWaves = NT / 64;
@@ -134,12 +144,19 @@ __global__ __launch_bounds__(kBlock) void k_search_big(PileDev* __restrict__ pil
 }  // namespace
 
 void launch_bin(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk) {
+  if (nblk <= 0) return;
   hipLaunchKernelGGL(k_bin, dim3(nblk), dim3(kBlock), 0, st, piles, wl);
 }
+void launch_place(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk) {
+  if (nblk <= 0) return;
+  hipLaunchKernelGGL(k_place, dim3(nblk), dim3(kBlock), 0, st, piles, wl);
+}
 void launch_scatter(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk) {
+  if (nblk <= 0) return;
   hipLaunchKernelGGL(k_scatter, dim3(nblk), dim3(kBlock), 0, st, piles, wl);
 }
 void launch_cell_sort(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk) {
+  if (nblk <= 0) return;
   hipLaunchKernelGGL(k_cell_sort, dim3(nblk), dim3(kBlock), 0, st, piles, wl);
 }
 void launch_search_big(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk) {

@@ -42,11 +42,11 @@ __device__ __forceinline__ int status_of(const PileDev& P) {
 // status) are read with atomic loads, from the second level.
 __device__ __forceinline__ void stage_sync() { __syncthreads(); }
 
-// Exclusive prefix sum of in[0, n) into out[0, n) and the total into out[n],
-// by the whole workgroup: each thread scans one contiguous run, the run
+// Exclusive prefix sum of in[0, n) into out[0, n) and the total into out[n], in
+// returned to zero, by the whole workgroup: each thread scans one contiguous run, the run
 // totals are scanned across the workgroup.  Integer sums: any order gives
 // the same result.
-__device__ void block_scan(const uint32_t* __restrict__ in, uint32_t* __restrict__ out, int n,
+__device__ void block_scan(uint32_t* __restrict__ in, uint32_t* __restrict__ out, int n,
                            uint32_t* sh /* [kFusedWaves + 1] */) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int per = (n + kFusedThreads - 1) / kFusedThreads;
@@ -69,6 +69,7 @@ __device__ void block_scan(const uint32_t* __restrict__ in, uint32_t* __restrict
   uint32_t run = before + x - sum;
   for (int k = b0; k < b1; ++k) {
     const uint32_t v = in[k];
+    in[k] = 0u;
     out[k] = run;
     run += v;
   }
@@ -144,10 +145,11 @@ __global__ __launch_bounds__(kFusedThreads) void k_fused(PileDev* __restrict__ p
       if ((tid & 63) == 0)
         for (int k = 0; k < kBbox; ++k) red[tid >> 6][k] = acc[k];
       stage_sync();
-      if (tid == 0) {
-        for (int w = 1; w < kFusedWaves; ++w) bbox_combine(red[0], red[w]);
-        grid_from_vals(P, red[0], mode, cp.dt);
+      if (tid < 64) {
+        for (int w = 1; w < kFusedWaves; ++w) bbox_combine(acc, red[w]);
+        grid_from_vals(P, acc, tid, kCellsNow);
       }
+      if ((tid >> 6) == 1) walls_at(P, tid & 63, mode, cp.dt);
       stage_sync();
       ok = status_of(P) == 0;
     }
@@ -158,9 +160,13 @@ __global__ __launch_bounds__(kFusedThreads) void k_fused(PileDev* __restrict__ p
       stage_sync();
       block_scan(P.cell_cnt, P.cell_start, (1 << (3 * P.bits)) + 1, scan_sh);
       stage_sync();
-      for (int i = tid; i < P.ns; i += kFusedThreads) scatter_one(P, i);
-      stage_sync();
-      for (int k = tid; k < P.ns; k += kFusedThreads) cell_sort_one(P, k);
+      if (P.rows) {
+        for (int i = tid; i < P.ns; i += kFusedThreads) place_one(P, i);
+      } else {
+        for (int i = tid; i < P.ns; i += kFusedThreads) scatter_one(P, i);
+        stage_sync();
+        for (int k = tid; k < P.ns; k += kFusedThreads) cell_sort_one(P, k);
+      }
       stage_sync();
       // contact search (the counter was cleared before the last barriers)
       search_all(P, search_sh, &run_total, big_up, big_lo, big_fill);

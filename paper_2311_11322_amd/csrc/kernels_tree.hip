@@ -470,7 +470,7 @@ __global__ __launch_bounds__(64) void k_tree_walk(const PileDev* __restrict__ pi
     // (a tree pile has at least two levels)
     const Rec64* r0 = (const Rec64*)P.jrec + w.base;
     const double xyz[3] = {r0->x, r0->y, r0->z};
-    const Grid& g0 = *P.grid;
+    const CellGrid& g0 = P.grid->c[P.parity];
     int d1 = 0, d2 = 0;
     for (int a = 0; a < 3; ++a) {
       const int c = cell_coord(xyz[a], g0.lo[a], g0.inv_cell, 1 << L, 0, 0.0);
@@ -485,7 +485,7 @@ __global__ __launch_bounds__(64) void k_tree_walk(const PileDev* __restrict__ pi
   const ConstRec64 rec = (ConstRec64)P.jrec;
   const ConstU cstart = (ConstU)P.cell_start;
   const ConstD mom = (ConstD)P.tmom;
-  const Grid& g = *P.grid;
+  const CellGrid& g = P.grid->c[P.parity];
   const double cell = g.cell, theta = P.theta;
   double x = 0.0, y = 0.0, z = 0.0, ei = 0.0;
   if (active) {

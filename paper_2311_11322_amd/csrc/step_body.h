@@ -247,24 +247,37 @@ __device__ __forceinline__ void move_block(PileDev& P, int base, const ContactPa
   }
 }
 
-// The pile's cell grid, centre of mass, bulk radius and stop rule, wall
-// offsets and velocities, from the reduced partials of all its spheres.
+// Which cells an evaluation's bounding box sets: those of this evaluation (1),
+// those of the next (2).
+constexpr int kCellsNow = 1, kCellsNext = 2;
+
+// A lane's value in every lane of the wave.
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffff), lane);
+  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// The pile's centre of mass, bulk radius and stop rule, and the cells named by
+// cells, from the reduced partials of all its spheres: by one wave, every lane
+// with the same vals.
 // Cells are at least one largest-sphere diameter; an open pile's grid spans
 // its bounding box, or only the part of it within three rms radii of the
 // centre of mass when that is smaller.
-__device__ __forceinline__ void grid_from_vals(PileDev& P, double vals[kBbox], int mode,
-                                               double dt) {
-  *P.runs = 0ull;                      // the search of this evaluation starts
-  // written in place: a local Grid (its wall arrays indexed by a count
-  // known only at run time) would live in scratch memory
-  Grid& g = *P.grid;
+__device__ __forceinline__ void grid_from_vals(PileDev& P, const double vals[kBbox], int lane,
+                                               int cells) {
+  if (lane == 0) *P.runs = 0ull;       // the search of this evaluation starts
+  Grid& gr = *P.grid;
+  CellGrid g;
   bool finite = true;
   for (int k = 0; k < kBbox; ++k) finite = finite && isfinite(vals[k]);
   if (!finite) {
-    atomicOr(&P.status, kStUnstable);
+    if (lane == 0) atomicOr(&P.status, kStUnstable);
     return;
   }
-  for (int k = 0; k < 3; ++k) g.com[k] = vals[7 + k] / vals[6];
+  double com[3];
+  for (int k = 0; k < 3; ++k) com[k] = vals[7 + k] / vals[6];
   // second moment about the centre of mass, from the one about the reference
   // point c: <|r - com|^2>_m = <|r - c|^2>_m - |com - c|^2
   double s2;
@@ -272,10 +285,10 @@ __device__ __forceinline__ void grid_from_vals(PileDev& P, double vals[kBbox], i
     double c[3];
     bbox_ref(P, c);
     s2 = vals[10] / vals[6];
-    for (int k = 0; k < 3; ++k) s2 -= (g.com[k] - c[k]) * (g.com[k] - c[k]);
+    for (int k = 0; k < 3; ++k) s2 -= (com[k] - c[k]) * (com[k] - c[k]);
     s2 = fmax(s2, 0.0);
   }
-  g.R_bulk = sqrt(s2 * (5.0 / 3.0));
+  const double R_bulk = sqrt(s2 * (5.0 / 3.0));
   if (P.periodic) {
     for (int k = 0; k < 3; ++k) {
       g.nc[k] = P.n_periodic;
@@ -298,8 +311,8 @@ __device__ __forceinline__ void grid_from_vals(PileDev& P, double vals[kBbox], i
       // the 27-cell search still finds every contact)
       const double h = 3.0 * sqrt(s2) + P.cell_min;
       for (int k = 0; k < 3; ++k) {
-        lo[k] = fmax(lo[k], g.com[k] - h);
-        hi[k] = fmax(lo[k], fmin(hi[k], g.com[k] + h));
+        lo[k] = fmax(lo[k], com[k] - h);
+        hi[k] = fmax(lo[k], fmin(hi[k], com[k] + h));
       }
     }
     // cube cells; the key's 3 * bits bits go one at a time to the axis whose
@@ -310,34 +323,24 @@ __device__ __forceinline__ void grid_from_vals(PileDev& P, double vals[kBbox], i
       g.lo[k] = lo[k];
       ext[k] = hi[k] - lo[k];
     }
-    // per-axis bit counts kept in scalars (an array indexed by the chosen
-    // axis would live in scratch memory)
-    int b0 = 0, b1 = 0, b2 = 0;
-    for (int t = 0; t < 3 * P.bits; ++t) {
-      if (P.tree) {                      // the tree's pyramid needs a cubic code
-        const int a = t % 3;
-        b0 += a == 0;
-        b1 += a == 1;
-        b2 += a == 2;
-        continue;
+    int b0 = P.bits, b1 = P.bits, b2 = P.bits;
+    if (!P.tree) {                       // the tree's pyramid needs a cubic code
+      // handing out bits one by one to the axis with the longest cells (below
+      // 10 bits, the first axis on a tie) takes the 3 * bits longest of the
+      // lengths ext / 2^n, n < 10, of the axes: lane (axis, n) ranks its length
+      const int axis = lane / 10, n = lane % 10;
+      const double len = lane < 30 ? ldexp(axis == 0 ? ext[0] : (axis == 1 ? ext[1] : ext[2]), -n)
+                                   : -1.0;
+      int rank = 0;
+#pragma unroll
+      for (int q = 0; q < 30; ++q) {
+        const double o = lane_value(len, q);
+        rank += (o > len || (o == len && (q / 10 < axis || (q / 10 == axis && q % 10 < n)))) ? 1 : 0;
       }
-      // the axis with the longest cells among those below 10 bits (the
-      // first one on a tie)
-      int a = -1;
-      double best = -1.0;
-      const double l0 = ldexp(ext[0], -b0), l1 = ldexp(ext[1], -b1), l2 = ldexp(ext[2], -b2);
-      if (b0 < 10 && l0 > best) {
-        best = l0;
-        a = 0;
-      }
-      if (b1 < 10 && l1 > best) {
-        best = l1;
-        a = 1;
-      }
-      if (b2 < 10 && l2 > best) a = 2;
-      b0 += a == 0;
-      b1 += a == 1;
-      b2 += a == 2;
+      const uint64_t in = __ballot(lane < 30 && rank < 3 * P.bits);
+      b0 = __popcll(in & 0x3ffull);
+      b1 = __popcll(in & 0xffc00ull);
+      b2 = __popcll(in & 0x3ff00000ull);
     }
     const int b[3] = {b0, b1, b2};
     double fit = 0.0;
@@ -349,37 +352,78 @@ __device__ __forceinline__ void grid_from_vals(PileDev& P, double vals[kBbox], i
     g.cell = fmax(P.cell_min, fit + 1e-300);
   }
   g.inv_cell = 1.0 / g.cell;
+  if (lane != 0) return;
+  if (cells & kCellsNow) gr.c[P.parity] = g;
+  if (cells & kCellsNext) gr.c[P.parity ^ 1] = g;
+  for (int k = 0; k < 3; ++k) gr.com[k] = com[k];
+  gr.R_bulk = R_bulk;
   if (P.stop_growth > 0.0) {
     // the stop rule: the first evaluation sets the reference radius; an
     // evaluation at or beyond stop_growth times it stops the pile (its step
     // is not committed, like a failure)
     if (!(P.R0 > 0.0)) {
-      P.R0 = g.R_bulk;
-    } else if (g.R_bulk >= P.stop_growth * P.R0) {
+      P.R0 = R_bulk;
+    } else if (R_bulk >= P.stop_growth * P.R0) {
       atomicOr(&P.status, kStStopped);
     }
   }
-  // time of this evaluation: the end of the step being taken, or the
-  // current time for an evaluation in place; walls displaced rigidly by
-  // A sin(omega t + phase), moving at A omega cos(omega t + phase)
-  g.t = (double)(P.step + (mode == kModeStep ? 1 : 0)) * dt;
-  for (int w = 0; w < 6; ++w) {
-    g.wall_d[w] = 0.0;
-    for (int k = 0; k < 3; ++k) g.wall_v[w][k] = 0.0;
-  }
-  if (P.n_walls > 0) {
-    const double ph = rn_add(rn_mul(P.wall_omega, g.t), P.wall_phase);
+}
+
+// Time of this evaluation (the end of the step being taken, or the current
+// time for an evaluation in place) and the walls at that time, wall w by lane
+// w of a wave: displaced rigidly by A sin(omega t + phase), moving at
+// A omega cos(omega t + phase).
+__device__ __forceinline__ void walls_at(const PileDev& P, int lane, int mode, double dt) {
+  Grid& g = *P.grid;
+  const double t = (double)(P.step + (mode == kModeStep ? 1 : 0)) * dt;
+  if (lane == 0) g.t = t;
+  if (lane >= 6) return;
+  double d = 0.0, v[3] = {0.0, 0.0, 0.0};
+  if (lane < P.n_walls) {
+    const double ph = rn_add(rn_mul(P.wall_omega, t), P.wall_phase);
     double sn, cs;
     sincos(ph, &sn, &cs);
-    for (int w = 0; w < P.n_walls; ++w) {
-      const double* n = P.wall[w];
-      const double* A = P.wall_amp[w];
-      const double shift =
-          rn_add(rn_add(rn_mul(n[0], A[0]), rn_mul(n[1], A[1])), rn_mul(n[2], A[2]));
-      g.wall_d[w] = rn_add(n[3], rn_mul(shift, sn));
-      for (int k = 0; k < 3; ++k) g.wall_v[w][k] = rn_mul(rn_mul(A[k], P.wall_omega), cs);
-    }
+    const double* n = P.wall[lane];
+    const double* A = P.wall_amp[lane];
+    const double shift =
+        rn_add(rn_add(rn_mul(n[0], A[0]), rn_mul(n[1], A[1])), rn_mul(n[2], A[2]));
+    d = rn_add(n[3], rn_mul(shift, sn));
+    for (int k = 0; k < 3; ++k) v[k] = rn_mul(rn_mul(A[k], P.wall_omega), cs);
   }
+  g.wall_d[lane] = d;
+  for (int k = 0; k < 3; ++k) g.wall_v[lane][k] = v[k];
+}
+
+// The pile's block partials combined by a block of 256 threads (each thread its
+// share in block order, then across the block), and from them its grid
+// (grid_from_vals); the walls by another wave meanwhile.
+struct GridLds {
+  double red[4][kBbox];
+};
+__device__ __forceinline__ void grid_block(PileDev& P, int mode, double dt, int cells,
+                                           GridLds& sh) {
+  constexpr int kThreads = 256;
+  double vals[kBbox];
+  bbox_identity(vals);
+  // unrolled so that several partials' loads are in flight (same order)
+#pragma unroll 4
+  for (int b = threadIdx.x; b < P.n_rblk; b += kThreads) {
+    const double* p = P.bpart + (size_t)b * kBbox;
+    bbox_combine(vals, p);
+  }
+  for (int off = 32; off > 0; off >>= 1) {
+    double o[kBbox];
+    for (int k = 0; k < kBbox; ++k) o[k] = __shfl_xor(vals[k], off);
+    bbox_combine(vals, o);
+  }
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  if (lane == 0)
+    for (int k = 0; k < kBbox; ++k) sh.red[wave][k] = vals[k];
+  __syncthreads();
+  if (wave == 1) walls_at(P, lane, mode, dt);
+  if (wave != 0) return;
+  for (int j = 1; j < kThreads / 64; ++j) bbox_combine(vals, sh.red[j]);
+  grid_from_vals(P, vals, lane, cells);
 }
 
 // Force on sphere i: its contact force plus, in a pile with gravity, its
@@ -452,10 +496,10 @@ __device__ __forceinline__ void reduce_tail(const PileDev& P, int A, const doubl
     for (int k = 0; k < 3; ++k) v[k] = P.vA[nxt][k * na + A] + 0.5 * cp.dt * a[k];
     if (P.spin_dw != 0.0) {
       // spin-up: w += dw z-hat about the pile's centre of mass
-      const Grid g = *P.grid;
+      const double* com = P.grid->com;
       const double dw = P.spin_dw;
-      const double rel[3] = {P.rA[nxt][A] - g.com[0], P.rA[nxt][na + A] - g.com[1],
-                             P.rA[nxt][2 * na + A] - g.com[2]};
+      const double rel[3] = {P.rA[nxt][A] - com[0], P.rA[nxt][na + A] - com[1],
+                             P.rA[nxt][2 * na + A] - com[2]};
       const double z[3] = {0.0, 0.0, dw};
       double dv[3], dwb[3];
       cross3(z, rel, dv);

@@ -14,7 +14,7 @@ namespace dem {
 namespace {
 
 // Cell of a sphere on the pile's current grid.
-__device__ __forceinline__ void sphere_cell(const PileDev& P, const Grid& g, double x, double y,
+__device__ __forceinline__ void sphere_cell(const PileDev& P, const CellGrid& g, double x, double y,
                                             double z, int c[3]) {
   c[0] = cell_coord(x, g.lo[0], g.inv_cell, g.nc[0], P.periodic, P.box);
   c[1] = cell_coord(y, g.lo[1], g.inv_cell, g.nc[1], P.periodic, P.box);
@@ -24,58 +24,68 @@ __device__ __forceinline__ void sphere_cell(const PileDev& P, const Grid& g, dou
 // Key of a cell: row-major in a pile without gravity, so that the search reads
 // a row of neighbours as one range; Morton in a pile with gravity, whose tiles
 // and tree nodes are runs of neighbouring cells.
-__device__ __forceinline__ uint32_t cell_key(const PileDev& P, const Grid& g, int cx, int cy,
+__device__ __forceinline__ uint32_t cell_key(const PileDev& P, const CellGrid& g, int cx, int cy,
                                              int cz) {
   return P.rows ? (uint32_t)((cz * g.nc[1] + cy) * g.nc[0] + cx)
                 : morton_key(cx, cy, cz, g.nbits);
 }
 
-// Cell key of sphere i and its count (integer atomics on the cell table).
+// Cell key of a sphere with radius s at (x, y, z): the big spheres' cell comes
+// after all the others.
+__device__ __forceinline__ uint32_t sphere_key(const PileDev& P, const CellGrid& g, double x,
+                                               double y, double z, double s) {
+  if (P.n_big > 0 && s > P.s_cut) return 1u << (3 * P.bits);
+  int c[3];
+  sphere_cell(P, g, x, y, z, c);
+  return cell_key(P, g, c[0], c[1], c[2]);
+}
+
+// Cell key of sphere i and its arrival number in the cell (integer atomics on
+// the cell counts).
 __device__ __forceinline__ void bin_one(const PileDev& P, int i) {
-  const Grid g = *P.grid;
   const int ns = P.ns;
-  uint32_t key;
-  if (P.n_big > 0 && P.s[i] > P.s_cut) {
-    key = 1u << (3 * P.bits);               // the cell after the Morton cells
-  } else {
-    int c[3];
-    sphere_cell(P, g, P.r[i], P.r[ns + i], P.r[2 * ns + i], c);
-    key = cell_key(P, g, c[0], c[1], c[2]);
-  }
+  const uint32_t key = sphere_key(P, P.grid->c[P.parity], P.r[i], P.r[ns + i], P.r[2 * ns + i],
+                                  P.n_big > 0 ? P.s[i] : 0.0);
   P.key[i] = key;
-  atomicAdd(&P.cell_cnt[key], 1u);
+  P.num[i] = atomicAdd(&P.cell_cnt[key], 1u);
 }
 
-// Place sphere i into its cell's range (in atomic arrival order); the
-// counts return to zero, ready for the next step.
-__device__ __forceinline__ void scatter_one(const PileDev& P, int i) {
-  const uint32_t key = P.key[i];
-  const uint32_t k = atomicSub(&P.cell_cnt[key], 1u) - 1u;
-  P.sidx_raw[P.cell_start[key] + k] = (uint32_t)i;
-}
-
-// Order one cell's spheres by id, independent of atomic arrival order: the
-// sphere at raw slot k goes to its cell's start plus its rank (the number of
-// smaller ids in the cell).  The same thread writes the sphere's sorted
-// copies there: packed records for the search and, in a pile with gravity, its
-// source record and id.
-__device__ __forceinline__ void cell_sort_one(const PileDev& P, int k) {
+// The sorted copies of sphere i at slot d: packed records for the search and, in
+// a pile with gravity, its source record and id.
+__device__ __forceinline__ void place_sphere(const PileDev& P, uint32_t i, uint32_t d) {
   const int ns = P.ns;
-  const uint32_t* __restrict__ raw = P.sidx_raw;
-  const uint32_t i = raw[k];
-  const uint32_t key = P.key[i];
-  const uint32_t s0 = P.cell_start[key], s1 = P.cell_start[key + 1];
-  uint32_t r = 0;
-  for (uint32_t t = s0; t < s1; ++t) r += raw[t] < i;
-  const uint32_t d = s0 + r;
   const double x = P.r[i], y = P.r[ns + i], z = P.r[2 * ns + i], s = P.s[i];
-  if (P.G != 0.0) {                          // only gravity reads these copies
+  if (P.G != 0.0) {
     const double e = 0.5 * P.soft_frac * s;
     P.sidx[d] = i;
     ((Rec64*)P.jrec)[d] = Rec64{x, y, z, P.m[i], e, 0.0, 0.0, 0.0};
   }
   P.xg[d] = SortedGeom{x, y, z, s};
   P.sid[d] = SortedId{P.agg[i], i};
+}
+
+// Place sphere i, in arrival order inside its cell (piles without gravity: no
+// result depends on that order).
+__device__ __forceinline__ void place_one(const PileDev& P, int i) {
+  place_sphere(P, (uint32_t)i, P.cell_start[P.key[i]] + P.num[i]);
+}
+
+// Enter sphere i in its cell's range, in arrival order.
+__device__ __forceinline__ void scatter_one(const PileDev& P, int i) {
+  P.sidx_raw[P.cell_start[P.key[i]] + P.num[i]] = (uint32_t)i;
+}
+
+// Order one cell's spheres by id, independent of arrival order: the sphere at
+// raw slot k goes to its cell's start plus its rank (the number of smaller ids
+// in the cell).
+__device__ __forceinline__ void cell_sort_one(const PileDev& P, int k) {
+  const uint32_t* __restrict__ raw = P.sidx_raw;
+  const uint32_t i = raw[k];
+  const uint32_t key = P.key[i];
+  const uint32_t s0 = P.cell_start[key], s1 = P.cell_start[key + 1];
+  uint32_t r = 0;
+  for (uint32_t t = s0; t < s1; ++t) r += raw[t] < i;
+  place_sphere(P, i, s0 + r);
 }
 
 // Contact test exactly as written d^2 = (dx*dx + dy*dy) + dz*dz < S*S, each
@@ -127,7 +137,7 @@ __device__ __forceinline__ void search_partners(const PileDev& P, int k, int lan
   const int ns = P.ns;
   const SortedGeom* __restrict__ xg = P.xg;
   const SortedId* __restrict__ sid = P.sid;
-  const Grid& g = *P.grid;
+  const CellGrid& g = P.grid->c[P.parity];
   const uint32_t* __restrict__ cstart = P.cell_start;
   const SortedGeom mg = xg[k];
   const double x = mg.x, y = mg.y, z = mg.z, si = mg.s;
@@ -214,7 +224,7 @@ __device__ __forceinline__ void search_partners(const PileDev& P, int k, int lan
   }
   // walls are partners ns + w, after every sphere partner
   for (int w = lane; w < P.n_walls; w += Lanes)
-    if (wall_gap(P, w, g.wall_d[w], x, y, z) < si) emit((uint32_t)(ns + w));
+    if (wall_gap(P, w, P.grid->wall_d[w], x, y, z) < si) emit((uint32_t)(ns + w));
 }
 
 // A lane group's part of the LDS of a search by NT threads: kRunLds ids, which
@@ -366,7 +376,7 @@ __device__ __forceinline__ void search_big_one(PileDev& P, int kb, int tid, int 
   const uint32_t* __restrict__ cstart = P.cell_start;
   const int periodic = P.periodic;
   const double L = P.box;
-  const Grid& g = *P.grid;
+  const CellGrid& g = P.grid->c[P.parity];
   int c[3];
   sphere_cell(P, g, x, y, z, c);
   // reach in cells of any partner: (s_i + s_small) / cell, plus one for rounding
@@ -415,7 +425,7 @@ __device__ __forceinline__ void search_big_one(PileDev& P, int kb, int tid, int 
   const uint32_t bk = 1u << (3 * P.bits);
   for (uint32_t t = cstart[bk] + tid; t < cstart[bk + 1]; t += nthreads) test(t);
   for (int wi_ = tid; wi_ < P.n_walls; wi_ += nthreads) {
-    if (wall_gap(P, wi_, g.wall_d[wi_], x, y, z) < si) {
+    if (wall_gap(P, wi_, P.grid->wall_d[wi_], x, y, z) < si) {
       const uint32_t pos = atomicAdd(&fill[0], 1u);
       if (pos < (uint32_t)kBigRun) buf_up[pos] = (uint32_t)(ns + wi_);
     }
