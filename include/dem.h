@@ -179,7 +179,8 @@ dem_status dem_add_aggregates(dem_sim* sim, int64_t n_agg, const int32_t* sphere
                               const double* sphere_mass, const double* agg_vel,
                               const double* agg_spin, int64_t* first_agg_id);
 
-/* Advance n_steps fixed steps (replays of one captured HIP graph).  Returns
+/* Advance n_steps fixed steps (replays of one captured HIP graph; a small system
+ * without gravity takes up to 64 steps in one launch).  Returns
  * after the work is complete.  On CAPACITY / UNSTABLE (and on DEM_STOPPED,
  * the stop rule of dem_forcing) the state is that at the start of the
  * failing step and dem_state.step tells which step it is.

@@ -616,7 +616,8 @@ void release_side(Batch& b) {
 // have none that suit their positions (the t0 evaluation, the step after a
 // restore), so the cells come first, as in a pile with gravity.
 template <typename Mark>
-void enqueue_pass_marked(Batch& b, hipStream_t st, int mode, Mark mark, bool overlap, bool fresh) {
+void enqueue_pass_marked(Batch& b, hipStream_t st, int mode, Mark mark, bool overlap, bool fresh,
+                         bool whole = true) {
   const int np = (int)b.members.size();
   const bool staged = b.n_staged > 0;
   auto stage = [&](int k, hipStream_t s, bool run, auto&& launch) {
@@ -624,10 +625,12 @@ void enqueue_pass_marked(Batch& b, hipStream_t st, int mode, Mark mark, bool ove
     if (run) launch(s);
     mark(k, s, false);
   };
-  // small piles: their whole step (part 3), or the stages before gravity (part 1)
+  // small piles: their whole step (part 3) unless that is launched for several
+  // steps at once (fused_steps), or the stages before gravity (part 1)
   stage(kStageFusedA, st, b.n_fused_ng + b.n_fused_g > 0, [&](hipStream_t s) {
-    launch_fused(s, b.d_table, b.pl_fused_ng, b.n_fused_ng, b.cp, mode, 3, b.precision);
-    launch_fused(s, b.d_table, b.pl_fused_g, b.n_fused_g, b.cp, mode, 1, b.precision);
+    if (whole)
+      launch_fused(s, b.d_table, b.pl_fused_ng, b.n_fused_ng, b.cp, mode, 3, b.precision, 1);
+    launch_fused(s, b.d_table, b.pl_fused_g, b.n_fused_g, b.cp, mode, 1, b.precision, 1);
   });
   stage(0, st, staged, [&](hipStream_t s) {
     launch_move(s, b.d_table, b.wl_sph, b.n_sph_blk, b.cp, mode, !fresh);
@@ -682,7 +685,7 @@ void enqueue_pass_marked(Batch& b, hipStream_t st, int mode, Mark mark, bool ove
   if (fork) (void)hipStreamWaitEvent(st, b.join_ev, 0);
   else stage(kStageGravity, st, b.any_grav, gravity);
   stage(kStageFusedB, st, b.n_fused_g > 0, [&](hipStream_t s) {
-    launch_fused(s, b.d_table, b.pl_fused_g, b.n_fused_g, b.cp, mode, 2, b.precision);
+    launch_fused(s, b.d_table, b.pl_fused_g, b.n_fused_g, b.cp, mode, 2, b.precision, 1);
   });
   stage(9, st, staged, [&](hipStream_t s) {
     launch_reduce(s, b.d_table, b.wl_agg, b.n_agg_blk, b.cp, mode, b.reduce_stage,
@@ -693,8 +696,9 @@ void enqueue_pass_marked(Batch& b, hipStream_t st, int mode, Mark mark, bool ove
   });
 }
 
-void enqueue_pass(Batch& b, hipStream_t st, int mode, bool overlap, bool fresh) {
-  enqueue_pass_marked(b, st, mode, [](int, hipStream_t, bool) {}, overlap, fresh);
+void enqueue_pass(Batch& b, hipStream_t st, int mode, bool overlap, bool fresh,
+                  bool whole = true) {
+  enqueue_pass_marked(b, st, mode, [](int, hipStream_t, bool) {}, overlap, fresh, whole);
 }
 
 // The sorted copies of a batch whose positions are given (stateless hooks).
@@ -718,13 +722,30 @@ dem_status ensure_graph(Batch& b, hipStream_t st, dem_sim* errsim) {
     own_stream = true;
   }
   HIPCHK(errsim, hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
-  enqueue_pass(b, cap, kModeStep, true, false);
+  enqueue_pass(b, cap, kModeStep, true, false, false);
   hipGraph_t g = nullptr;
   hipError_t e = hipStreamEndCapture(cap, &g);
   if (own_stream) (void)hipStreamDestroy(cap);
   if (e != hipSuccess) return fail(errsim, DEM_ERR_DEVICE, hip_msg(e, "graph capture"));
   b.graph_def = g;
   HIPCHK(errsim, hipGraphInstantiate(&b.graph, g, nullptr, nullptr, 0));
+  return DEM_OK;
+}
+
+// n_steps steps of every member: the piles that one workgroup steps by itself
+// (k_fused without gravity) in launches of up to kFusedSteps steps, then the
+// others by as many launches of the captured step.
+dem_status run_steps(Batch& b, hipStream_t st, int64_t n_steps, dem_sim* errsim) {
+  if (b.n_fused_ng > 0) {
+    for (int64_t k = 0; k < n_steps; k += kFusedSteps)
+      launch_fused(st, b.d_table, b.pl_fused_ng, b.n_fused_ng, b.cp, kModeStep, 3, b.precision,
+                   (int)std::min<int64_t>(kFusedSteps, n_steps - k));
+    HIPCHK(errsim, hipGetLastError());
+  }
+  if (b.n_staged + b.n_fused_g == 0) return DEM_OK;
+  dem_status r = ensure_graph(b, st, errsim);
+  if (r != DEM_OK) return r;
+  for (int64_t k = 0; k < n_steps; ++k) HIPCHK(errsim, hipGraphLaunch(b.graph, st));
   return DEM_OK;
 }
 
@@ -1350,9 +1371,8 @@ dem_status dem_step(dem_sim* s, int64_t n_steps) {
                                          s->prof_steps, s);
     if (st != DEM_OK) return st;
   } else {
-    dem_status st = ensure_graph(s->own, s->stream, s);
+    dem_status st = run_steps(s->own, s->stream, n_steps, s);
     if (st != DEM_OK) return st;
-    for (int64_t k = 0; k < n_steps; ++k) HIPCHK(s, hipGraphLaunch(s->own.graph, s->stream));
   }
   HIPCHK(s, get_entry(s, s->own.d_table, s->stream));
   if (s->h.status != 0) {
@@ -2186,13 +2206,8 @@ dem_status dem_engine_step(dem_engine* e, int64_t n_steps) {
                                    b.members[0]);
     if (r != DEM_OK) return r;
   } else {
-    dem_status r = ensure_graph(b, e->stream, b.members[0]);
+    dem_status r = run_steps(b, e->stream, n_steps, b.members[0]);
     if (r != DEM_OK) return r;
-    for (int64_t k = 0; k < n_steps; ++k) {
-      hipError_t he = hipGraphLaunch(b.graph, e->stream);
-      if (he != hipSuccess)
-        return fail(b.members[0], DEM_ERR_DEVICE, hip_msg(he, "hipGraphLaunch"));
-    }
   }
   // one read-back of every entry's bookkeeping
   std::vector<PileDev> tab(b.members.size());

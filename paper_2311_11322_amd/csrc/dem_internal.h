@@ -330,9 +330,12 @@ void launch_tree(hipStream_t st, const PileDev* piles, WorkItem* const* wl_level
 void launch_fill_u32(hipStream_t st, uint32_t* p, uint32_t value, int64_t n);
 void launch_clear(hipStream_t st, const PileDev& h, int64_t cells);
 // The whole step of each listed pile in one workgroup: part 1 the stages
-// before gravity, part 2 those after it, part 3 all (no gravity).
+// before gravity, part 2 those after it, part 3 all (no gravity); that many steps.
 void launch_fused(hipStream_t st, const PileDev* piles, const int32_t* plist, int n,
-                  ContactParams cp, int mode, int part, int precision);
+                  ContactParams cp, int mode, int part, int precision, int steps);
+// Steps of one launch of k_fused without gravity: a launch apart costs about 8 us
+// beside a step's 28 (97 spheres); the bound keeps a launch to some milliseconds.
+constexpr int kFusedSteps = 64;
 // Piles of at most this many spheres run the fused step unless tuned
 // otherwise: one workgroup hides the latency of its dependent loads only for
 // a few hundred spheres (measured on MI355X: 97 spheres 41 us vs 52 us

@@ -110,7 +110,8 @@ __device__ void search_all(PileDev& P, SearchLds<kFusedLanes, kFusedThreads>& sh
 template <typename T>
 __global__ __launch_bounds__(kFusedThreads) void k_fused(PileDev* __restrict__ piles,
                                                          const int32_t* __restrict__ plist,
-                                                         ContactParams cp, int mode, int part) {
+                                                         ContactParams cp, int mode, int part,
+                                                         int steps) {
   __shared__ SearchLds<kFusedLanes, kFusedThreads> search_sh;
   __shared__ uint32_t big_up[kBigRun];
   __shared__ uint32_t big_lo[kBigRun];
@@ -122,97 +123,100 @@ __global__ __launch_bounds__(kFusedThreads) void k_fused(PileDev* __restrict__ p
   __shared__ MoveLds<kFusedThreads> move_sh;
   PileDev& P = piles[plist[blockIdx.x]];
   const int tid = threadIdx.x;
-  bool ok = status_of(P) == 0;            // a failed pile stays frozen
-  if (part & 1) {
-    if (ok) {
-      // kick, drift and rotate every aggregate; members, and the bounding box
-      // and mass moments of the pile
-      double acc[kBbox], cref[3];
-      bbox_identity(acc);
-      bbox_ref(P, cref);
-      for (int base = 0; base < P.ns; base += kFusedThreads) {
-        double one[kBbox];
-        bbox_identity(one);
-        move_block<kFusedThreads>(P, base, cp, mode, move_sh, cref, one);
-        bbox_combine(acc, one);
-        if (base + kFusedThreads < P.ns) stage_sync();      // move_sh is written again
-      }
-      for (int off = 32; off > 0; off >>= 1) {
-        double o[kBbox];
-        for (int k = 0; k < kBbox; ++k) o[k] = __shfl_xor(acc[k], off);
-        bbox_combine(acc, o);
-      }
-      if ((tid & 63) == 0)
-        for (int k = 0; k < kBbox; ++k) red[tid >> 6][k] = acc[k];
-      stage_sync();
-      if (tid < 64) {
-        for (int w = 1; w < kFusedWaves; ++w) bbox_combine(acc, red[w]);
-        grid_from_vals(P, acc, tid, kCellsNow);
-      }
-      if ((tid >> 6) == 1) walls_at(P, tid & 63, mode, cp.dt);
-      stage_sync();
-      ok = status_of(P) == 0;
-    }
-    if (ok) {
-      // counting sort of the cell keys
-      if (tid == 0) run_total = 0ull;
-      for (int i = tid; i < P.ns; i += kFusedThreads) bin_one(P, i);
-      stage_sync();
-      block_scan(P.cell_cnt, P.cell_start, (1 << (3 * P.bits)) + 1, scan_sh);
-      stage_sync();
-      if (P.rows) {
-        for (int i = tid; i < P.ns; i += kFusedThreads) place_one(P, i);
-      } else {
-        for (int i = tid; i < P.ns; i += kFusedThreads) scatter_one(P, i);
+  for (int step = 0; step < steps; ++step) {
+    bool ok = status_of(P) == 0;            // a failed pile stays frozen
+    if (part & 1) {
+      if (ok) {
+        // kick, drift and rotate every aggregate; members, and the bounding box
+        // and mass moments of the pile
+        double acc[kBbox], cref[3];
+        bbox_identity(acc);
+        bbox_ref(P, cref);
+        for (int base = 0; base < P.ns; base += kFusedThreads) {
+          double one[kBbox];
+          bbox_identity(one);
+          move_block<kFusedThreads>(P, base, cp, mode, move_sh, cref, one);
+          bbox_combine(acc, one);
+          if (base + kFusedThreads < P.ns) stage_sync();      // move_sh is written again
+        }
+        for (int off = 32; off > 0; off >>= 1) {
+          double o[kBbox];
+          for (int k = 0; k < kBbox; ++k) o[k] = __shfl_xor(acc[k], off);
+          bbox_combine(acc, o);
+        }
+        if ((tid & 63) == 0)
+          for (int k = 0; k < kBbox; ++k) red[tid >> 6][k] = acc[k];
         stage_sync();
-        for (int k = tid; k < P.ns; k += kFusedThreads) cell_sort_one(P, k);
+        if (tid < 64) {
+          for (int w = 1; w < kFusedWaves; ++w) bbox_combine(acc, red[w]);
+          grid_from_vals(P, acc, tid, kCellsNow);
+        }
+        if ((tid >> 6) == 1) walls_at(P, tid & 63, mode, cp.dt);
+        stage_sync();
+        ok = status_of(P) == 0;
       }
-      stage_sync();
-      // contact search (the counter was cleared before the last barriers)
-      search_all(P, search_sh, &run_total, big_up, big_lo, big_fill);
-      ok = status_of(P) == 0;
-    }
-    if (ok) {
-      // contact forces with the spring history
-      const PairCtx<T> c = pair_ctx<T>(P, cp);
-      bool bad = false;
-      for (int i = 0; i < P.ns; i += kFusedSpheres)
-        forces_group<T, kFusedThreads, kFusedSpheres>(P, c, cp, i, force_sh, bad);
-      if (bad) atomicOr(&P.status, kStUnstable);
-      stage_sync();
-      ok = status_of(P) == 0;
-    }
-  }
-  if (part & 2) {
-    if (ok) {
-      const int na = P.na, nxt = P.parity ^ 1;
-      for (int A = tid; A < na; A += kFusedThreads) {
-        double q[4], R[9];
-        for (int k = 0; k < 4; ++k) q[k] = P.q[nxt][k * na + A];
-        quat_rot(q, R);
-        double FA[3] = {0.0, 0.0, 0.0}, NA[3] = {0.0, 0.0, 0.0};
-        if (P.member_scan != 0) reduce_members_scan(P, A, R, FA, NA);
-        else reduce_members_direct(P, A, R, FA, NA);
-        reduce_tail(P, A, R, FA, NA, cp, mode);
+      if (ok) {
+        // counting sort of the cell keys
+        if (tid == 0) run_total = 0ull;
+        for (int i = tid; i < P.ns; i += kFusedThreads) bin_one(P, i);
+        stage_sync();
+        block_scan(P.cell_cnt, P.cell_start, (1 << (3 * P.bits)) + 1, scan_sh);
+        stage_sync();
+        if (P.rows) {
+          for (int i = tid; i < P.ns; i += kFusedThreads) place_one(P, i);
+        } else {
+          for (int i = tid; i < P.ns; i += kFusedThreads) scatter_one(P, i);
+          stage_sync();
+          for (int k = tid; k < P.ns; k += kFusedThreads) cell_sort_one(P, k);
+        }
+        stage_sync();
+        // contact search (the counter was cleared before the last barriers)
+        search_all(P, search_sh, &run_total, big_up, big_lo, big_fill);
+        ok = status_of(P) == 0;
       }
-      stage_sync();
+      if (ok) {
+        // contact forces with the spring history
+        const PairCtx<T> c = pair_ctx<T>(P, cp);
+        bool bad = false;
+        for (int i = 0; i < P.ns; i += kFusedSpheres)
+          forces_group<T, kFusedThreads, kFusedSpheres>(P, c, cp, i, force_sh, bad);
+        if (bad) atomicOr(&P.status, kStUnstable);
+        stage_sync();
+        ok = status_of(P) == 0;
+      }
     }
-    if (tid < 64) finish_one(P, tid, mode, cp.dt);
+    if (part & 2) {
+      if (ok) {
+        const int na = P.na, nxt = P.parity ^ 1;
+        for (int A = tid; A < na; A += kFusedThreads) {
+          double q[4], R[9];
+          for (int k = 0; k < 4; ++k) q[k] = P.q[nxt][k * na + A];
+          quat_rot(q, R);
+          double FA[3] = {0.0, 0.0, 0.0}, NA[3] = {0.0, 0.0, 0.0};
+          if (P.member_scan != 0) reduce_members_scan(P, A, R, FA, NA);
+          else reduce_members_direct(P, A, R, FA, NA);
+          reduce_tail(P, A, R, FA, NA, cp, mode);
+        }
+        stage_sync();
+      }
+      if (tid < 64) finish_one(P, tid, mode, cp.dt);
+    }
+    if (step + 1 < steps) stage_sync();     // the entry as the end of the step left it
   }
 }
 
 }  // namespace
 
 void launch_fused(hipStream_t st, const PileDev* piles, const int32_t* plist, int n, ContactParams cp,
-                  int mode, int part, int precision) {
+                  int mode, int part, int precision, int steps) {
   if (n <= 0) return;
   PileDev* p = const_cast<PileDev*>(piles);
   if (precision == 1)
     hipLaunchKernelGGL(k_fused<float>, dim3(n), dim3(kFusedThreads), 0, st, p, plist, cp, mode,
-                       part);
+                       part, steps);
   else
     hipLaunchKernelGGL(k_fused<double>, dim3(n), dim3(kFusedThreads), 0, st, p, plist, cp, mode,
-                       part);
+                       part, steps);
 }
 
 }  // namespace dem
