@@ -337,9 +337,9 @@ void launch_fused(hipStream_t st, const PileDev* piles, const int32_t* plist, in
 // beside a step's 28 (97 spheres); the bound keeps a launch to some milliseconds.
 constexpr int kFusedSteps = 64;
 // Piles of at most this many spheres run the fused step unless tuned
-// otherwise: one workgroup hides the latency of its dependent loads only for
-// a few hundred spheres (measured on MI355X: 97 spheres 41 us vs 52 us
-// staged, 303 spheres 67 vs 58 us, 962 spheres 148 vs 65 us per step).
+// otherwise: one workgroup tests every pair of them itself, the staged step
+// uses the chip (measured per step, fused and staged: 97 spheres 18.8 and 38.2
+// us, 256 spheres 34.5 and 43.0, 300 spheres 45.8 and 43.5).
 constexpr int64_t kFusedAutoMax = 256;
 // Counts are returned to zero.  grids: that many listed piles get the cells of
 // their next evaluation from the same launch.

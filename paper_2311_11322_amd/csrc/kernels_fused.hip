@@ -27,7 +27,9 @@ constexpr int kFusedThreads = 512;
 constexpr int kFusedWaves = kFusedThreads / 64;
 constexpr int kFusedLanes = kLanesSmall;          // lanes per sphere in the search
 constexpr int kFusedGroups = kFusedThreads / kFusedLanes;
-constexpr int kFusedSpheres = 128;                // spheres whose contacts are taken together
+constexpr int kPairThreads = kFusedThreads - 64;  // of the search without cells
+constexpr int kPairsMax = kPairThreads;           // its spheres at most
+constexpr int kFusedSpheres = kFusedThreads;      // spheres whose contacts are taken together
 
 // The pile's status as another thread of the workgroup may have set it.
 __device__ __forceinline__ int status_of(const PileDev& P) {
@@ -107,22 +109,139 @@ __device__ void search_all(PileDev& P, SearchLds<kFusedLanes, kFusedThreads>& sh
   }
 }
 
+// The spheres of a pile searched without cells, and the contacts found.
+struct PairsLds {
+  SortedGeom x[kPairsMax];
+  int32_t agg[kPairsMax];
+  uint32_t fill[kPairsMax][2];
+  uint32_t buf[kPairsMax][kRunLds];
+};
+
+// The search of a small pile without gravity: every pair of its spheres once,
+// from LDS, by the waves but the last, which works out the pile's moments
+// meanwhile.  A sphere's threads test it against the spheres at every L-th
+// distance in the ring of ids, each half the ring; a contact goes to the ids of
+// both its spheres.  By cells (moments, cells, binning, scan, placing, search) the
+// search is a chain of barriers and dependent loads: 18.0 us of a step of 97
+// spheres and 36 us of 250, now 5.2 (the moments) and 20.7 (FP64 rate: 75 ns
+// for a wave's 64 tests).
+// Called by the whole workgroup with sh.x, sh.agg and cleared sh.fill in place.
+__device__ __forceinline__ void search_pairs(PileDev& P, PairsLds& sh, unsigned long long* total,
+                             const double cref[3]) {
+  const int ns = P.ns, tid = threadIdx.x, nxt = P.parity ^ 1;
+  const int periodic = P.periodic;
+  const double box = P.box;
+  if (tid >= kPairThreads) {
+    const int lane = tid - kPairThreads;
+    double acc[kBbox];
+    bbox_identity(acc);
+    for (int i = lane; i < ns; i += 64) {
+      const SortedGeom g = sh.x[i];
+      double one[kBbox];
+      moments_one(P, i, g.x, g.y, g.z, cref, one);
+      bbox_combine(acc, one);
+    }
+    bbox_wave(acc);
+    grid_from_vals(P, acc, lane, kCellsNow);
+  }
+  int lg = 0;                                     // 2^lg threads of one wave per sphere
+  while (lg < 6 && (ns << (lg + 1)) <= kPairThreads) ++lg;
+  const int L = 1 << lg, i = tid >> lg, lane = tid & (L - 1);
+  const bool active = tid < kPairThreads && i < ns;
+  SortedGeom me{};
+  int ai = 0;
+  // the contact test without branches, so that tests overlap: the number of boxes
+  // to shift by (-1, 0, 1; every wave has pairs across a face) times the box is
+  // exact, so the shifted distance is rounded once, as in touching
+  const double far = periodic ? 0.5 * box : INFINITY, shift = periodic ? box : 0.0;
+  auto image = [&](double d) { return fma((double)((int)(d < -far) - (int)(d > far)), shift, d); };
+  auto meets = [&](int j) {
+    const SortedGeom o = sh.x[j];
+    return (sh.agg[j] != ai) & touching(image(o.x - me.x), image(o.y - me.y), image(o.z - me.z),
+                                        me.s + o.s, 0, 0.0);
+  };
+  auto enter_up = [&](int a, int b) {
+    const uint32_t pos = atomicAdd(&sh.fill[a][0], 1u);
+    if (pos < (uint32_t)kRunLds) sh.buf[a][pos] = (uint32_t)b;
+  };
+  auto enter = [&](int j) {
+    const int a = min(i, j), b = max(i, j);
+    enter_up(a, b);
+    const uint32_t pos = atomicAdd(&sh.fill[b][1], 1u);
+    if (pos < (uint32_t)kRunLds) sh.buf[b][kRunLds - 1 - pos] = (uint32_t)a;
+  };
+  if (active) {
+    me = sh.x[i];
+    ai = sh.agg[i];
+    const int half = (ns - 1) / 2;
+    for (int d0 = 1 + lane; d0 <= half; d0 += 8 * L) {
+      uint32_t met = 0;
+      auto other = [&](int u) {
+        const int j = i + min(d0 + u * L, half);
+        return j < ns ? j : j - ns;
+      };
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        met |= (uint32_t)(meets(other(u)) & (d0 + u * L <= half)) << u;
+      for (; met != 0; met &= met - 1) enter(other(__builtin_ctz(met)));
+    }
+    // an even ring's opposite sphere, from the first half alone
+    if ((ns & 1) == 0 && lane == 0 && i < ns / 2 && meets(i + ns / 2)) enter(i + ns / 2);
+    for (int w = lane; w < P.n_walls; w += L)
+      if (wall_gap(P, w, P.grid->wall_d[w], me.x, me.y, me.z) < me.s) enter_up(i, ns + w);
+  }
+  __syncthreads();
+  if (!active) return;
+  const uint32_t nup = sh.fill[i][0], nlo = sh.fill[i][1];
+  unsigned long long at = 0;
+  if (lane == 0) at = atomicAdd(total, ((unsigned long long)nup << 32) | (unsigned long long)nlo);
+  at = __shfl(at, (tid & 63) - lane);
+  const uint32_t u0 = (uint32_t)(at >> 32), l0 = (uint32_t)at;
+  const unsigned long long cap = (unsigned long long)P.cap_pairs;
+  if ((unsigned long long)u0 + nup > cap || (unsigned long long)l0 + nlo > cap) {
+    if (lane == 0) atomicOr(&P.status, kStCapacity);
+    return;
+  }
+  uint32_t* up_out = P.pair_j[nxt] + u0;
+  uint32_t* lo_out = P.lo_nbr + l0;
+  if (lane == 0) {
+    P.up_run[nxt][i] = make_uint2(u0, nup);
+    P.lo_run[i] = make_uint2(l0, nlo);
+  }
+  if (nup + nlo > (uint32_t)kRunLds) {
+    // more contacts than the LDS keeps: once more, in order
+    if (lane != 0) return;
+    for (int j = 0; j < ns; ++j)
+      if (meets(j)) *(j < i ? lo_out++ : up_out++) = (uint32_t)j;
+    for (int w = 0; w < P.n_walls; ++w)
+      if (wall_gap(P, w, P.grid->wall_d[w], me.x, me.y, me.z) < me.s) *up_out++ = (uint32_t)(ns + w);
+    return;
+  }
+  put_run<1>(sh.buf[i], nup, lane, L, up_out);
+  put_run<1>(sh.buf[i] + (kRunLds - nlo), nlo, lane, L, lo_out);
+}
+
 template <typename T>
 __global__ __launch_bounds__(kFusedThreads) void k_fused(PileDev* __restrict__ piles,
                                                          const int32_t* __restrict__ plist,
                                                          ContactParams cp, int mode, int part,
                                                          int steps) {
-  __shared__ SearchLds<kFusedLanes, kFusedThreads> search_sh;
-  __shared__ uint32_t big_up[kBigRun];
-  __shared__ uint32_t big_lo[kBigRun];
-  __shared__ uint32_t big_fill[4];
+  // the search and the forces take turns in this one
+  __shared__ union {
+    PairsLds pairs;
+    struct {
+      SearchLds<kFusedLanes, kFusedThreads> lanes;
+      uint32_t big_up[kBigRun], big_lo[kBigRun], big_fill[4];
+    } cells;
+    ForceLds<kFusedThreads, kFusedSpheres> force;
+  } sh;
   __shared__ unsigned long long run_total;
   __shared__ double red[kFusedWaves][kBbox];
   __shared__ uint32_t scan_sh[kFusedWaves + 1];
-  __shared__ ForceLds<kFusedThreads, kFusedSpheres> force_sh;
   __shared__ MoveLds<kFusedThreads> move_sh;
   PileDev& P = piles[plist[blockIdx.x]];
   const int tid = threadIdx.x;
+  const bool pairs = P.rows != 0 && P.ns <= kPairsMax;
   for (int step = 0; step < steps; ++step) {
     bool ok = status_of(P) == 0;            // a failed pile stays frozen
     if (part & 1) {
@@ -132,32 +251,40 @@ __global__ __launch_bounds__(kFusedThreads) void k_fused(PileDev* __restrict__ p
         double acc[kBbox], cref[3];
         bbox_identity(acc);
         bbox_ref(P, cref);
+        if (tid == 0) run_total = 0ull;
+        if ((tid >> 6) == kFusedWaves - 1) walls_at(P, tid & 63, mode, cp.dt);
         for (int base = 0; base < P.ns; base += kFusedThreads) {
           double one[kBbox];
           bbox_identity(one);
           move_block<kFusedThreads>(P, base, cp, mode, move_sh, cref, one);
+          if (pairs && tid < P.ns) {
+            sh.pairs.x[tid] = SortedGeom{one[0], one[1], one[2], P.s[tid]};
+            sh.pairs.agg[tid] = P.agg[tid];
+            sh.pairs.fill[tid][0] = sh.pairs.fill[tid][1] = 0u;
+          }
           bbox_combine(acc, one);
           if (base + kFusedThreads < P.ns) stage_sync();      // move_sh is written again
         }
-        for (int off = 32; off > 0; off >>= 1) {
-          double o[kBbox];
-          for (int k = 0; k < kBbox; ++k) o[k] = __shfl_xor(acc[k], off);
-          bbox_combine(acc, o);
+        if (pairs) {
+          stage_sync();
+          search_pairs(P, sh.pairs, &run_total, cref);
+          stage_sync();
+          if (tid == 0) *P.runs = run_total;
+        } else {
+          bbox_wave(acc);
+          if ((tid & 63) == 0)
+            for (int k = 0; k < kBbox; ++k) red[tid >> 6][k] = acc[k];
+          stage_sync();
+          if (tid < 64) {
+            for (int w = 1; w < kFusedWaves; ++w) bbox_combine(acc, red[w]);
+            grid_from_vals(P, acc, tid, kCellsNow);
+          }
+          stage_sync();
         }
-        if ((tid & 63) == 0)
-          for (int k = 0; k < kBbox; ++k) red[tid >> 6][k] = acc[k];
-        stage_sync();
-        if (tid < 64) {
-          for (int w = 1; w < kFusedWaves; ++w) bbox_combine(acc, red[w]);
-          grid_from_vals(P, acc, tid, kCellsNow);
-        }
-        if ((tid >> 6) == 1) walls_at(P, tid & 63, mode, cp.dt);
-        stage_sync();
         ok = status_of(P) == 0;
       }
-      if (ok) {
+      if (ok && !pairs) {
         // counting sort of the cell keys
-        if (tid == 0) run_total = 0ull;
         for (int i = tid; i < P.ns; i += kFusedThreads) bin_one(P, i);
         stage_sync();
         block_scan(P.cell_cnt, P.cell_start, (1 << (3 * P.bits)) + 1, scan_sh);
@@ -171,7 +298,8 @@ __global__ __launch_bounds__(kFusedThreads) void k_fused(PileDev* __restrict__ p
         }
         stage_sync();
         // contact search (the counter was cleared before the last barriers)
-        search_all(P, search_sh, &run_total, big_up, big_lo, big_fill);
+        search_all(P, sh.cells.lanes, &run_total, sh.cells.big_up, sh.cells.big_lo,
+                   sh.cells.big_fill);
         ok = status_of(P) == 0;
       }
       if (ok) {
@@ -179,7 +307,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_fused(PileDev* __restrict__ p
         const PairCtx<T> c = pair_ctx<T>(P, cp);
         bool bad = false;
         for (int i = 0; i < P.ns; i += kFusedSpheres)
-          forces_group<T, kFusedThreads, kFusedSpheres>(P, c, cp, i, force_sh, bad);
+          forces_group<T, kFusedThreads, kFusedSpheres>(P, c, cp, i, sh.force, bad);
         if (bad) atomicOr(&P.status, kStUnstable);
         stage_sync();
         ok = status_of(P) == 0;

@@ -173,6 +173,31 @@ __device__ __forceinline__ void given_one(const PileDev& P, int i, double vals[k
   vals[10] = 0.0;
 }
 
+// Combine the partials of a wave's lanes, in every lane.
+__device__ __forceinline__ void bbox_wave(double a[kBbox]) {
+  for (int off = 32; off > 0; off >>= 1) {
+    double o[kBbox];
+    for (int k = 0; k < kBbox; ++k) o[k] = __shfl_xor(a[k], off);
+    bbox_combine(a, o);
+  }
+}
+
+// Bounding-box and mass-moment contributions of sphere i at (x, y, z), second
+// moment about cref.
+__device__ __forceinline__ void moments_one(const PileDev& P, int i, double x, double y, double z,
+                                            const double cref[3], double vals[kBbox]) {
+  const double r[3] = {x, y, z}, mi = P.m[i];
+  double d2 = 0.0;
+  for (int k = 0; k < 3; ++k) {
+    vals[k] = r[k];
+    vals[3 + k] = r[k];
+    vals[7 + k] = mi * r[k];
+    d2 += (r[k] - cref[k]) * (r[k] - cref[k]);
+  }
+  vals[6] = mi;
+  vals[10] = mi * d2;
+}
+
 // Member reconstruction of sphere i of the aggregate in state (rA, q, wa, vp)
 // (SetSpacePos / SetSpaceVel, Eq. 3): r_i = r_A + R b_i, v_i = vpred_A + w_A x
 // (R b_i).  Its bounding-box and mass-moment contributions (second moment
@@ -186,19 +211,13 @@ __device__ __forceinline__ void reconstruct_one(const PileDev& P, int i, const M
   double d[3], wxd[3];
   rot_apply(R, bb, d);
   cross3(m.w, d, wxd);
-  const double mi = P.m[i];
-  double d2 = 0.0;
+  double r[3];
   for (int k = 0; k < 3; ++k) {
-    const double x = m.r[k] + d[k];
-    P.r[k * ns + i] = x;
+    r[k] = m.r[k] + d[k];
+    P.r[k * ns + i] = r[k];
     P.v[k * ns + i] = m.vpred[k] + wxd[k];
-    vals[k] = x;
-    vals[3 + k] = x;
-    vals[7 + k] = mi * x;
-    d2 += (x - cref[k]) * (x - cref[k]);
   }
-  vals[6] = mi;
-  vals[10] = mi * d2;
+  moments_one(P, i, r[0], r[1], r[2], cref, vals);
 }
 
 // The new states of the aggregates of one block's NT spheres, in LDS.
@@ -411,11 +430,7 @@ __device__ __forceinline__ void grid_block(PileDev& P, int mode, double dt, int 
     const double* p = P.bpart + (size_t)b * kBbox;
     bbox_combine(vals, p);
   }
-  for (int off = 32; off > 0; off >>= 1) {
-    double o[kBbox];
-    for (int k = 0; k < kBbox; ++k) o[k] = __shfl_xor(vals[k], off);
-    bbox_combine(vals, o);
-  }
+  bbox_wave(vals);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   if (lane == 0)
     for (int k = 0; k < kBbox; ++k) sh.red[wave][k] = vals[k];

@@ -296,9 +296,20 @@ __device__ __forceinline__ void store_long_runs(const PileDev& P, int k, uint32_
   sort_run(lo_out, nlo);
 }
 
-// Stores the runs found by find_slot at u0 (upper) and l0 (lower), each sorted:
-// ids in a run are distinct, so an entry's rank is the number of smaller
-// entries.
+// Writes the n ids b[0], b[St], .. to out, sorted: ids in a run are distinct, so
+// an entry's rank is the number of smaller entries.  Lane of a group of lanes.
+template <int St>
+__device__ __forceinline__ void put_run(const uint32_t* b, uint32_t n, int lane, int lanes,
+                                        uint32_t* out) {
+  for (uint32_t e = lane; e < n; e += lanes) {
+    const uint32_t v = b[e * St];
+    uint32_t r = 0;
+    for (uint32_t f = 0; f < n; ++f) r += b[f * St] < v;
+    out[r] = v;
+  }
+}
+
+// Stores the runs found by find_slot at u0 (upper) and l0 (lower), each sorted.
 template <int Lanes, int NT>
 __device__ __forceinline__ void store_runs(const PileDev& P, int k, uint32_t i, int grp, int lane,
                                            SearchLds<Lanes, NT>& sh, uint32_t nup, uint32_t nlo,
@@ -314,17 +325,9 @@ __device__ __forceinline__ void store_runs(const PileDev& P, int k, uint32_t i, 
     if (lane == 0) store_long_runs(P, k, i, nup, nlo, u0, l0);
     return;
   }
-  auto put = [&](const uint32_t* b, uint32_t n, uint32_t* out) {
-    for (uint32_t e = lane; e < n; e += Lanes) {
-      const uint32_t v = b[e * st];
-      uint32_t r = 0;
-      for (uint32_t f = 0; f < n; ++f) r += b[f * st] < v;
-      out[r] = v;
-    }
-  };
   const uint32_t* buf = sh.ids(grp);
-  put(buf, nup, P.pair_j[nxt] + u0);
-  put(buf + (kRunLds - nlo) * st, nlo, P.lo_nbr + l0);
+  put_run<st>(buf, nup, lane, Lanes, P.pair_j[nxt] + u0);
+  put_run<st>(buf + (kRunLds - nlo) * st, nlo, lane, Lanes, P.lo_nbr + l0);
 }
 
 // Room for nup upper and nlo lower contacts in the pile's lists: the first

@@ -309,7 +309,7 @@ __device__ __forceinline__ void wall_contact(const PileDev& P, const PairCtx<T>&
 // force and torque of one round of contacts on the sphere they belong to.
 template <int NT, int S>
 struct ForceLds {
-  uint32_t start[S + 1], lo0[S], up0[S], nlo[S];
+  uint32_t start[S + 1], lo0[S], up0[S], nlo[S], wave[S / 64];
   double res[6][NT];
 };
 
@@ -338,37 +338,45 @@ template <typename T, int NT, int S>
 __device__ __forceinline__ void forces_group(const PileDev& P, const PairCtx<T>& c,
                                              const ContactParams& cp, int base,
                                              ForceLds<NT, S>& sh, bool& bad) {
-  static_assert(S % 64 == 0 && 3 * S <= NT, "one thread per sphere and axis");
+  static_assert(S % 64 == 0 && (S & (S - 1)) == 0 && S <= NT, "a wave per 64 spheres, a search by halves");
+  constexpr int K = (3 * S + NT - 1) / NT;   // sums (sphere, axis) of a thread
   const int ns = c.ns, na = c.na, tid = threadIdx.x;
   const int n = min(S, ns - base);
-  if (tid < 64) {
-    // numbers of contacts, and their prefix sum (one wave)
-    uint32_t before = 0;
-    for (int q = 0; q < S; q += 64) {
-      const int l = q + tid, i = base + l;
-      uint32_t nc = 0;
-      if (l < n) {
-        const uint2 lo = P.lo_run[i], up = c.up_run[i];
-        sh.lo0[l] = lo.x;
-        sh.up0[l] = up.x;
-        sh.nlo[l] = lo.y;
-        nc = lo.y + up.y;
-      }
-      uint32_t x = nc;
-      for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t y = __shfl_up(x, off);
-        if (tid >= off) x += y;
-      }
-      sh.start[l] = before + x - nc;
-      before += __shfl(x, 63);
+  if (tid < S) {
+    // numbers of contacts, and their prefix sum
+    const int i = base + tid;
+    uint32_t nc = 0;
+    if (tid < n) {
+      const uint2 lo = P.lo_run[i], up = c.up_run[i];
+      sh.lo0[tid] = lo.x;
+      sh.up0[tid] = up.x;
+      sh.nlo[tid] = lo.y;
+      nc = lo.y + up.y;
     }
-    if (tid == 0) sh.start[S] = before;
+    uint32_t x = nc;
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t y = __shfl_up(x, off);
+      if ((tid & 63) >= off) x += y;
+    }
+    sh.start[tid] = x - nc;
+    if ((tid & 63) == 63) sh.wave[tid >> 6] = x;
   }
   __syncthreads();
-  const uint32_t total = sh.start[S];
-  // this thread's sphere and axis in the ordered sums
-  const int ls = tid % S, ax = tid / S;
-  double f = 0.0, t = 0.0;
+  uint32_t total = 0;
+  if constexpr (S == 64) {
+    total = sh.wave[0];
+    if (tid == 0) sh.start[S] = total;
+  } else {
+    uint32_t before = 0;
+    for (int w = 0; w < S / 64; ++w) {
+      if (w < tid >> 6) before += sh.wave[w];
+      total += sh.wave[w];
+    }
+    if (tid < S) sh.start[tid] += before;
+    if (tid == 0) sh.start[S] = total;
+    __syncthreads();
+  }
+  double f[K] = {}, t[K] = {};
   for (uint32_t r0 = 0; r0 < total; r0 += NT) {
     const uint32_t e = r0 + (uint32_t)tid;
     if (e < total) {
@@ -410,18 +418,25 @@ __device__ __forceinline__ void forces_group(const PileDev& P, const PairCtx<T>&
       sh.res[5][tid] = lower ? (double)r.Tb.z : (double)r.Ta.z;
     }
     __syncthreads();
-    if (ax < 3) {
+#pragma unroll
+    for (int u = 0; u < K; ++u) {
+      const int ls = (tid + u * NT) % S, ax = (tid + u * NT) / S;
+      if (ax >= 3) continue;
       const uint32_t e0 = max(sh.start[ls], r0), e1 = min(sh.start[ls + 1], r0 + (uint32_t)NT);
       for (uint32_t q = e0; q < e1; ++q) {
-        f += sh.res[ax][q - r0];
-        t += sh.res[3 + ax][q - r0];
+        f[u] += sh.res[ax][q - r0];
+        t[u] += sh.res[3 + ax][q - r0];
       }
     }
     __syncthreads();
   }
-  if (ax < 3 && ls < n) {
-    P.F[ax * ns + base + ls] = f;
-    P.tau[ax * ns + base + ls] = t;
+#pragma unroll
+  for (int u = 0; u < K; ++u) {
+    const int ls = (tid + u * NT) % S, ax = (tid + u * NT) / S;
+    if (ax < 3 && ls < n) {
+      P.F[ax * ns + base + ls] = f[u];
+      P.tau[ax * ns + base + ls] = t[u];
+    }
   }
   __syncthreads();                       // sh is free for the next group
 }
