@@ -329,6 +329,26 @@ void launch_tree(hipStream_t st, const PileDev* piles, WorkItem* const* wl_level
                  const bool* any_order);
 void launch_fill_u32(hipStream_t st, uint32_t* p, uint32_t value, int64_t n);
 void launch_clear(hipStream_t st, const PileDev& h, int64_t cells);
+// Fields of a state read-out: component-major src [comps][n] to row-major dst
+// [n][comps].  add: a second array added to src; spin: src is the orientation,
+// add the body-frame spin, and dst gets the space-frame spin.
+struct ReadField {
+  const double* src;
+  const double* add;
+  double* dst;
+  int64_t n;
+  int32_t comps, spin, block0;
+};
+constexpr int kReadFields = 14;
+struct ReadList {
+  ReadField f[kReadFields];
+  int n;
+};
+void launch_read(hipStream_t st, ReadList& list);
+// The n contacts of a pile in canonical order: keys (i << 32) | j and the
+// history [n][kHist], through offset [ns].
+void launch_read_pairs(hipStream_t st, const PileDev& h, uint32_t* offset, uint64_t* keys,
+                       double* hist);
 // The whole step of each listed pile in one workgroup: part 1 the stages
 // before gravity, part 2 those after it, part 3 all (no gravity); that many steps.
 void launch_fused(hipStream_t st, const PileDev* piles, const int32_t* plist, int n,

@@ -350,6 +350,77 @@ __global__ void k_fill_u32(uint32_t* __restrict__ p, uint32_t value, int64_t n) 
   if (i < n) p[i] = value;
 }
 
+// A state read-out: one thread per row of a field.
+__global__ __launch_bounds__(kBlock) void k_read(ReadList list) {
+  int q = 0;
+  while (q + 1 < list.n && (int)blockIdx.x >= list.f[q + 1].block0) ++q;
+  const ReadField f = list.f[q];
+  const int64_t n = f.n, i = (int64_t)((int)blockIdx.x - f.block0) * kBlock + threadIdx.x;
+  if (i >= n) return;
+  double* out = f.dst + i * f.comps;
+  if (f.spin) {
+    // R(q) w_b, every product and sum rounded
+    const double w = f.src[i], x = f.src[n + i], y = f.src[2 * n + i], z = f.src[3 * n + i];
+    auto two = [](double a) { return rn_mul(2.0, a); };
+    auto mul = [](double a, double b) { return rn_mul(a, b); };
+    auto add = [](double a, double b) { return rn_add(a, b); };
+    const double R[9] = {add(1.0, -two(add(mul(y, y), mul(z, z)))),
+                         two(add(mul(x, y), -mul(w, z))), two(add(mul(x, z), mul(w, y))),
+                         two(add(mul(x, y), mul(w, z))), add(1.0, -two(add(mul(x, x), mul(z, z)))),
+                         two(add(mul(y, z), -mul(w, x))), two(add(mul(x, z), -mul(w, y))),
+                         two(add(mul(y, z), mul(w, x))), add(1.0, -two(add(mul(x, x), mul(y, y))))};
+    const double o[3] = {f.add[i], f.add[n + i], f.add[2 * n + i]};
+    for (int c = 0; c < 3; ++c)
+      out[c] = add(add(mul(R[3 * c], o[0]), mul(R[3 * c + 1], o[1])), mul(R[3 * c + 2], o[2]));
+    return;
+  }
+  for (int c = 0; c < f.comps; ++c) {
+    const double v = f.src[c * n + i];
+    out[c] = f.add ? v + f.add[c * n + i] : v;
+  }
+}
+
+// First canonical contact of every sphere: the prefix sum of the lengths of the
+// upper runs, by one block (each thread a contiguous share).
+constexpr int kOffsetThreads = 1024;
+__global__ __launch_bounds__(kOffsetThreads) void k_read_offsets(const uint2* __restrict__ run,
+                                                                 int ns,
+                                                                 uint32_t* __restrict__ offset) {
+  __shared__ uint32_t wsum[kOffsetThreads / 64];
+  const int tid = threadIdx.x, per = (ns + kOffsetThreads - 1) / kOffsetThreads;
+  const int b0 = min(ns, tid * per), b1 = min(ns, b0 + per);
+  uint32_t sum = 0;
+  for (int i = b0; i < b1; ++i) sum += run[i].y;
+  uint32_t x = sum;
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t y = __shfl_up(x, off);
+    if ((tid & 63) >= off) x += y;
+  }
+  if ((tid & 63) == 63) wsum[tid >> 6] = x;
+  __syncthreads();
+  uint32_t at = x - sum;
+  for (int w = 0; w < tid >> 6; ++w) at += wsum[w];
+  for (int i = b0; i < b1; ++i) {
+    offset[i] = at;
+    at += run[i].y;
+  }
+}
+
+__global__ __launch_bounds__(kBlock) void k_read_pairs(PileDev P, const uint32_t* __restrict__ offset,
+                                                       uint64_t* __restrict__ keys,
+                                                       double* __restrict__ hist) {
+  const int i = blockIdx.x * kBlock + threadIdx.x;
+  if (i >= P.ns) return;
+  const uint2 run = P.up_run[P.parity][i];
+  const uint32_t* __restrict__ pj = P.pair_j[P.parity] + run.x;
+  const double* __restrict__ rows = P.hist[P.parity] + (size_t)run.x * kHistRow;
+  uint32_t p = offset[i];
+  for (uint32_t e = 0; e < run.y; ++e, ++p) {
+    keys[p] = ((uint64_t)i << 32) | pj[e];
+    for (int c = 0; c < kHist; ++c) hist[(size_t)p * kHist + c] = rows[(size_t)e * kHistRow + c];
+  }
+}
+
 // No contacts and no counts: empty runs of every sphere, zero cell counts.
 __global__ void k_clear(PileDev P, int64_t cells) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -392,6 +463,21 @@ void launch_fill_u32(hipStream_t st, uint32_t* p, uint32_t value, int64_t n) {
   if (n <= 0) return;
   hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, st,
                      p, value, n);
+}
+void launch_read(hipStream_t st, ReadList& list) {
+  int blk = 0;
+  for (int q = 0; q < list.n; ++q) {
+    list.f[q].block0 = blk;
+    blk += (int)((list.f[q].n + kBlock - 1) / kBlock);
+  }
+  if (blk > 0) hipLaunchKernelGGL(k_read, dim3(blk), dim3(kBlock), 0, st, list);
+}
+void launch_read_pairs(hipStream_t st, const PileDev& h, uint32_t* offset, uint64_t* keys,
+                       double* hist) {
+  hipLaunchKernelGGL(k_read_offsets, dim3(1), dim3(kOffsetThreads), 0, st, h.up_run[h.parity], h.ns,
+                     offset);
+  hipLaunchKernelGGL(k_read_pairs, dim3((h.ns + kBlock - 1) / kBlock), dim3(kBlock), 0, st, h,
+                     offset, keys, hist);
 }
 void launch_clear(hipStream_t st, const PileDev& h, int64_t cells) {
   const int64_t n = std::max<int64_t>(std::max<int64_t>(h.ns, cells), 16);

@@ -315,8 +315,8 @@ class Sim:
             st.pair_hist = _p(hist)
         _check(lib().dem_read_state(self.h, C.byref(st)), self.h)
         if pairs:
-            out["pair_keys"] = keys[:st.n_pairs].copy()
-            out["pair_hist"] = hist[:st.n_pairs].copy()
+            out["pair_keys"] = keys[:st.n_pairs]
+            out["pair_hist"] = hist[:st.n_pairs]
         out["n_pairs"] = int(st.n_pairs)
         out["step"] = int(st.step)
         return out
