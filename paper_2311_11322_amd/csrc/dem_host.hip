@@ -67,15 +67,6 @@ struct Sizes {
   int precision;
 };
 
-// Cells per axis of a periodic cube of side L: as many as fit with a side of
-// at least cell_min (with a relative margin against rounding), at least one,
-// and no more than the Morton table holds.
-int periodic_cells(double L, double cell_min, int bits) {
-  const double ratio = L / (cell_min * (1.0 + 1e-12));
-  int n = ratio >= 1.0 ? (int)std::min(std::floor(ratio), 1e9) : 1;
-  return std::max(1, std::min(n, 1 << bits));
-}
-
 // Spheres much larger than the rest -- above twice the median radius, if
 // there are at most kMaxBig of them -- are searched separately, so that the
 // cells can be sized for the others (a boulder among grains).
@@ -1060,51 +1051,6 @@ static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
 
 namespace {
 
-// First bytes of the scratch: the largest radius (bit pattern of a positive
-// double, ordered like an unsigned integer) and a flag for invalid input.
-struct NoAllocHdr {
-  unsigned long long max_r_bits;
-  uint32_t bad;
-  uint32_t pad;
-};
-
-// One thread per sphere: row-major device positions into the search's
-// component-major array; radius and position checks; largest radius.
-__global__ __launch_bounds__(kBlock) void k_noalloc_ingest(const double* __restrict__ pos,
-                                                           const double* __restrict__ rad, int n,
-                                                           double* __restrict__ r,
-                                                           NoAllocHdr* __restrict__ hdr) {
-  const int i = blockIdx.x * kBlock + threadIdx.x;
-  double smax = 0.0;
-  bool bad = false;
-  if (i < n) {
-    const double x = pos[3 * i], y = pos[3 * i + 1], z = pos[3 * i + 2], s = rad[i];
-    r[i] = x;
-    r[n + i] = y;
-    r[2 * n + i] = z;
-    bad = !(isfinite(x) && isfinite(y) && isfinite(z) && isfinite(s) && s > 0.0);
-    smax = bad ? 0.0 : s;
-  }
-  for (int off = 32; off > 0; off >>= 1) smax = fmax(smax, __shfl_xor(smax, off));
-  const bool any_bad = __any(bad);
-  if ((threadIdx.x & 63) == 0) {
-    if (any_bad) atomicOr(&hdr->bad, 1u);
-    if (smax > 0.0) atomicMax(&hdr->max_r_bits, (unsigned long long)__double_as_longlong(smax));
-  }
-}
-
-// One thread per sphere: its upper run as canonical keys, up to cap in all.
-__global__ __launch_bounds__(kBlock) void k_noalloc_keys(const uint32_t* __restrict__ off,
-                                                         const uint2* __restrict__ run,
-                                                         const uint32_t* __restrict__ pj, int n,
-                                                         uint64_t* __restrict__ out, int64_t cap) {
-  const int i = blockIdx.x * kBlock + threadIdx.x;
-  if (i >= n) return;
-  const uint2 r = run[i];
-  for (int64_t e = 0, p = off[i]; e < r.y && p < cap; ++e, ++p)
-    out[p] = (uint64_t(i) << 32) | pj[r.x + e];
-}
-
 std::mutex g_scratch_mutex;
 void* g_scratch_ptr[kMaxDevices] = {};
 
@@ -1135,44 +1081,27 @@ struct Placer {
   }
 };
 
-// Places the header, the table entry, the work lists and every buffer the
-// search kernels touch for n spheres; returns the bytes used.
-struct NoAllocPlan {
-  NoAllocHdr* hdr;
-  PileDev* entry;
-  WorkItem* wl;
-  ScanSeg* seg_cells;
-  ScanItem* item_cells;
-  uint32_t* sums_cells;
-  ScanSeg* seg_pairs;
-  ScanItem* item_pairs;
-  uint32_t* sums_pairs;
-  uint32_t* key_off;                 // [n + 1] first key of each sphere's contacts
-  int n_blk, n_item_cells, n_item_pairs, max_items_cells, max_items_pairs;
-  int64_t cells;
-  size_t bytes;
-};
-
+// Places the table entry, the work lists and every buffer the search kernels
+// touch for n spheres; returns the bytes used.
 int64_t scan_items(int64_t n) { return (n + kScanChunk - 1) / kScanChunk; }
 
-NoAllocPlan plan_noalloc(char* base, int64_t n, PileDev& h) {
+size_t plan_noalloc(char* base, int64_t n, PileDev& h, NoAllocLists& q) {
   Placer L{base};
-  NoAllocPlan q{};
-  q.cells = int64_t(1) << (3 * choose_bits(n));
+  const int64_t cells = int64_t(1) << (3 * choose_bits(n));
   q.n_blk = (int)((n + kBlock - 1) / kBlock);
-  q.n_item_cells = (int)scan_items(q.cells + 1);
-  q.max_items_cells = q.n_item_cells;
-  q.max_items_pairs = (int)scan_items(n);
-  q.n_item_pairs = q.max_items_pairs;
-  q.hdr = L.take<NoAllocHdr>(1);
+  q.cells.n = (int32_t)(cells + 1);
+  q.cells.n_items = (int32_t)scan_items(cells + 1);
+  q.keys.n = (int32_t)n;
+  q.keys.n_items = (int32_t)scan_items(n);
+  q.out = L.take<NoAllocOut>(1);
   q.entry = L.take<PileDev>(1);
   q.wl = L.take<WorkItem>(q.n_blk);
   q.seg_cells = L.take<ScanSeg>(1);
-  q.item_cells = L.take<ScanItem>(q.n_item_cells);
-  q.sums_cells = L.take<uint32_t>(q.n_item_cells);
-  q.seg_pairs = L.take<ScanSeg>(1);
-  q.item_pairs = L.take<ScanItem>(q.n_item_pairs);
-  q.sums_pairs = L.take<uint32_t>(q.n_item_pairs);
+  q.item_cells = L.take<ScanItem>(q.cells.n_items);
+  q.sums_cells = L.take<uint32_t>(q.cells.n_items);
+  q.seg_keys = L.take<ScanSeg>(1);
+  q.item_keys = L.take<ScanItem>(q.keys.n_items);
+  q.sums_keys = L.take<uint32_t>(q.keys.n_items);
   h.r = L.take<double>(3 * n);
   h.key = L.take<uint32_t>(n);
   h.num = L.take<uint32_t>(n);
@@ -1180,17 +1109,16 @@ NoAllocPlan plan_noalloc(char* base, int64_t n, PileDev& h) {
   h.sid = L.take<SortedId>(n);
   h.bpart = L.take<double>(kBbox * q.n_blk);
   h.grid = L.take<Grid>(1);
-  h.cell_cnt = L.take<uint32_t>(q.cells + 1);
-  h.cell_start = L.take<uint32_t>(q.cells + 2);
-  h.cnt_up = L.take<uint32_t>(n);
-  q.key_off = L.take<uint32_t>(n + 1);
+  h.cell_cnt = q.cells.in = L.take<uint32_t>(cells + 1);
+  h.cell_start = q.cells.out = L.take<uint32_t>(cells + 2);
+  h.cnt_up = q.keys.in = L.take<uint32_t>(n);
+  q.keys.out = L.take<uint32_t>(n + 1);
   h.runs = L.take<unsigned long long>(16);
   h.up_run[0] = h.up_run[1] = L.take<uint2>(n);
   h.lo_run = L.take<uint2>(n);
   h.pair_j[0] = h.pair_j[1] = L.take<uint32_t>(kNoAllocMaxPairs);
   h.lo_nbr = L.take<uint32_t>(kNoAllocMaxPairs);
-  q.bytes = L.off;
-  return q;
+  return L.off;
 }
 
 }  // namespace
@@ -1886,19 +1814,9 @@ dem_status dem_find_contacts_noalloc(const double* pos, const double* radius,
   void* base = nullptr;
   HIPCHK(nullptr, noalloc_scratch(dev, &base));
   PileDev h{};
-  const NoAllocPlan q = plan_noalloc(static_cast<char*>(base), n, h);
-  if (q.bytes > kNoAllocScratchBytes)
+  NoAllocLists q{};
+  if (plan_noalloc(static_cast<char*>(base), n, h, q) > kNoAllocScratchBytes)
     return fail(nullptr, DEM_ERR_INVALID_ARG, "search does not fit the static scratch");
-  // positions in, radius checks and the largest radius out
-  launch_fill_u32(st, reinterpret_cast<uint32_t*>(q.hdr), 0u, sizeof(NoAllocHdr) / 4);
-  hipLaunchKernelGGL(k_noalloc_ingest, dim3(q.n_blk), dim3(kBlock), 0, st, pos, radius, (int)n,
-                     h.r, q.hdr);
-  NoAllocHdr hdr{};
-  HIPCHK(nullptr, hipMemcpyAsync(&hdr, q.hdr, sizeof hdr, hipMemcpyDeviceToHost, st));
-  HIPCHK(nullptr, hipStreamSynchronize(st));
-  if (hdr.bad) return fail(nullptr, DEM_ERR_INVALID_ARG, "bad radius or position");
-  double smax;
-  std::memcpy(&smax, &hdr.max_r_bits, sizeof smax);
   // the table entry of a pile of given positions (no aggregates, no gravity)
   h.na = 0;
   h.ns = (int32_t)n;
@@ -1908,70 +1826,20 @@ dem_status dem_find_contacts_noalloc(const double* pos, const double* radius,
   h.periodic = box ? 1 : 0;
   h.box = box ? box[0] : 0.0;
   h.n_rblk = q.n_blk;
-  h.cell_min = 2.0 * smax;
   h.s_cut = INFINITY;
-  h.s_small = smax;
-  h.n_big = 0;
   h.fail_step = -1;
   h.s = const_cast<double*>(radius);
   h.agg = const_cast<int32_t*>(agg);
-  if (box) h.n_periodic = periodic_cells(box[0], h.cell_min, h.bits);
-  // work lists and scan segments (fixed-size host staging)
-  WorkItem wl[kNoAllocMaxSpheres / kBlock];
-  for (int b = 0; b < q.n_blk; ++b) wl[b] = WorkItem{0, b * kBlock};
-  ScanSeg sc{};
-  sc.in = h.cell_cnt;
-  sc.out = h.cell_start;
-  sc.n = (int32_t)(q.cells + 1);
-  sc.n_items = q.n_item_cells;
-  ScanItem ic[(((int64_t(1) << 18) + 1) + kScanChunk - 1) / kScanChunk];
-  static_assert(sizeof(ic) / sizeof(ic[0]) >= (size_t)(((int64_t(1) << 18) + 1 + kScanChunk - 1) /
-                                                        kScanChunk), "cell scan items");
-  for (int c = 0; c < q.n_item_cells; ++c) ic[c] = ScanItem{0, c};
-  ScanSeg sp{};
-  ScanItem ip[(kNoAllocMaxSpheres + kScanChunk - 1) / kScanChunk];
-  sp.in = h.cnt_up;
-  sp.out = q.key_off;
-  sp.n = (int32_t)n;
-  sp.n_items = q.max_items_pairs;
-  for (int c = 0; c < q.max_items_pairs; ++c) ip[c] = ScanItem{0, c};
-  HIPCHK(nullptr, hipMemcpyAsync(q.entry, &h, sizeof h, hipMemcpyHostToDevice, st));
-  HIPCHK(nullptr, hipMemcpyAsync(q.wl, wl, q.n_blk * sizeof(WorkItem), hipMemcpyHostToDevice, st));
-  HIPCHK(nullptr, hipMemcpyAsync(q.seg_cells, &sc, sizeof sc, hipMemcpyHostToDevice, st));
-  HIPCHK(nullptr, hipMemcpyAsync(q.item_cells, ic, q.n_item_cells * sizeof(ScanItem),
-                                 hipMemcpyHostToDevice, st));
-  HIPCHK(nullptr, hipMemcpyAsync(q.seg_pairs, &sp, sizeof sp, hipMemcpyHostToDevice, st));
-  HIPCHK(nullptr, hipMemcpyAsync(q.item_pairs, ip, q.n_item_pairs * sizeof(ScanItem),
-                                 hipMemcpyHostToDevice, st));
-  // the cell counts start at zero (the scan returns them to zero)
-  launch_fill_u32(st, h.cell_cnt, 0u, q.cells + 1);
-  const PileDev* t = q.entry;
-  launch_move(st, t, q.wl, q.n_blk, ContactParams{}, kModeInit, false);
-  launch_grid(st, t, nullptr, 1, kModeInit, 1.0);
-  launch_bin(st, t, q.wl, q.n_blk);
-  launch_scan(st, q.seg_cells, 1, q.item_cells, q.n_item_cells, q.sums_cells, q.max_items_cells,
-              ScanGrids{});
-  launch_place(st, t, q.wl, q.n_blk);
-  launch_search(st, t, q.wl, q.n_blk);
+  launch_noalloc(st, h, q, pos, radius, pairs_out, cap);
   HIPCHK(nullptr, hipGetLastError());
-  int32_t status = 0;
-  unsigned long long runs = 0;
-  HIPCHK(nullptr, hipMemcpyAsync(&status, &q.entry->status, sizeof status, hipMemcpyDeviceToHost, st));
-  HIPCHK(nullptr, hipMemcpyAsync(&runs, h.runs, sizeof runs, hipMemcpyDeviceToHost, st));
+  NoAllocOut got{};
+  HIPCHK(nullptr, hipMemcpyAsync(&got, q.out, sizeof got, hipMemcpyDeviceToHost, st));
   HIPCHK(nullptr, hipStreamSynchronize(st));
-  const int64_t total = int64_t(runs >> 32);
-  *n_out = total;
-  if (status & kStCapacity)
+  if (got.bad) return fail(nullptr, DEM_ERR_INVALID_ARG, "bad radius or position");
+  *n_out = int64_t(got.runs >> 32);
+  if (got.status & kStCapacity)
     return fail(nullptr, DEM_ERR_CAPACITY, "more contacts than the static scratch holds");
-  if (status != 0) return fail(nullptr, DEM_ERR_INVALID_ARG, "non-finite positions");
-  if (cap > 0 && total > 0) {
-    launch_scan(st, q.seg_pairs, 1, q.item_pairs, q.n_item_pairs, q.sums_pairs, q.max_items_pairs,
-                ScanGrids{});
-    hipLaunchKernelGGL(k_noalloc_keys, dim3(q.n_blk), dim3(kBlock), 0, st, q.key_off, h.up_run[1],
-                       h.pair_j[1], (int)n, pairs_out, cap);
-    HIPCHK(nullptr, hipGetLastError());
-    HIPCHK(nullptr, hipStreamSynchronize(st));
-  }
+  if (got.status != 0) return fail(nullptr, DEM_ERR_INVALID_ARG, "non-finite positions");
   return DEM_OK;
 }
 

@@ -372,6 +372,38 @@ struct ScanGrids {
 void launch_scan(hipStream_t st, const ScanSeg* segs, int n_segs, const ScanItem* items,
                  int n_items, uint32_t* item_sums, int max_seg_items, ScanGrids grids);
 
+// What the search without allocation reports: the largest radius (bit pattern
+// of a positive double, ordered like an unsigned integer), a flag for invalid
+// input, the pile's status and its counter of contacts.
+struct NoAllocOut {
+  unsigned long long max_r_bits, runs;
+  uint32_t bad;
+  int32_t status;
+};
+// Its table entry, work list and scan segments (cell counts; contacts per
+// sphere), filled in on the device.
+struct NoAllocLists {
+  NoAllocOut* out;
+  PileDev* entry;
+  WorkItem* wl;
+  ScanSeg *seg_cells, *seg_keys;
+  ScanItem *item_cells, *item_keys;
+  uint32_t *sums_cells, *sums_keys;
+  ScanSeg cells, keys;
+  int n_blk;
+};
+void launch_noalloc(hipStream_t st, const PileDev& h, const NoAllocLists& q, const double* pos,
+                    const double* radius, uint64_t* keys, int64_t cap);
+
+// Cells per axis of a periodic cube of side L: as many as fit with a side of
+// at least cell_min (with a relative margin against rounding), at least one,
+// and no more than the key holds.
+__host__ __device__ inline int periodic_cells(double L, double cell_min, int bits) {
+  const double ratio = L / (cell_min * (1.0 + 1e-12));
+  const double n = ratio >= 1.0 ? fmin(floor(ratio), (double)(1 << bits)) : 1.0;
+  return (int)n;
+}
+
 // ---------------------------------------------------------------------------
 // small device helpers
 // ---------------------------------------------------------------------------

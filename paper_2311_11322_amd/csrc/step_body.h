@@ -160,15 +160,11 @@ __device__ __forceinline__ void bbox_ref(const PileDev& P, double cref[3]) {
   for (int k = 0; k < 3; ++k) cref[k] = (na > 0 && !P.given) ? P.rA[cur][k * na] : 0.0;
 }
 
-// Bounding-box contribution of sphere i of a pile whose positions are given
+// Bounding-box contribution of a sphere of a pile whose positions are given
 // (stateless hooks).
-__device__ __forceinline__ void given_one(const PileDev& P, int i, double vals[kBbox]) {
-  for (int k = 0; k < 3; ++k) {
-    const double x = P.r[k * P.ns + i];
-    vals[k] = x;
-    vals[3 + k] = x;
-    vals[7 + k] = x;
-  }
+__device__ __forceinline__ void given_vals(double x, double y, double z, double vals[kBbox]) {
+  const double r[3] = {x, y, z};
+  for (int k = 0; k < 3; ++k) vals[k] = vals[3 + k] = vals[7 + k] = r[k];
   vals[6] = 1.0;
   vals[10] = 0.0;
 }
@@ -238,7 +234,7 @@ __device__ __forceinline__ void move_block(PileDev& P, int base, const ContactPa
                                            double vals[kBbox]) {
   const int ns = P.ns, tid = threadIdx.x, i = base + tid;
   if (P.na == 0 || P.given) {
-    if (i < ns) given_one(P, i, vals);
+    if (i < ns) given_vals(P.r[i], P.r[ns + i], P.r[2 * ns + i], vals);
     return;
   }
   const int a0 = P.agg[base], a1 = P.agg[min(base + NT, ns) - 1];
