@@ -179,8 +179,9 @@ dem_status dem_add_aggregates(dem_sim* sim, int64_t n_agg, const int32_t* sphere
                               const double* sphere_mass, const double* agg_vel,
                               const double* agg_spin, int64_t* first_agg_id);
 
-/* Advance n_steps fixed steps (replays of one captured HIP graph; a small system
- * without gravity takes up to 64 steps in one launch).  Returns
+/* Advance n_steps fixed steps (with gravity replays of one captured HIP graph, one
+ * a step; without, many steps to a launch: a graph of 8, or 64 in one workgroup
+ * for a small system).  Returns
  * after the work is complete.  On CAPACITY / UNSTABLE (and on DEM_STOPPED,
  * the stop rule of dem_forcing) the state is that at the start of the
  * failing step and dem_state.step tells which step it is.
@@ -283,7 +284,7 @@ const char* dem_last_error(const dem_sim* sim);
 
 /* ---- batching and serving -------------------------------------------------
  * An engine steps many independent systems together: every kernel of a step
- * covers all attached systems in one launch, one HIP graph per step.  State
+ * covers all attached systems in one launch (dem_step).  State
  * and contact history stay in each system's own device buffers. */
 
 /* hbm_budget_bytes: total device footprint the attached systems may use. */

@@ -70,3 +70,25 @@ def test_pairs_equal_cells(n, periodic):
     for a, b in zip(*got):
         for k in FIELDS + ("pair_keys", "pair_hist"):
             assert np.array_equal(a[k], b[k]), k
+
+
+@pytest.mark.parametrize("fused", [1, 2])
+@pytest.mark.parametrize("n_steps", [2, 15, 16, 23, 64, 65])
+def test_steps_of_one_call(fused, n_steps):
+    """However many steps a call takes to a launch, the state is that of as
+    many calls of one step."""
+    from paper_2311_11322_amd import dem
+    print("[case] steps of one call", fused, n_steps, flush=True)
+    prm, args = _system(200, False)
+    got = []
+    for calls in ([n_steps], [1] * n_steps):
+        sim = dem.Sim(prm, max_contacts=64)
+        sim.set_tuning(fused=fused)
+        sim.add_aggregates(*args)
+        for n in calls:
+            sim.step(n)
+        got.append(sim.read_state(FIELDS, pairs=True))
+        sim.close()
+    assert got[0]["step"] == n_steps
+    for k in FIELDS + ("pair_keys", "pair_hist"):
+        assert np.array_equal(got[0][k], got[1][k]), k
