@@ -37,16 +37,14 @@ CONTACT_BYTES_FIXED = 390
 CONTACT_BYTES_PER_CONTACT = 64
 
 
-# HBM traffic of the gravity stage per launch (bytes), from rocprofv3 --pmc
-# FETCH_SIZE and WRITE_SIZE runs scaled by a plain-copy calibration (see the
-# profile summaries); valid only for the gravity source it was measured on.
+# HBM traffic of the gravity stage per launch (bytes), from rocprofv3 --pmc runs
+# of the L2-to-memory request counters (see the profile summaries); valid only for
+# the gravity source it was measured on.
 MEASURED_TRAFFIC = {
-    # (precision, spheres, tile, form of the exact sum):
+    # (precision, spheres, tile asked for or the first supported, form of the exact sum):
     #     (bytes per launch, source_hash("kernels_gravity.hip"))
-    ("fp64", 124958, 512, 1): (2299.0e6, "065b5f21aae1cf9c"),
-    ("fp32", 124958, 1024, 1): (539.8e6, "065b5f21aae1cf9c"),
-    ("fp64", 124958, 512, 2): (196.9e6, "065b5f21aae1cf9c"),
-    ("fp64", 499845, 512, 1): (26922.6e6, "065b5f21aae1cf9c"),
+    ("fp64", 124958, 512, 1): (2623.5e6, "efd60b0144299520"),
+    ("fp32", 124958, 1024, 1): (1703.8e6, "efd60b0144299520"),
 }
 
 
@@ -55,8 +53,7 @@ MEASURED_TRAFFIC = {
 # gravity source it was measured on.
 MEASURED_TREE_FLOP = {
     # (spheres, opening angle, leaf, order): (FLOP per launch, source_hash("kernels_tree.hip"))
-    (124958, 0.5, 32, 4): (3.609e10, "471bb11951ce97d0"),
-    (999660, 0.5, 32, 4): (3.797e11, "471bb11951ce97d0"),
+    (124958, 0.5, 32, 4): (3.609e10, "717675e5cf6ba7e6"),
 }
 
 
