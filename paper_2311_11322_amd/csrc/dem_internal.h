@@ -489,6 +489,11 @@ __device__ __forceinline__ int cell_coord(double x, double lo, double inv_cell, 
   return (int)c;
 }
 
+// The pile's status as another thread or block may have set it in this launch.
+__device__ __forceinline__ int status_of(const PileDev& P) {
+  return __hip_atomic_load(&P.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Workgroups are dispatched round-robin over the 8 XCDs, each with its own
 // L2.  This bijection of [0, n) gives XCD x (blocks b with b % 8 == x) one
 // contiguous range of logical blocks, so spatially adjacent work shares an

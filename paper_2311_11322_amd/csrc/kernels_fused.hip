@@ -31,11 +31,6 @@ constexpr int kPairThreads = kFusedThreads - 64;  // of the search without cells
 constexpr int kPairsMax = kPairThreads;           // its spheres at most
 constexpr int kFusedSpheres = kFusedThreads;      // spheres whose contacts are taken together
 
-// The pile's status as another thread of the workgroup may have set it.
-__device__ __forceinline__ int status_of(const PileDev& P) {
-  return __hip_atomic_load(&P.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 // Between stages: a workgroup barrier.  All waves of the workgroup run on
 // one compute unit and share its first-level cache, so the barrier's
 // workgroup-scope release and acquire make every global write of a stage

@@ -330,6 +330,14 @@ __device__ __forceinline__ void store_runs(const PileDev& P, int k, uint32_t i, 
   put_run<st>(buf + (kRunLds - nlo) * st, nlo, lane, Lanes, P.lo_nbr + l0);
 }
 
+// Whether the pile's search goes on.  A failed pile's does not; but a stateless
+// search (given positions) whose lists are full goes on counting, so that it
+// reports how many contacts there are.
+__device__ __forceinline__ bool searching(const PileDev& P) {
+  const int st = status_of(P);
+  return st == 0 || (st == kStCapacity && (P.given || P.na == 0));
+}
+
 // Room for nup upper and nlo lower contacts in the pile's lists: the first
 // entries, taken in arrival order (the order of the runs in the lists decides
 // no result; read-outs go by sphere).  False, and a capacity failure, when
@@ -351,13 +359,13 @@ __device__ __forceinline__ bool take_runs(PileDev& P, uint32_t nup, uint32_t nlo
 // of kBigRun entries and fill[4]; every thread of the block calls this):
 // they split the cells within reach of any other sphere and the big
 // spheres' cell, gather both runs in LDS, rank-sort them and store them.  A
-// run longer than kBigRun is a capacity failure.
+// run longer than kBigRun is counted, and a capacity failure.
 __device__ __forceinline__ void search_big_one(PileDev& P, int kb, int tid, int nthreads,
                                                uint32_t* buf_up, uint32_t* buf_lo,
                                                uint32_t* fill) {
   // one read of the status for the whole block (another block of this pile
   // may set it meanwhile), so that every thread takes the same path
-  if (tid == 0) fill[0] = P.status != 0 ? 1u : 0u;
+  if (tid == 0) fill[0] = searching(P) ? 0u : 1u;
   __syncthreads();
   const bool failed = fill[0] != 0u;
   __syncthreads();
@@ -435,13 +443,11 @@ __device__ __forceinline__ void search_big_one(PileDev& P, int kb, int tid, int 
   }
   __syncthreads();
   const uint32_t run_up = fill[0], run_lo = fill[1];
-  if (run_up > (uint32_t)kBigRun || run_lo > (uint32_t)kBigRun) {
-    if (tid == 0) atomicOr(&P.status, kStCapacity);
-    return;
-  }
   if (tid == 0) {
+    const bool fits = run_up <= (uint32_t)kBigRun && run_lo <= (uint32_t)kBigRun;
+    if (!fits) atomicOr(&P.status, kStCapacity);
     uint32_t u0, l0;
-    const bool ok = take_runs(P, run_up, run_lo, u0, l0);
+    const bool ok = take_runs(P, run_up, run_lo, u0, l0) && fits;
     fill[2] = ok ? u0 : 0xffffffffu;
     fill[3] = l0;
     if (ok) {
