@@ -411,11 +411,17 @@ __global__ __launch_bounds__(kBlock) void k_grav_combine(const PileDev* __restri
                                                          const WorkItem* __restrict__ wl,
                                                          int precision) {
   __shared__ double red[4][3][64];
+  __shared__ int failed;
   const WorkItem w = wl[blockIdx.x >> 2];
   const int base = w.base + (int)(blockIdx.x & 3) * 64;
   const PileDev& P = piles[w.pile];
   const int ns = P.ns;
-  if (P.status != 0 || P.G == 0.0 || base >= ns) return;   // uniform over the block
+  if (P.G == 0.0 || base >= ns) return;                    // uniform over the block
+  // one read of the status for the whole block: the search and the contact
+  // forces run beside this and may set it, and every wave takes the barrier below
+  if (threadIdx.x == 0) failed = status_of(P);
+  __syncthreads();
+  if (failed != 0) return;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int k = base + lane;
   double g[3] = {0.0, 0.0, 0.0};
