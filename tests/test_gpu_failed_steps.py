@@ -1,6 +1,8 @@
 """Steps that fail inside a call of many steps -- too many contacts, an overlap above
-the limit -- in each route of a staged step: eight to a graph launch, and with
-gravity beside the contacts (with and without a perturber).  The state is that at the start of the failing
+the limit -- in each route of a step: the pair search and the cells of the
+one-workgroup step (up to 64 steps a launch), its two parts around gravity, staged
+steps eight to a graph launch, and staged steps with gravity beside the contacts
+(with and without a perturber).  The state is that at the start of the failing
 step, bit for bit, and the run goes on from there like one that did not fail."""
 import numpy as np
 import pytest
@@ -11,6 +13,11 @@ pytestmark = pytest.mark.gpu
 
 FIELDS = ("agg_pos", "agg_vel", "agg_acc", "agg_torque", "agg_quat", "agg_spin_body")
 ROUTES = {                   # spheres, G, tuning, perturber
+    "pairs": (200, 0.0, {}, False),
+    "pairs_most": (448, 0.0, dict(fused=1), False),
+    "cells": (500, 0.0, dict(fused=1), False),
+    "parts": (200, 1.0, {}, False),
+    "parts_perturber": (200, 1.0, {}, True),
     "staged": (3000, 0.0, {}, False),
     "staged_large": (40000, 0.0, {}, False),
     "gravity": (3000, 1.0, {}, False),
