@@ -762,7 +762,13 @@ dem_status ensure_graph(Batch& b, hipStream_t st, int steps, dem_sim* errsim) {
 // launch, and the few left over are enqueued kernel by kernel (a step of 2,350
 // spheres by graphs of one step 49.9 us, of eight 45.5, without graphs 45.8 and
 // more work for the host; with gravity, flyby of 3,000, one step 78.1, four 77.3).
-dem_status run_steps(Batch& b, hipStream_t st, int64_t n_steps, dem_sim* errsim) {
+// fresh: the first step works its cells out first (after a restore).
+dem_status run_steps(Batch& b, hipStream_t st, int64_t n_steps, bool fresh, dem_sim* errsim) {
+  if (fresh) {
+    enqueue_pass(b, st, kModeStep, false, true);
+    HIPCHK(errsim, hipGetLastError());
+    if (--n_steps == 0) return DEM_OK;
+  }
   if (b.n_fused_ng > 0) {
     for (int64_t k = 0; k < n_steps; k += kFusedSteps)
       launch_fused(st, b.d_table, b.pl_fused_ng, b.n_fused_ng, b.cp, kModeStep, 3, b.precision,
@@ -782,9 +788,9 @@ dem_status run_steps(Batch& b, hipStream_t st, int64_t n_steps, dem_sim* errsim)
   return DEM_OK;
 }
 
-// Eager launches of n_steps passes with a HIP event between consecutive
-// kernels on the stream; accumulates each kernel family's milliseconds.
-dem_status profiled_passes(Batch& b, hipStream_t st, int64_t n_steps,
+// Eager launches of n_steps passes (the first fresh or not) with a HIP event between
+// consecutive kernels on the stream; accumulates each kernel family's milliseconds.
+dem_status profiled_passes(Batch& b, hipStream_t st, int64_t n_steps, bool fresh,
                            std::vector<hipEvent_t>& events, std::vector<double>& prof_ms,
                            int64_t& prof_steps, dem_sim* errsim) {
   const size_t per_step = size_t(2) * kNumStages;
@@ -799,7 +805,7 @@ dem_status profiled_passes(Batch& b, hipStream_t st, int64_t n_steps,
     hipEvent_t* ev = &events[size_t(k) * per_step];
     enqueue_pass_marked(b, st, kModeStep, [&](int m, hipStream_t s, bool begin) {
       if (rec == hipSuccess) rec = hipEventRecord(ev[2 * m + (begin ? 0 : 1)], s);
-    }, false, false);
+    }, false, fresh && k == 0);
   }
   HIPCHK(errsim, rec);
   HIPCHK(errsim, hipStreamSynchronize(st));
@@ -820,7 +826,7 @@ dem_status profiled_passes(Batch& b, hipStream_t st, int64_t n_steps,
 // the second stream beside the contact kernels), with a HIP event before and
 // after the gravity stage only, on the stream that runs it; accumulates the
 // gravity stage's milliseconds.
-dem_status gravity_timed_passes(Batch& b, hipStream_t st, int64_t n_steps,
+dem_status gravity_timed_passes(Batch& b, hipStream_t st, int64_t n_steps, bool fresh,
                                 std::vector<hipEvent_t>& events, std::vector<double>& prof_ms,
                                 int64_t& prof_steps, dem_sim* errsim) {
   HIPCHK(errsim, ensure_side(b));
@@ -835,7 +841,7 @@ dem_status gravity_timed_passes(Batch& b, hipStream_t st, int64_t n_steps,
     hipEvent_t* ev = &events[size_t(2) * k];
     enqueue_pass_marked(b, st, kModeStep, [&](int m, hipStream_t s, bool begin) {
       if (m == kStageGravity && rec == hipSuccess) rec = hipEventRecord(ev[begin ? 0 : 1], s);
-    }, true, false);
+    }, true, fresh && k == 0);
   }
   HIPCHK(errsim, rec);
   HIPCHK(errsim, hipStreamSynchronize(st));
@@ -1325,27 +1331,17 @@ dem_status dem_step(dem_sim* s, int64_t n_steps) {
   s->stepped = true;
   if (n_steps == 0) return DEM_OK;
   s->mirrored = false;
-  if (s->regrid) {
-    // the first step after a restore works its cells out first
-    enqueue_pass(s->own, s->stream, kModeStep, false, true);
-    HIPCHK(s, hipGetLastError());
-    s->regrid = false;
-    --n_steps;
-  }
-  if (n_steps == 0) {
-    // that was the only step
-  } else if (s->profiling == 1) {
-    dem_status st = profiled_passes(s->own, s->stream, n_steps, s->events, s->prof_ms,
-                                    s->prof_steps, s);
-    if (st != DEM_OK) return st;
-  } else if (s->profiling == 2) {
-    dem_status st = gravity_timed_passes(s->own, s->stream, n_steps, s->events, s->prof_ms,
-                                         s->prof_steps, s);
-    if (st != DEM_OK) return st;
-  } else {
-    dem_status st = run_steps(s->own, s->stream, n_steps, s);
-    if (st != DEM_OK) return st;
-  }
+  dem_status st;
+  if (s->profiling == 1)
+    st = profiled_passes(s->own, s->stream, n_steps, s->regrid, s->events, s->prof_ms,
+                         s->prof_steps, s);
+  else if (s->profiling == 2)
+    st = gravity_timed_passes(s->own, s->stream, n_steps, s->regrid, s->events, s->prof_ms,
+                              s->prof_steps, s);
+  else
+    st = run_steps(s->own, s->stream, n_steps, s->regrid, s);
+  if (st != DEM_OK) return st;
+  s->regrid = false;
   HIPCHK(s, get_entry(s, s->own.d_table, s->stream));
   if (s->h.status != 0) {
     dem_status code = status_code(s->h.status);
@@ -2119,24 +2115,12 @@ dem_status dem_engine_step(dem_engine* e, int64_t n_steps) {
     regrid = regrid || s->regrid;
     s->mirrored = false;
   }
-  if (regrid) {
-    // the first step after a restore works its cells out first
-    enqueue_pass(b, e->stream, kModeStep, false, true);
-    const hipError_t he = hipGetLastError();
-    if (he != hipSuccess) return fail(b.members[0], DEM_ERR_DEVICE, hip_msg(he, "step"));
-    for (dem_sim* s : b.members) s->regrid = false;
-    --n_steps;
-  }
-  if (n_steps == 0) {
-    // that was the only step
-  } else if (e->profiling) {
-    dem_status r = profiled_passes(b, e->stream, n_steps, e->events, e->prof_ms, e->prof_steps,
-                                   b.members[0]);
-    if (r != DEM_OK) return r;
-  } else {
-    dem_status r = run_steps(b, e->stream, n_steps, b.members[0]);
-    if (r != DEM_OK) return r;
-  }
+  const dem_status r =
+      e->profiling ? profiled_passes(b, e->stream, n_steps, regrid, e->events, e->prof_ms,
+                                     e->prof_steps, b.members[0])
+                   : run_steps(b, e->stream, n_steps, regrid, b.members[0]);
+  if (r != DEM_OK) return r;
+  for (dem_sim* s : b.members) s->regrid = false;
   // one read-back of every entry's bookkeeping
   std::vector<PileDev> tab(b.members.size());
   hipError_t he = hipMemcpyAsync(tab.data(), b.d_table, tab.size() * sizeof(PileDev),
