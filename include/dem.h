@@ -23,6 +23,9 @@
  *    aggregate ids are consecutive in call order.  Both are persistent and
  *    define the canonical contact order: pairs (i, j), i < j, sorted
  *    lexicographically, keyed as (uint64)i << 32 | j.
+ *  - Calls on one system from several threads take turns, a read-out and a step
+ *    (or an engine's step of the system) among them; different systems do not
+ *    wait for each other.
  *  - Device memory is owned by the library and obtained through the
  *    caller's allocator (NULL: hipMalloc/hipFree).  All device work is
  *    issued on the stream given at creation (NULL: the null stream).
@@ -188,7 +191,8 @@ dem_status dem_add_aggregates(dem_sim* sim, int64_t n_agg, const int32_t* sphere
  * STATE if the system is attached to an engine or has no aggregates. */
 dem_status dem_step(dem_sim* sim, int64_t n_steps);
 
-/* Copy the state to host buffers (synchronises the stream). */
+/* Copy the state to host buffers (synchronises the stream).  The fields are put in
+ * order on the device, in the system's own step buffers. */
 dem_status dem_read_state(dem_sim* sim, dem_state* out);
 
 /* Counts: aggregates, spheres, contacts of the last evaluation. */

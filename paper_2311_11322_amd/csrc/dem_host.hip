@@ -329,6 +329,11 @@ struct Batch {
 };
 
 struct dem_sim {
+  // Held by every call that touches the system's device buffers: a read-out uses
+  // buffers that only a step uses otherwise, so readers in several threads, and
+  // a reader and a stepping thread, take turns.  An attached system's calls hold
+  // its engine too, whose steps hold the engine alone.
+  std::recursive_mutex use;
   dem_params prm{};
   Allocator alloc;
   hipStream_t stream = nullptr;
@@ -360,6 +365,7 @@ struct dem_sim {
 };
 
 struct dem_engine {
+  std::recursive_mutex use;
   size_t budget = 0, used = 0;
   hipStream_t stream = nullptr;
   Batch batch;
@@ -393,6 +399,14 @@ dem_status require_device(dem_sim* s) {
                     "loading this library");
   return DEM_OK;
 }
+
+// A system, and the engine it is attached to, held for one call.
+struct Hold {
+  std::unique_lock<std::recursive_mutex> sim, engine;
+  explicit Hold(dem_sim* s) : sim(s->use) {
+    if (s->engine) engine = std::unique_lock<std::recursive_mutex>(s->engine->use);
+  }
+};
 
 #define HIPCHK(sim, call)                                                   \
   do {                                                                      \
@@ -1320,6 +1334,7 @@ dem_status dem_add_aggregates(dem_sim* s, int64_t n_agg, const int32_t* spa, con
 
 dem_status dem_step(dem_sim* s, int64_t n_steps) {
   if (!s) return fail(nullptr, DEM_ERR_INVALID_ARG, "sim is NULL");
+  const Hold hold(s);
   if (s->engine) return fail(s, DEM_ERR_STATE, "system is attached to an engine");
   if (!s->has_aggs) return fail(s, DEM_ERR_STATE, "no aggregates");
   if (n_steps < 0) return fail(s, DEM_ERR_INVALID_ARG, "negative step count");
@@ -1401,6 +1416,7 @@ dem_status store_rows(dem_sim* s, double* d, int k, int64_t n, const double* hos
 
 dem_status dem_read_state(dem_sim* s, dem_state* out) {
   if (!s || !out) return fail(s, DEM_ERR_INVALID_ARG, "NULL argument");
+  const Hold hold(s);
   if (!s->has_aggs) return fail(s, DEM_ERR_STATE, "no aggregates");
   hipStream_t st = stream_of(s);
   if (!s->mirrored) HIPCHK(s, get_entry(s, entry_of(s), st));
@@ -1496,6 +1512,7 @@ dem_status dem_read_state(dem_sim* s, dem_state* out) {
 
 dem_status dem_restore_state(dem_sim* s, const dem_state* in) {
   if (!s || !in) return fail(s, DEM_ERR_INVALID_ARG, "NULL argument");
+  const Hold hold(s);
   if (!s->has_aggs) return fail(s, DEM_ERR_STATE, "no aggregates");
   if (s->engine) return fail(s, DEM_ERR_STATE, "system is attached to an engine");
   if (!in->agg_pos || !in->agg_vel || !in->agg_acc || !in->agg_torque || !in->agg_quat ||
@@ -1547,6 +1564,7 @@ dem_status dem_restore_state(dem_sim* s, const dem_state* in) {
 
 dem_status dem_set_forcing(dem_sim* s, const dem_forcing* f) {
   if (!s || !f) return fail(s, DEM_ERR_INVALID_ARG, "NULL argument");
+  const Hold hold(s);
   bool ok = std::isfinite(f->spin_dw) && std::isfinite(f->pert_mass) && f->pert_mass >= 0.0 &&
             std::isfinite(f->stop_growth) && f->stop_growth >= 0.0;
   for (int k = 0; k < 3; ++k) ok = ok && std::isfinite(f->pert_pos[k]) && std::isfinite(f->pert_vel[k]);
@@ -1577,6 +1595,7 @@ dem_status dem_set_forcing(dem_sim* s, const dem_forcing* f) {
 
 dem_status dem_get_forcing(dem_sim* s, dem_forcing* out) {
   if (!s || !out) return fail(s, DEM_ERR_INVALID_ARG, "NULL argument");
+  const Hold hold(s);
   *out = s->forcing;
   if (!s->has_aggs) return DEM_OK;
   if (!s->mirrored) HIPCHK(s, get_entry(s, entry_of(s), stream_of(s)));
@@ -1593,6 +1612,7 @@ dem_status dem_get_forcing(dem_sim* s, dem_forcing* out) {
 
 dem_status dem_reserve_contacts(dem_sim* s, int32_t per_sphere) {
   if (!s || per_sphere <= 0) return fail(s, DEM_ERR_INVALID_ARG, "bad argument");
+  const Hold hold(s);
   if (s->engine) return fail(s, DEM_ERR_STATE, "system is attached to an engine");
   if (!s->has_aggs) {
     s->c_max = per_sphere;
@@ -2051,7 +2071,9 @@ dem_status engine_table(dem_engine* e, dem_sim* errsim) {
 
 dem_status dem_engine_attach(dem_engine* e, dem_sim* s) {
   if (!e || !s) return fail(s, DEM_ERR_INVALID_ARG, "NULL argument");
+  const Hold hold(s);
   if (s->engine) return fail(s, DEM_ERR_STATE, "already attached");
+  const std::lock_guard<std::recursive_mutex> with(e->use);
   if (!s->has_aggs) return fail(s, DEM_ERR_STATE, "no aggregates");
   if (s->h.status != 0) return fail(s, DEM_ERR_STATE, "system has failed; restore it first");
   if (!e->batch.members.empty() && !same_contact_model(e->batch.members[0]->prm, s->prm))
@@ -2079,6 +2101,7 @@ dem_status dem_engine_attach(dem_engine* e, dem_sim* s) {
 
 dem_status dem_engine_detach(dem_engine* e, dem_sim* s) {
   if (!e || !s) return fail(s, DEM_ERR_INVALID_ARG, "NULL argument");
+  const Hold hold(s);
   if (s->engine != e) return fail(s, DEM_ERR_STATE, "not attached to this engine");
   Batch& b = e->batch;
   HIPCHK(s, hipStreamSynchronize(e->stream));
@@ -2104,6 +2127,7 @@ dem_status dem_engine_detach(dem_engine* e, dem_sim* s) {
 
 dem_status dem_engine_step(dem_engine* e, int64_t n_steps) {
   if (!e) return fail(nullptr, DEM_ERR_INVALID_ARG, "engine is NULL");
+  const std::lock_guard<std::recursive_mutex> hold(e->use);
   Batch& b = e->batch;
   if (b.members.empty() || n_steps <= 0) return DEM_OK;
   if (b.dirty) {
