@@ -346,9 +346,10 @@ typedef struct {
     int32_t gravity_form;      /* form of the exact softened sum (Eq. 4): 0 automatic --
                                   pairs unless their partial sums would exceed 64 GiB;
                                   1 pairs: each unordered pair once, one partial sum per
-                                  sphere and tile or source segment of a tile, past 256
-                                  tiles on super-tiles of ceil(tiles / 256) tiles, one per
-                                  super-tile (at most 352 x 3 values per sphere); 2 per
+                                  sphere and tile (or half or quarter of a tile of a pile
+                                  of few), past 256 tiles on super-tiles of
+                                  ceil(tiles / 256) tiles, one per super-tile (at most
+                                  256 x 3 values per sphere); 2 per
                                   target: each ordered pair from its target's side, one
                                   partial per sphere and source split (16 splits), about
                                   1.7x the time.  Same sum in another order (rounding). */

@@ -72,7 +72,7 @@ int ceil_log2(uint64_t v) {
 // Device footprint of one system, byte for byte what alloc_pile allocates.
 struct Sizes {
   int64_t na, ns, cap, cells, g_tile, g_nt, g_np, n_rblk;
-  int64_t g_m0, g_segs, g_seg;   // see PileDev
+  int64_t g_m0, g_segs;      // see PileDev
   int g_form;                // 1 super-tile pairs, 2 per-target
   bool grav;
   bool tree;
@@ -136,25 +136,23 @@ Sizes pile_sizes(const dem_params& p, int64_t na, int64_t ns, int c_max, int til
   z.tree = z.grav && p.gravity_tree;
   z.tree_nodes = z.tree ? ((z.cells << 3) - 1) / 7 : 0;
   z.precision = p.precision;
-  // the exact sum's form: pairs (one partial per tile, source segment or
-  // super-tile) unless asked otherwise or their partials would exceed
-  // kSymPartialMax
+  // the exact sum's form: pairs (one partial per tile or super-tile) unless
+  // asked otherwise or their partials would exceed kSymPartialMax
   const GravPlan plan = gravity_plan(p.precision, ns, tile);
   z.g_tile = plan.tile;
   z.g_nt = (ns + z.g_tile - 1) / z.g_tile;
-  z.g_seg = plan.seg;
-  z.g_segs = z.g_tile / z.g_seg;
+  z.g_m0 = z.g_nt;
+  z.g_segs = 1;
   int64_t pair_np;
   if (z.g_nt > kGravSlots) {
-    const int64_t span = (z.g_nt + kGravSlots - 1) / kGravSlots;
-    z.g_m0 = -1;
+    const int64_t span = (z.g_nt + kGravSlots - 1) / kGravSlots;   // tiles per super-tile
     pair_np = (z.g_nt + span - 1) / span;
   } else {
-    z.g_m0 = std::min<int64_t>(plan.m0, z.g_nt);
-    const int64_t last = ns - (z.g_nt - 1) * z.g_tile;       // slots of the last tile
+    z.g_m0 = plan.m0;
+    z.g_segs = plan.segs;
+    const int64_t seg = z.g_tile / z.g_segs, last = ns - (z.g_nt - 1) * z.g_tile;
     pair_np = z.g_m0 == z.g_nt ? z.g_nt
-                               : z.g_m0 + (z.g_nt - z.g_m0 - 1) * z.g_segs +
-                                     (last + z.g_seg - 1) / z.g_seg;
+                               : z.g_m0 + (z.g_nt - z.g_m0 - 1) * z.g_segs + (last + seg - 1) / seg;
   }
   const int64_t part_bytes = pair_np * 3 * ns * (p.precision == 1 ? 4 : 8);
   z.g_form = form != 0 ? form : (part_bytes > kSymPartialMax ? 2 : 1);
@@ -162,8 +160,9 @@ Sizes pile_sizes(const dem_params& p, int64_t na, int64_t ns, int c_max, int til
     if (tile <= 0) z.g_tile = default_tile(p.precision);
     z.g_nt = (ns + z.g_tile - 1) / z.g_tile;
     const int64_t span = (z.g_nt + kGravSplits - 1) / kGravSplits;
-    z.g_m0 = -1;
     z.g_np = (z.g_nt + span - 1) / span;
+    z.g_m0 = z.g_nt;
+    z.g_segs = 1;
   } else {
     z.g_np = pair_np;
   }
@@ -494,9 +493,9 @@ dem_status rebuild(Batch& b, hipStream_t st, dem_sim* errsim) {
       b.any_grav = true;
       pairs += (int64_t)h.ns * h.ns / 2;
       if (!(h.soft_frac > 0.0)) b.all_soft = false;
-      // every (target tile, source tile or segment) and every super-tile pair
-      // (si <= sj) of the pile: each unordered pair once; or every (target
-      // group, source split) of the per-target form
+      // every pair of tiles (i <= j), or of super-tiles, of the pile: each
+      // unordered pair once; or every (target group, source split) of the
+      // per-target form
       int g = 0;
       while (g < n_groups && tiles[g] != h.g_tile) ++g;
       if (g == n_groups) tiles[n_groups++] = h.g_tile;
@@ -507,16 +506,16 @@ dem_status rebuild(Batch& b, hipStream_t st, dem_sim* errsim) {
         for (int tg = 0; tg < n_grp; ++tg)
           for (int sp = 0; sp < h.g_np; ++sp) gsg[g].push_back({p, tg, sp, 0});
       } else {
-        if (h.g_m0 >= 0) {
+        if (h.g_nt <= kGravSlots) {
           auto row0 = [&](int t) { return t < h.g_m0 ? t : h.g_m0 + (t - h.g_m0) * h.g_segs; };
           for (int i = 0; i < h.g_nt; ++i)
             for (int j = i; j < h.g_nt; ++j) {
               const int j1 = std::min((j + 1) * h.g_tile, h.ns);
-              const int seg = j < h.g_m0 ? h.g_tile : h.g_seg;
+              const int seg = j < h.g_m0 ? h.g_tile : h.g_tile / h.g_segs;
               int row = row0(j);
               for (int s = j * h.g_tile; s < j1; s += seg)
                 glg[g].push_back({p, i * h.g_tile, s, std::min(s + seg, j1), row++,
-                                  i == j ? -1 : row0(i), {0, 0}});
+                                  i == j ? -1 : row0(i), seg / grav_pair_waves(h.g_tile), 0});
             }
         } else {
           // super-tiles of several tiles: items weighted by their tile pairs
@@ -967,7 +966,6 @@ dem_status alloc_pile(dem_sim* s, int64_t na, int64_t ns) {
   h.g_np = (int32_t)s->sz.g_np;
   h.g_m0 = (int32_t)s->sz.g_m0;
   h.g_segs = (int32_t)s->sz.g_segs;
-  h.g_seg = (int32_t)s->sz.g_seg;
   h.n_rblk = (int32_t)s->sz.n_rblk;
   h.box = s->prm.box[0];
   h.G = s->prm.G;

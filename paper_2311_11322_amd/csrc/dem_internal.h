@@ -93,11 +93,9 @@ struct PileDev {
   int32_t g_tile;            // gravity tile (slots per tile)
   int32_t g_nt;              // gravity tiles
   int32_t g_form;            // 1: symmetric super-tile pairs; 2: per-target
-  int32_t g_np;              // partial-sum rows: tiles and source segments, super-tiles, or splits
-  int32_t g_m0;              // pairs of single tiles: tiles from g_m0 on are cut into segments
-  int32_t g_segs;            // source segments of such a tile (rows g_m0 + (J - g_m0) g_segs + s)
-  int32_t g_seg;             // sources per segment
-  int32_t pad7;
+  int32_t g_np;              // partial-sum rows: tiles x segments, super-tiles, or source splits
+  int32_t g_m0;              // pairs of single tiles: tiles from g_m0 on are cut, as sources,
+  int32_t g_segs;            // into g_segs segments (rows g_m0 + (J - g_m0) g_segs + s)
   int32_t n_rblk;            // reconstruct blocks (bbox partials)
   int32_t n_periodic;        // cells per axis of a periodic pile
   int32_t member_scan;       // 1: reduction finds members by scanning all spheres
@@ -214,14 +212,15 @@ struct WorkItem {
 };
 
 // One block of the pair kernel: the targets from slot i0 on (one tile) against
-// the sources in slots [j0, j1) of the same or a later tile.  The targets' sums
-// go to row row_t of the partial sums, the sources' reactions to row row_r
-// (row_r < 0: sources of the targets' own tile, ordered pairs one way).
+// the sources in slots [j0, j1) of the same or a later tile, per of them for each
+// wave.  The targets' sums go to row row_t of the partial sums, the sources'
+// reactions to row row_r (row_r < 0: sources of the targets' own tile, ordered
+// pairs one way).
 struct GravPair {
   int32_t pile;
   int32_t i0, j0, j1;
   int32_t row_t, row_r;
-  int32_t pad[2];
+  int32_t per, pad;
 };
 
 // One block of the super-tile kernel: the super-tile pair (ti, tj), ti <= tj,
@@ -288,16 +287,17 @@ void launch_gravity_combine(hipStream_t st, const PileDev* piles, const WorkItem
 // Supported tile sizes for a precision (the large piles' default first);
 // returns the count.
 int gravity_tiles(int precision, int* tiles);
-// How the exact sum of a pile in the pair form is cut into blocks: its tile
-// (the given one, or chosen by the number of spheres when tile is 0) and, for
-// piles of at most kGravSlots tiles, which tiles are cut into segments of how
-// many sources.
+// How the exact sum of a pile in the pair form is cut into blocks: its tile (the
+// given one, or chosen by the number of spheres when tile is 0) and, for piles of
+// at most kGravSlots tiles, the segments into which tiles from m0 on are cut as sources.
 struct GravPlan {
-  int tile, seg, m0;
+  int tile, segs, m0;
 };
+// Waves of a block of the pair kernel, which share its sources, for a tile size.
+constexpr int grav_pair_waves(int tile) { return tile < 256 ? tile / 64 : 4; }
 GravPlan gravity_plan(int precision, int64_t ns, int tile);
 // Tile sizes the pair kernel is built for: the supported ones and smaller.
-constexpr int kGravTileSizes = 5;
+constexpr int kGravTileSizes = 6;
 // Aggregates in one launch from which the member reduction stages its
 // members through LDS (below it, direct member reads are faster: few waves,
 // and the members stay in L2 between a wave's member iterations).

@@ -2,20 +2,21 @@
 // paper, with Plummer softening eps_ij = soft_frac (s_i + s_j) / 2).
 //
 // Spheres are taken in cell-sorted (Morton) order and cut into tiles of B
-// slots.  A pile of at most kGravSlots tiles runs k_grav_pairs: one wave per
-// (target tile I, sources of tile J >= I or of a segment of it), so every
-// unordered pair of spheres is evaluated once (Newton's third law):
+// slots.  A pile of at most kGravSlots tiles runs k_grav_pairs: one block per
+// pair of tiles (I, J >= I), or per segment of J, so every unordered pair of spheres
+// is evaluated once (Newton's third law), by up to four waves that share the sources:
 //  * each lane holds IPT = B / 64 targets in registers, with their sums;
 //  * the sources enter 64 at a time, one per lane, together with a reaction
 //    accumulator, and rotate one lane per step (DPP wave_ror:1), so that after
 //    64 steps every source has met every target of the wave and is back in
 //    its own lane holding its complete reaction sum;
 //  * sources of the targets' own tile rotate without a reaction (ordered
-//    pairs, one way).
-// Each block stores its targets' sums in the row of its sources (tile or
-// segment) and its sources' reactions in the row of its targets' tile; the
-// combine kernel adds a sphere's rows in a fixed order, so the result is
-// deterministic and independent of other piles.
+//    pairs, one way);
+//  * the waves' sums of a target are added in LDS, in order.
+// Each block stores its targets' sums in the row of its sources (tile or segment)
+// and its sources' reactions in the row of its targets' tile; the combine kernel
+// adds a sphere's rows in a fixed order, so the result is deterministic and
+// independent of other piles.
 //
 // A larger pile runs k_grav_tiles: its tiles are grouped into at most
 // kGravSlots super-tiles of `span` consecutive tiles and one wave takes one
@@ -121,13 +122,27 @@ __device__ __forceinline__ void ring(Src<T> s, const T (&xi)[IPT], const T (&yi)
 #define GRAV_WAVES(T, IPT) \
   __attribute__((amdgpu_waves_per_eu(1, (sizeof(T) == 8 && IPT == 8) ? 2 : 8)))
 
+// One block per (target tile, source tile or segment of it).  Bound by the FP64
+// (FP32) instruction rate of `ring`: a pair of tiles of 512 takes one compute unit
+// 56 us (28 us).  Up to four waves share the sources, because a row of partial sums
+// then serves all of them: with one wave per block a small pile needed a row for
+// every 64 or 128 sources to fill the chip, and an engine that fills it anyway spent
+// its gain, and more, on writing and reading those rows.  Gravity stage, FP64, in
+// tiles of 512 by one wave / a row per 64 to 256 sources / so: 25 piles of 16,000
+// spheres 2.59 / 2.77 / 2.59 ms, one of 13,001 231 / 102 / 92 us, 124,958 6017 / 5999
+// / 6032 us.
 template <typename T, int IPT, bool SOFT>
-__global__ __launch_bounds__(64) GRAV_WAVES(T, IPT) void k_grav_pairs(
+__global__ __launch_bounds__(64 * grav_pair_waves(64 * IPT)) GRAV_WAVES(T, IPT) void k_grav_pairs(
     const PileDev* __restrict__ piles, const GravPair* __restrict__ gp) {
+  constexpr int B = 64 * IPT, W = grav_pair_waves(64 * IPT);
+  __shared__ T sums[W][3][B];
+  __shared__ int failed[W];
   const GravPair it = gp[blockIdx.x];
   const PileDev& P = piles[it.pile];
-  if (P.status != 0) return;
-  const int ns = P.ns, lane = threadIdx.x;
+  const int ns = P.ns, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  // The search and the contact forces run beside this and may set the status: each
+  // wave takes what it reads to the block's barrier, and none leaves before.
+  const int st = P.status;
   const Rec64* __restrict__ rec = (const Rec64*)P.jrec;
   double c15;
   series_coeffs(c15);
@@ -151,21 +166,23 @@ __global__ __launch_bounds__(64) GRAV_WAVES(T, IPT) void k_grav_pairs(
     mi[u] = k < ns ? r.m : (T)0;
     ax[u] = ay[u] = az[u] = (T)0;
   }
+  // the wave's sources; none in a short last tile's last waves
+  const int j0 = it.j0 + wv * it.per, j1 = st != 0 ? j0 : min(j0 + it.per, it.j1);
   // with few targets per lane a round of 64 sources is short, so the next 64
   // are loaded while the current ones go round
   constexpr bool kAhead = IPT < 8;
-  Rec64 next = rec[min(it.j0 + lane, it.j1 - 1)];
-  for (int jc = it.j0; jc < it.j1; jc += 64) {
+  Rec64 next = rec[min(j0 + lane, it.j1 - 1)];
+  for (int jc = j0; jc < j1; jc += 64) {
     const int jx = jc + lane;
     Src<T> s = relative<T>(next, an);
-    if (jx >= it.j1) s.m = (T)0;
+    if (jx >= j1) s.m = (T)0;
     if (kAhead) next = rec[min(jx + 64, it.j1 - 1)];
     T bx, by, bz;
     if (it.row_r < 0) {
       ring<T, IPT, SOFT, false>(s, xi, yi, zi, ei, mi, ax, ay, az, c15, bx, by, bz);
     } else {
       ring<T, IPT, SOFT, true>(s, xi, yi, zi, ei, mi, ax, ay, az, c15, bx, by, bz);
-      if (jx < it.j1) {
+      if (jx < j1) {
         T* q = part + (size_t)it.row_r * 3 * ns + jx;
         q[0] = -bx;
         q[ns] = -by;
@@ -174,16 +191,27 @@ __global__ __launch_bounds__(64) GRAV_WAVES(T, IPT) void k_grav_pairs(
     }
     if (!kAhead) next = rec[min(jx + 64, it.j1 - 1)];
   }
+  T* __restrict__ row = part + (size_t)it.row_t * 3 * ns + it.i0;
+  const int n = min(B, ns - it.i0);
 #pragma unroll
   for (int u = 0; u < IPT; ++u) {
-    const int k = it.i0 + u * 64 + lane;
-    if (k < ns) {
-      T* q = part + (size_t)it.row_t * 3 * ns + k;
-      q[0] = ax[u];
-      q[ns] = ay[u];
-      q[2 * (size_t)ns] = az[u];
-    }
+    sums[wv][0][u * 64 + lane] = ax[u];
+    sums[wv][1][u * 64 + lane] = ay[u];
+    sums[wv][2][u * 64 + lane] = az[u];
   }
+  if (lane == 0) failed[wv] = st;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < W; ++w)
+    if (failed[w] != 0) return;
+#pragma unroll
+  for (int c = 0; c < 3; ++c)
+    for (int k = threadIdx.x; k < n; k += 64 * W) {
+      double g = (double)sums[0][c][k];
+#pragma unroll
+      for (int w = 1; w < W; ++w) g += (double)sums[w][c][k];
+      row[(size_t)c * ns + k] = (T)g;
+    }
 }
 
 template <typename T, int IPT, bool SOFT>
@@ -372,15 +400,14 @@ __global__ __launch_bounds__(64) void k_grav_split(const PileDev* __restrict__ p
 }
 
 // Sum of the partials of slot k over its rows q0 <= q < q1, in row order, FP64.
-// The rows a slot of tile T receives are: every row below m0 (a tile each), the
-// first row of each cut tile before T (the reaction of its targets), and from
-// tile T on every row.  Eight rows' loads are in flight.
+// The rows of a slot are every row below m0 (a tile each), the first row of each
+// of the b cut tiles before its own (the reaction of that tile's targets), and every
+// row after those.  Eight rows' loads are in flight.
 template <typename T>
 __device__ __forceinline__ void sum_rows(const T* __restrict__ part, size_t ns, int k, int q0,
                                          int q1, int m0, int b, int segs, double g[3]) {
-  // rows of tile T and after start at m0 + b * segs, where b cut tiles precede T
   auto row = [&](int q) {
-    return q < m0 ? q : (q < m0 + b ? m0 + (q - m0) * segs : m0 + b * segs + (q - m0 - b));
+    return q < m0 ? q : (q < m0 + b ? m0 + (q - m0) * segs : b * (segs - 1) + q);
   };
   int q = q0;
   for (; q + 8 <= q1; q += 8) {
@@ -399,8 +426,8 @@ __device__ __forceinline__ void sum_rows(const T* __restrict__ part, size_t ns, 
 }
 
 // 64 sorted slots per block, four threads per slot: each adds a quarter of the
-// slot's rows -- per tile, source segment, super-tile, source split, or
-// level-2 subtree of the tree -- and the four sums are added in order, FP64.
+// slot's rows -- per tile, super-tile, source split, or level-2 subtree of the
+// tree -- and the four sums are added in order, FP64.
 // (One thread per slot with three loads in flight took 5.3 us for 3 rows of
 // 3,000 spheres and 11.5 us for 26 rows of 13,001, a chain of memory
 // latencies.)  The gravity force G m_i sum is stored under the sphere's id.  With a
@@ -411,40 +438,31 @@ __global__ __launch_bounds__(kBlock) void k_grav_combine(const PileDev* __restri
                                                          const WorkItem* __restrict__ wl,
                                                          int precision) {
   __shared__ double red[4][3][64];
-  __shared__ int failed;
+  __shared__ int failed[4];
   const WorkItem w = wl[blockIdx.x >> 2];
   const int base = w.base + (int)(blockIdx.x & 3) * 64;
   const PileDev& P = piles[w.pile];
   const int ns = P.ns;
   if (P.G == 0.0 || base >= ns) return;                    // uniform over the block
-  // one read of the status for the whole block: the search and the contact
-  // forces run beside this and may set it, and every wave takes the barrier below
-  if (threadIdx.x == 0) failed = status_of(P);
-  __syncthreads();
-  if (failed != 0) return;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  // the search and the contact forces run beside this and may set the status:
+  // each wave takes what it reads to the barrier, and the first decides by all
+  const int st = P.status;
+  if (lane == 0) failed[wv] = st;
   const int k = base + lane;
   double g[3] = {0.0, 0.0, 0.0};
-  if (k < ns) {
-    if (P.tree) {
-      constexpr int per = kTreeParts / 4;
-      sum_rows<double>(P.tpart, ns, k, wv * per, (wv + 1) * per, kTreeParts, 0, 1, g);
-    } else {
-      // super-tiles and source splits (g_m0 < 0): every row
-      const int m0 = P.g_m0 < 0 ? P.g_np : P.g_m0;
-      const int b = P.g_m0 < 0 ? 0 : max(0, k / P.g_tile - m0);
-      // the rows from the slot's own tile on are contiguous up to the last
-      const int n = m0 + b + (P.g_np - (m0 + b * P.g_segs));
-      const int q0 = (int)((int64_t)n * wv / 4), q1 = (int)((int64_t)n * (wv + 1) / 4);
-      if (precision == 1)
-        sum_rows<float>((const float*)P.gpart, ns, k, q0, q1, m0, b, P.g_segs, g);
-      else
-        sum_rows<double>((const double*)P.gpart, ns, k, q0, q1, m0, b, P.g_segs, g);
-    }
+  if (k < ns && st == 0) {
+    const int m0 = P.g_m0, segs = P.g_segs;
+    const int b = P.tree || segs == 1 ? 0 : max(0, k / P.g_tile - m0);
+    const int n = P.tree ? kTreeParts : P.g_np - b * (segs - 1);
+    const int q0 = n * wv / 4, q1 = n * (wv + 1) / 4;
+    if (P.tree) sum_rows<double>(P.tpart, ns, k, q0, q1, n, 0, 1, g);
+    else if (precision == 1) sum_rows<float>((const float*)P.gpart, ns, k, q0, q1, m0, b, segs, g);
+    else sum_rows<double>((const double*)P.gpart, ns, k, q0, q1, m0, b, segs, g);
   }
   for (int c = 0; c < 3; ++c) red[wv][c][lane] = g[c];
   __syncthreads();
-  if (wv != 0) return;
+  if (wv != 0 || (failed[0] | failed[1] | failed[2] | failed[3]) != 0) return;
   double pull[3] = {0.0, 0.0, 0.0};
   if (k < ns) {
     for (int c = 0; c < 3; ++c)
@@ -488,41 +506,48 @@ int gravity_tiles(int precision, int* tiles) {
   return 3;
 }
 
-// A block is one wave, so a small pile needs small tiles and short segments to
-// reach every SIMD, and a large one needs its last blocks short: with whole
-// tiles only, the launch ends on a few waves working alone.  Targets per lane
-// amortise the sources' rotation, so the tile grows with the pile.  Gravity
-// stage in us on one MI355X, whole default tiles (512 FP64, 1024 FP32) ->
-// the plan's, FP64 / FP32: 1,000 spheres 212 -> 14 / 475 -> 13; 3,000
-// 212 -> 20 / 617 -> 17; 6,000 214 -> 45 / 617 -> 34; 13,001 222 -> 96 /
-// 623 -> 70; 20,000 243 -> 201 / 626 -> 133; 32,000 480 -> 418 / 627 -> 266;
-// 50,000 1032 -> 967 / 1014 -> 582; 124,958 6402 -> 6305 / 3669 -> 3354;
-// 180,001 FP32 7185 -> 6769.  Neighbouring choices (half or twice the tile or
-// the segment) were within 5 % of these or slower.  A given tile keeps its
-// size and is cut by the same rule.
+// Targets per lane amortise the sources' rotation (8 moves of 32 bits a step in
+// FP32, 16 in FP64), and a tile needs a row of partial sums, so the tile grows with
+// the pile as far as its blocks still fill the 256 compute units evenly: a block is
+// one compute unit's, and the launch lasts as long as the unit with the most.  Step
+// of one pile in us, FP64 by tiles of 128 / 192 / 256 / 512: 2,000 spheres 76 / 78 /
+// 81 / 119, 3,500 85 / 82 / 85 / 121, 6,000 98 / 101 / 100 / 124, 9,000 122 / 124 /
+// 116 / 127; by 256 / 512: 10,500 (231 blocks of 512, one round) 144 / 126, 13,001
+// 154 / 172, 16,000 184 / 214, 20,000 249 / 265; FP32: 2,000 75 / 76 / 76 / 108, 3,500
+// 81 / 79 / 80 / 111, 8,000 104 / 100 / 98 / 105; by 512 / 768 / 1024: 40,000 455 /
+// 491 / 562, 70,000 1208 / 1177 / 1257, 124,958 3491 / - / 3513.  An engine that fills
+// the chip takes any of them, the larger the better above some 4,000 spheres, because
+// of the rows: 25 piles of 16,000 spheres, 256 / 512: FP64 2928 / 2907 us, FP32 1941 /
+// 1650; 20 of 20,000 in FP64 are 1.3 % slower where the tile is cut than where not.
+//
+// A source tile is cut in segments (a row each) while that halves the one round of
+// blocks, or where a few blocks beyond one or two rounds would double or half as much
+// again the time: FP32, 12,000 spheres (300 blocks of 512) 137 -> 120 us, 16,000 (528)
+// 168 -> 143; 14,500 (435) 139 either way.  In tiles of 1024 the last two, in
+// quarters, end the launch evenly (124,958 spheres, FP32, gravity stage 3393 -> 3338
+// us).  A given tile keeps its size and is cut by the same rule.
 GravPlan gravity_plan(int precision, int64_t ns, int tile) {
-  GravPlan p;
-  if (tile > 0) {
-    p.tile = tile;
-  } else if (ns <= 1500) {
-    p.tile = 64;
-  } else if (ns <= 4500) {
-    p.tile = 128;
-  } else if (ns <= 24000) {
-    p.tile = 256;
-  } else {
-    // FP32 tiles of 512 up to the largest pile that has kGravSlots of them
-    p.tile = precision == 1 && ns > 512 * kGravSlots ? 1024 : 512;
+  GravPlan p{tile, 1, 0};
+  if (tile <= 0) {
+    if (ns <= 2500) p.tile = 128;
+    else if (ns <= 4200) p.tile = 192;
+    else if (precision == 0) p.tile = ns <= 9500 || (ns > 22 * 512 && ns <= 18432) ? 256 : 512;
+    else p.tile = ns <= 8000 ? 256 : (ns <= 45000 ? 512 : (ns <= 98304 ? 768 : 1024));
   }
-  if (ns <= 40000) {
-    // every tile is cut
-    p.seg = std::min(p.tile, ns <= 8000 ? 64 : (ns <= 24000 ? 128 : 256));
-    p.m0 = p.seg < p.tile ? 0 : INT32_MAX;
-  } else {
-    // the last 8,192 slots' tiles are cut, and their blocks issued last
-    p.seg = std::max(64, p.tile / 4);
-    p.m0 = (int)std::max<int64_t>(0, (ns + p.tile - 1) / p.tile - 8192 / p.tile);
+  constexpr int64_t kUnits = 256;
+  const int64_t nt = (ns + p.tile - 1) / p.tile, pairs = nt * (nt + 1) / 2;
+  const int per = p.tile / grav_pair_waves(p.tile);    // sources of a wave, uncut
+  if (pairs < 4 * kUnits) {
+    for (int64_t b = pairs; per / p.segs % 128 == 0; b *= 2) {
+      const bool uneven = b > kUnits && b < kUnits * 5 / 2 && b % kUnits < kUnits * 3 / 4;
+      if (2 * b > kUnits && !uneven) break;
+      p.segs *= 2;
+    }
+  } else if (p.tile == 1024) {
+    p.segs = 4;
+    p.m0 = (int)nt - 2;
   }
+  if (p.segs == 1) p.m0 = (int)nt;
   return p;
 }
 
@@ -534,9 +559,11 @@ template <typename T, int IPT>
 static void pairs_launch(hipStream_t st, const PileDev* piles, const GravPair* gp, int n,
                          bool soft) {
   if (soft)
-    hipLaunchKernelGGL((k_grav_pairs<T, IPT, true>), dim3(n), dim3(64), 0, st, piles, gp);
+    hipLaunchKernelGGL((k_grav_pairs<T, IPT, true>), dim3(n), dim3(64 * grav_pair_waves(64 * IPT)), 0, st,
+                       piles, gp);
   else
-    hipLaunchKernelGGL((k_grav_pairs<T, IPT, false>), dim3(n), dim3(64), 0, st, piles, gp);
+    hipLaunchKernelGGL((k_grav_pairs<T, IPT, false>), dim3(n), dim3(64 * grav_pair_waves(64 * IPT)), 0, st,
+                       piles, gp);
 }
 
 void launch_gravity_pairs(hipStream_t st, const PileDev* piles, const GravPair* gp, int nitems,
@@ -544,14 +571,15 @@ void launch_gravity_pairs(hipStream_t st, const PileDev* piles, const GravPair* 
   if (nitems <= 0) return;
   const int ipt = tile / 64;
   if (precision == 1) {
-    if (ipt == 1) pairs_launch<float, 1>(st, piles, gp, nitems, softened);
-    else if (ipt == 2) pairs_launch<float, 2>(st, piles, gp, nitems, softened);
+    if (ipt == 2) pairs_launch<float, 2>(st, piles, gp, nitems, softened);
+    else if (ipt == 3) pairs_launch<float, 3>(st, piles, gp, nitems, softened);
     else if (ipt == 4) pairs_launch<float, 4>(st, piles, gp, nitems, softened);
     else if (ipt == 8) pairs_launch<float, 8>(st, piles, gp, nitems, softened);
+    else if (ipt == 12) pairs_launch<float, 12>(st, piles, gp, nitems, softened);
     else pairs_launch<float, 16>(st, piles, gp, nitems, softened);
   } else {
-    if (ipt == 1) pairs_launch<double, 1>(st, piles, gp, nitems, softened);
-    else if (ipt == 2) pairs_launch<double, 2>(st, piles, gp, nitems, softened);
+    if (ipt == 2) pairs_launch<double, 2>(st, piles, gp, nitems, softened);
+    else if (ipt == 3) pairs_launch<double, 3>(st, piles, gp, nitems, softened);
     else if (ipt == 4) pairs_launch<double, 4>(st, piles, gp, nitems, softened);
     else pairs_launch<double, 8>(st, piles, gp, nitems, softened);
   }
