@@ -1393,12 +1393,13 @@ dem_status fetch_rows(dem_sim* s, const double* d, int k, int64_t n, double* hos
   return DEM_OK;
 }
 
-// The caller's history [n][kHist] as the device's rows.
-std::vector<double> hist_rows(const double* hist, int64_t n) {
-  std::vector<double> rows(size_t(kHistRow) * n, 0.0);
-  for (int64_t p = 0; p < n; ++p)
-    for (int c = 0; c < kHist; ++c) rows[p * kHistRow + c] = hist[p * kHist + c];
-  return rows;
+// The caller's history [n][kHist] as the device's rows of half `to`, through the
+// other half, which only a step uses.
+hipError_t put_history(const PileDev& h, int to, const double* hist, int64_t n, hipStream_t st) {
+  double* packed = h.hist[to ^ 1];
+  const hipError_t e = hipMemcpyAsync(packed, hist, size_t(n) * kHist * 8, hipMemcpyHostToDevice, st);
+  if (e == hipSuccess) launch_history_rows(st, packed, h.hist[to], n);
+  return e;
 }
 
 dem_status store_rows(dem_sim* s, double* d, int k, int64_t n, const double* host, hipStream_t st) {
@@ -1545,9 +1546,7 @@ dem_status dem_restore_state(dem_sim* s, const dem_state* in) {
   HIPCHK(s, hipMemcpyAsync(h.up_run[cur], run.data(), ns * 8, hipMemcpyHostToDevice, st));
   if (np) {
     HIPCHK(s, hipMemcpyAsync(h.pair_j[cur], pj.data(), np * 4, hipMemcpyHostToDevice, st));
-    const std::vector<double> rows = hist_rows(in->pair_hist, np);
-    HIPCHK(s, hipMemcpyAsync(h.hist[cur], rows.data(), rows.size() * 8, hipMemcpyHostToDevice, st));
-    HIPCHK(s, hipStreamSynchronize(st));
+    HIPCHK(s, put_history(h, cur, in->pair_hist, np, st));
   }
   launch_fill_u32(st, h.cell_cnt, 0u, s->sz.cells + 1);
   s->regrid = true;
@@ -1978,8 +1977,7 @@ dem_status dem_contact_forces(const dem_params* params, int64_t n, const double*
   HIPCHK(s, hipMemcpy(h.up_run[0], run.data(), n * 8, hipMemcpyHostToDevice));
   if (n_old) {
     HIPCHK(s, hipMemcpy(h.pair_j[0], pj.data(), n_old * 4, hipMemcpyHostToDevice));
-    const std::vector<double> rows = hist_rows(old_hist, n_old);
-    HIPCHK(s, hipMemcpy(h.hist[0], rows.data(), rows.size() * 8, hipMemcpyHostToDevice));
+    HIPCHK(s, put_history(h, 0, old_hist, n_old, st));
   }
   launch_fill_u32(st, h.cell_cnt, 0u, s->sz.cells + 1);
   r = ensure_own_table(s);

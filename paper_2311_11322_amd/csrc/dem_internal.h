@@ -349,6 +349,8 @@ void launch_read(hipStream_t st, ReadList& list);
 // history [n][kHist], through offset [ns].
 void launch_read_pairs(hipStream_t st, const PileDev& h, uint32_t* offset, uint64_t* keys,
                        double* hist);
+// n contacts' history [n][kHist] to rows [n][kHistRow].
+void launch_history_rows(hipStream_t st, const double* packed, double* rows, int64_t n);
 // The whole step of each listed pile in one workgroup: part 1 the stages
 // before gravity, part 2 those after it, part 3 all (no gravity); that many steps.
 void launch_fused(hipStream_t st, const PileDev* piles, const int32_t* plist, int n,

@@ -421,6 +421,14 @@ __global__ __launch_bounds__(kBlock) void k_read_pairs(PileDev P, const uint32_t
   }
 }
 
+// One thread per value of a row (the last one is zero).
+__global__ __launch_bounds__(kBlock) void k_history_rows(const double* __restrict__ packed,
+                                                         double* __restrict__ rows, int64_t n) {
+  const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x, p = t / kHistRow;
+  const int c = (int)(t % kHistRow);
+  if (p < n) rows[t] = c < kHist ? packed[p * kHist + c] : 0.0;
+}
+
 // No contacts and no counts: empty runs of every sphere, zero cell counts.
 __global__ void k_clear(PileDev P, int64_t cells) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -478,6 +486,11 @@ void launch_read_pairs(hipStream_t st, const PileDev& h, uint32_t* offset, uint6
                      offset);
   hipLaunchKernelGGL(k_read_pairs, dim3((h.ns + kBlock - 1) / kBlock), dim3(kBlock), 0, st, h,
                      offset, keys, hist);
+}
+void launch_history_rows(hipStream_t st, const double* packed, double* rows, int64_t n) {
+  const int64_t t = n * kHistRow;
+  hipLaunchKernelGGL(k_history_rows, dim3((unsigned)((t + kBlock - 1) / kBlock)), dim3(kBlock), 0, st,
+                     packed, rows, n);
 }
 void launch_clear(hipStream_t st, const PileDev& h, int64_t cells) {
   const int64_t n = std::max<int64_t>(std::max<int64_t>(h.ns, cells), 16);
