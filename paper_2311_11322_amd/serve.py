@@ -216,14 +216,16 @@ def shape_bucket(workloads: Sequence, precision: int):
 def autotune(workloads: Sequence, precision: int, steps: int = 3,
              cell_scales=(1.0, 1.25, 1.5, 2.0), tiles=None, cache: Optional[Dict] = None) -> Dict:
     """Pick the gravity tile and cell scale that minimise the measured step
-    time of this batch (a few steps per candidate).  The choice is cached
-    per shape bucket (``shape_bucket``): a later batch of the same shape
-    reuses it without measuring."""
+    time of this batch (a few steps per candidate).  Tile 0, the library's own
+    choice for each pile, is among them, in the place of the first supported
+    size, which it takes for the largest piles.  The choice is cached per shape
+    bucket (``shape_bucket``): a later batch of the same shape reuses it without
+    measuring."""
     cache = _TUNE_CACHE if cache is None else cache
     key = shape_bucket(workloads, precision)
     if key in cache:
         return dict(cache[key], cached=True)
-    tiles = list(tiles) if tiles else dem.gravity_tiles(precision)
+    tiles = list(tiles) if tiles else [0] + dem.gravity_tiles(precision)[1:]
     has_grav = any(w.params.get("G", 0.0) != 0.0 for w in workloads)
     if not has_grav:
         tiles = tiles[:1]
