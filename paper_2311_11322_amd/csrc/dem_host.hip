@@ -306,6 +306,7 @@ struct Batch {
   int n_fused_g = 0;
   int32_t* pl_fused_ng = nullptr;
   int n_fused_ng = 0;
+  int fused_steps = 1;                       // steps of one launch of those
   int n_staged = 0;                          // piles stepped by the staged kernels
   WorkItem* wl_grav = nullptr;               // spheres of every pile with gravity
   int n_grav_blk = 0;
@@ -456,6 +457,7 @@ dem_status rebuild(Batch& b, hipStream_t st, dem_sim* errsim) {
   b.tree_leaf_levels = 0;
   b.all_soft = true;
   int64_t tot_na = 0;
+  int fused_max = kFusedLong;
   b.n_staged = 0;
   for (int p = 0; p < (int)b.members.size(); ++p) {
     const dem_sim* s = b.members[p];
@@ -466,6 +468,7 @@ dem_status rebuild(Batch& b, hipStream_t st, dem_sim* errsim) {
     for (int a = 0; a < h.na; a += kBlock) wall.push_back({p, a});
     if (h.fused) {
       (h.G != 0.0 ? pfg : pfng).push_back(p);
+      if (h.G == 0.0) fused_max = std::max(fused_max, h.ns);
     } else {
       b.n_staged++;
       for (int a = 0; a < h.na; a += kBlock) wa.push_back({p, a});
@@ -552,6 +555,7 @@ dem_status rebuild(Batch& b, hipStream_t st, dem_sim* errsim) {
   b.n_fused_g = (int)pfg.size();
   HIPCHK(errsim, upload(b, &b.pl_fused_ng, pfng, st));
   b.n_fused_ng = (int)pfng.size();
+  b.fused_steps = std::max(1, kFusedSteps * kFusedLong / fused_max);
   HIPCHK(errsim, upload(b, &b.wl_sph, wsph, st));
   HIPCHK(errsim, upload(b, &b.wl_bin, wbin, st));
   b.n_bin_blk = (int)wbin.size();
@@ -768,8 +772,8 @@ dem_status ensure_graph(Batch& b, hipStream_t st, int steps, dem_sim* errsim) {
 }
 
 // n_steps steps of every member: the piles that one workgroup steps by itself
-// (k_fused without gravity) in launches of up to kFusedSteps steps, then the
-// others.  With gravity a step forks, and each is one launch of the captured
+// (k_fused without gravity) in launches of up to kFusedSteps steps (fewer where a
+// pile is large), then the others.  With gravity a step forks, and each is one launch of the captured
 // step.  Without, it is a row of short kernels, and the queue idles some 4 us
 // between two graph launches: calls of many steps take kGraphSteps of them in a
 // launch, and the few left over are enqueued kernel by kernel (a step of 2,350
@@ -783,9 +787,9 @@ dem_status run_steps(Batch& b, hipStream_t st, int64_t n_steps, bool fresh, dem_
     if (--n_steps == 0) return DEM_OK;
   }
   if (b.n_fused_ng > 0) {
-    for (int64_t k = 0; k < n_steps; k += kFusedSteps)
+    for (int64_t k = 0; k < n_steps; k += b.fused_steps)
       launch_fused(st, b.d_table, b.pl_fused_ng, b.n_fused_ng, b.cp, kModeStep, 3, b.precision,
-                   (int)std::min<int64_t>(kFusedSteps, n_steps - k));
+                   (int)std::min<int64_t>(b.fused_steps, n_steps - k));
     HIPCHK(errsim, hipGetLastError());
   }
   if (b.n_staged + b.n_fused_g == 0) return DEM_OK;

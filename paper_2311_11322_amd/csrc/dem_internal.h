@@ -356,8 +356,11 @@ void launch_history_rows(hipStream_t st, const double* packed, double* rows, int
 void launch_fused(hipStream_t st, const PileDev* piles, const int32_t* plist, int n,
                   ContactParams cp, int mode, int part, int precision, int steps);
 // Steps of one launch of k_fused without gravity: a launch apart costs about 8 us
-// beside a step's 28 (97 spheres); the bound keeps a launch to some milliseconds.
+// beside a step's 17 (97 spheres); the bound keeps a launch to some milliseconds (57 us
+// a step at 400 spheres, 366 us at 2,350), piles of more than kFusedLong spheres get
+// fewer steps in proportion.
 constexpr int kFusedSteps = 64;
+constexpr int kFusedLong = 512;
 // Piles of at most this many spheres run the fused step unless tuned
 // otherwise: one workgroup tests every pair of them itself, the staged step
 // uses the chip (measured per step, fused and staged: 97 spheres 18.8 and 38.2
