@@ -41,7 +41,7 @@ CONTACT_BYTES_PER_CONTACT = 64
 # of the L2-to-memory request counters (see the profile summaries); valid only for
 # the gravity source it was measured on.
 MEASURED_TRAFFIC = {
-    # (precision, spheres, tile asked for or the first supported, form of the exact sum):
+    # (precision, spheres, tile asked for (0: the library's choice), form of the exact sum):
     #     (bytes per launch, source_hash("kernels_gravity.hip"))
     ("fp64", 124958, 512, 1): (2623.5e6, "efd60b0144299520"),
     ("fp32", 124958, 1024, 1): (1703.8e6, "efd60b0144299520"),
@@ -361,8 +361,7 @@ def main():
         flop = mt[0] if mt and mt[1] == source_hash("kernels_tree.hip") else float("nan")
     achieved = flop / (grav_ms * 1e-3) / 1e12
     dt_key = "fp32" if prec == dem.PREC_FP32_FORCE else "fp64"
-    tile = args.gravity_tile or dem.gravity_tiles(prec)[0]
-    meas = MEASURED_TRAFFIC.get((dt_key, n, tile, args.gravity_form or 1))
+    meas = MEASURED_TRAFFIC.get((dt_key, n, args.gravity_tile, args.gravity_form or 1))
     traffic = (meas[0] if meas and meas[1] == source_hash("kernels_gravity.hip")
                and args.gravity == "direct"
                else None)

@@ -1,8 +1,8 @@
 // dem_host.hip -- host runtime behind the C-ABI of include/dem.h.
 //
 // Owns each system's device buffers (through the caller's allocator), the
-// device table of piles, the static work lists, and one captured HIP graph
-// per batch that replays a whole step.  No host synchronisation happens
+// device table of piles, the static work lists, and one captured HIP graph per
+// batch, of a step (with gravity) or of several.  No host synchronisation happens
 // inside a step; dem_step reads back one small status record per call.
 #include <algorithm>
 #include <cmath>
@@ -29,8 +29,8 @@ constexpr int kGraphSteps = 8;                 // steps of one graph launch (no 
 // Whether the gravity of a batch (pairs in all) takes longer than its contact
 // search and forces (spheres in all), and so gets the step's own queue.  Measured
 // with one pile, us per step with gravity first and second, FP64: 3,000 spheres
-// 87 and 78, 8,000 113 and 106, 10,000 126 and 130, 40,000 748 and 762; FP32:
-// 3,000 87 and 78, 4,500 88 and 82, 6,000 89 and 93, 10,000 104 and 114.  In large
+// 90 and 83, 9,000 125 and 117, 10,000 120 and 129, 40,000 706 and 719; FP32:
+// 3,000 87 and 79, 4,500 89 and 82, 6,000 90 and 91, 10,000 108 and 116.  In large
 // batches a sphere's contacts take 0.6 ns and a thousand pairs 1.1 ns (FP64) or
 // 0.5 ns (FP32).
 bool gravity_longer(int precision, int64_t pairs, int64_t spheres) {
@@ -637,7 +637,7 @@ void release_side(Batch& b) {
 // mark(k, stream, begin) is called before (begin) and after each stage k on
 // the stream that runs it.  Gravity depends only on the sorted copies of the
 // cell sort and is read only by the member reduction, so with `overlap` it runs on the
-// batch's second stream beside the search, scan and force kernels (the
+// batch's second stream beside the search and force kernels (the
 // captured step); without, every stage runs in order on one stream (the
 // t0 evaluation, the stateless hooks, and the profiled passes, whose event
 // spans then time each stage alone).  fresh: piles that bin on carried cells
@@ -1143,10 +1143,10 @@ struct Placer {
   }
 };
 
-// Places the table entry, the work lists and every buffer the search kernels
-// touch for n spheres; returns the bytes used.
 int64_t scan_items(int64_t n) { return (n + kScanChunk - 1) / kScanChunk; }
 
+// Places the table entry, the work lists and every buffer the search kernels
+// touch for n spheres; returns the bytes used.
 size_t plan_noalloc(char* base, int64_t n, PileDev& h, NoAllocLists& q) {
   Placer L{base};
   const int64_t cells = int64_t(1) << (3 * choose_bits(n));

@@ -177,7 +177,7 @@ struct PileDev {
   double* v;                 // [3][ns]
   double* F;                 // [3][ns] contact force (gravity is added by the reduction)
   double* tau;               // [3][ns] contact torque about the centre
-  uint32_t* key;             // [ns] Morton cell code
+  uint32_t* key;             // [ns] cell key (row-major, or Morton with gravity)
   uint32_t* sidx;            // [ns] sphere at sorted slot (piles with gravity)
   uint32_t* num;             // [ns] arrival number of sphere i in its cell
   uint32_t* sidx_raw;        // [ns] sphere at slot, in arrival order (piles with gravity)

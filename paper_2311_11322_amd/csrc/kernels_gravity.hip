@@ -127,10 +127,10 @@ __device__ __forceinline__ void ring(Src<T> s, const T (&xi)[IPT], const T (&yi)
 // 56 us (28 us).  Up to four waves share the sources, because a row of partial sums
 // then serves all of them: with one wave per block a small pile needed a row for
 // every 64 or 128 sources to fill the chip, and an engine that fills it anyway spent
-// its gain, and more, on writing and reading those rows.  Gravity stage, FP64, in
-// tiles of 512 by one wave / a row per 64 to 256 sources / so: 25 piles of 16,000
-// spheres 2.59 / 2.77 / 2.59 ms, one of 13,001 231 / 102 / 92 us, 124,958 6017 / 5999
-// / 6032 us.
+// its gain, and more, on writing and reading those rows.  Gravity stage, FP64, by one
+// wave for a whole pair of 512 / one for 64 to 256 sources, a row each / so: 25 piles
+// of 16,000 spheres 2.59 / 2.77 / 2.59 ms in tiles of 512 (2.70 in the plan's 256), one
+// of 13,001 231 / 102 / 91 us, one of 124,958 6017 / 5999 / 6032 us.
 template <typename T, int IPT, bool SOFT>
 __global__ __launch_bounds__(64 * grav_pair_waves(64 * IPT)) GRAV_WAVES(T, IPT) void k_grav_pairs(
     const PileDev* __restrict__ piles, const GravPair* __restrict__ gp) {
@@ -518,7 +518,7 @@ int gravity_tiles(int precision, int* tiles) {
 // 491 / 562, 70,000 1208 / 1177 / 1257, 124,958 3491 / - / 3513.  An engine that fills
 // the chip takes any of them, the larger the better above some 4,000 spheres, because
 // of the rows: 25 piles of 16,000 spheres, 256 / 512: FP64 2928 / 2907 us, FP32 1941 /
-// 1650; 20 of 20,000 in FP64 are 1.3 % slower where the tile is cut than where not.
+// 1650; 20 of 20,000 in FP64 by tiles of 512, cut in halves / not: 3515 / 3424.
 //
 // A source tile is cut in segments (a row each) while that halves the one round of
 // blocks, or where a few blocks beyond one or two rounds would double or half as much

@@ -2,8 +2,8 @@
 // step: the fifth-order rotation step, kick/drift/rotate of one aggregate,
 // member reconstruction, the per-pile cell grid from reduced partials, the
 // member reduction (GetAccelAndTorque, which adds each sphere's gravity force
-// to its contact force) and the end-of-step bookkeeping.  Included by the staged kernels and by the fused
-// per-pile step, so both do the same arithmetic.
+// to its contact force) and the end-of-step bookkeeping.  Included by the staged
+// kernels and by the fused per-pile step, so both do the same arithmetic.
 //
 // Paper references: leapfrog for centres of mass and a fifth-order
 // Runge-Kutta step for orientation and spin (Sec. 2.1-2.2); predicted member

@@ -1,5 +1,5 @@
 // step_contact.h -- per-element device functions of the contact search:
-// cell binning (counting sort of Morton codes, rank by id inside a cell),
+// cell binning (counting sort of cell keys; with gravity rank by id in a cell),
 // and the search that skips pairs inside one aggregate (the 27 neighbouring
 // cells of a sphere split among a group of lanes; big spheres searched
 // apart).  Included by the staged kernels and by the fused per-pile step.

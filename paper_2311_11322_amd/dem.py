@@ -383,7 +383,7 @@ class Sim:
 
 
 class Engine:
-    """Steps many systems together (one graph per step covering all)."""
+    """Steps many systems together (each launch covers all)."""
 
     def __init__(self, hbm_budget_bytes: int, stream=None):
         h = C.c_void_p()

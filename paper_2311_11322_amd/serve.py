@@ -1,7 +1,7 @@
 """Batched and served DEM runs on one GPU.
 
 * :func:`run_batch` steps many independent piles together through one
-  engine (every kernel of a step covers all piles; one HIP graph per step).
+  engine (every kernel of a step covers all piles).
 * :class:`Server` is a continuous-batching request loop: requests arrive over
   time, are admitted while the engine's HBM budget allows (footprint from the
   library), join the running batch at the next chunk boundary, and leave it
