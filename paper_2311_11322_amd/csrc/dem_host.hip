@@ -26,6 +26,13 @@ constexpr int kDefaultContacts = 8;
 constexpr int kFindContactsCap = 64;
 constexpr int kGraphSteps = 8;                 // steps of one graph launch (no gravity)
 
+// Pairs of whole tiles in a launch (of all its piles, by their numbers of spheres)
+// from which piles whose tiles can be taken in halves as targets take them whole: one
+// pile of 13,001 (322 pairs, 1.3 a compute unit) 174 us a step with whole tiles, 158
+// with halves; engines of piles of 500-20,000, 24 of them (2,450) 810 and 788, 48
+// (4,900) 1,390 and 1,351, 96 (10,000) 2,681 and 2,722, 256 (26,000) 6,912 and 7,005.
+constexpr double kWholeUnits = 7000.0;
+
 // Whether the gravity of a batch (pairs in all) takes longer than its contact
 // search and forces (spheres in all), and so gets the step's own queue.  Measured
 // with one pile, us per step with gravity first and second, FP64: 3,000 spheres
@@ -72,7 +79,7 @@ int ceil_log2(uint64_t v) {
 // Device footprint of one system, byte for byte what alloc_pile allocates.
 struct Sizes {
   int64_t na, ns, cap, cells, g_tile, g_nt, g_np, n_rblk;
-  int64_t g_m0, g_segs;      // see PileDev
+  int64_t g_m0, g_segs, g_half;   // see PileDev
   int g_form;                // 1 super-tile pairs, 2 per-target
   bool grav;
   bool tree;
@@ -143,6 +150,7 @@ Sizes pile_sizes(const dem_params& p, int64_t na, int64_t ns, int c_max, int til
   z.g_nt = (ns + z.g_tile - 1) / z.g_tile;
   z.g_m0 = z.g_nt;
   z.g_segs = 1;
+  z.g_half = 0;
   int64_t pair_np;
   if (z.g_nt > kGravSlots) {
     const int64_t span = (z.g_nt + kGravSlots - 1) / kGravSlots;   // tiles per super-tile
@@ -150,8 +158,10 @@ Sizes pile_sizes(const dem_params& p, int64_t na, int64_t ns, int c_max, int til
   } else {
     z.g_m0 = plan.m0;
     z.g_segs = plan.segs;
+    z.g_half = plan.half ? 1 : 0;
     const int64_t seg = z.g_tile / z.g_segs, last = ns - (z.g_nt - 1) * z.g_tile;
-    pair_np = z.g_m0 == z.g_nt ? z.g_nt
+    pair_np = plan.half ? 2 * z.g_nt - 1
+              : z.g_m0 == z.g_nt ? z.g_nt
                                : z.g_m0 + (z.g_nt - z.g_m0 - 1) * z.g_segs + (last + seg - 1) / seg;
   }
   const int64_t part_bytes = pair_np * 3 * ns * (p.precision == 1 ? 4 : 8);
@@ -163,6 +173,7 @@ Sizes pile_sizes(const dem_params& p, int64_t na, int64_t ns, int c_max, int til
     z.g_np = (z.g_nt + span - 1) / span;
     z.g_m0 = z.g_nt;
     z.g_segs = 1;
+    z.g_half = 0;
   } else {
     z.g_np = pair_np;
   }
@@ -286,6 +297,9 @@ struct Batch {
   WorkItem* wl_place = nullptr;
   int n_place_blk = 0;
   bool finish_in_reduce = false;             // no staged pile has too many blocks for it
+  // pair blocks of whole tiles whose reactions are kept by halves
+  GravPair* gh = nullptr;
+  int n_ghalf = 0;
   // gravity pair blocks, grouped by tile size (one launch per group)
   GravPair* gl[kGravTileSizes] = {};
   int n_grav[kGravTileSizes] = {};
@@ -444,7 +458,7 @@ dem_status rebuild(Batch& b, hipStream_t st, dem_sim* errsim) {
   b.finish_in_reduce = true;
   std::vector<GravItem> gmg[kGravTileSizes], gsg[kGravTileSizes];
   std::vector<std::pair<int64_t, GravItem>> gmw[kGravTileSizes];
-  std::vector<GravPair> glg[kGravTileSizes];
+  std::vector<GravPair> glg[kGravTileSizes], ghalf;
   int tiles[kGravTileSizes] = {};
   int n_groups = 0;
   std::vector<ScanSeg> sc;
@@ -458,6 +472,16 @@ dem_status rebuild(Batch& b, hipStream_t st, dem_sim* errsim) {
   b.all_soft = true;
   int64_t tot_na = 0;
   int fused_max = kFusedLong;
+  auto group = [&](int tile) {
+    int g = 0;
+    while (g < n_groups && tiles[g] != tile) ++g;
+    if (g == n_groups) tiles[n_groups++] = tile;
+    return g;
+  };
+  double units = 0.0;                        // pairs of whole tiles in the launch
+  for (const dem_sim* s : b.members)
+    if (s->h.G != 0.0 && !s->h.tree) units += 0.5 * s->h.ns * s->h.ns / (kHalvedTile * kHalvedTile);
+  const bool halved = units < kWholeUnits;
   b.n_staged = 0;
   for (int p = 0; p < (int)b.members.size(); ++p) {
     const dem_sim* s = b.members[p];
@@ -499,9 +523,7 @@ dem_status rebuild(Batch& b, hipStream_t st, dem_sim* errsim) {
       // every pair of tiles (i <= j), or of super-tiles, of the pile: each
       // unordered pair once; or every (target group, source split) of the
       // per-target form
-      int g = 0;
-      while (g < n_groups && tiles[g] != h.g_tile) ++g;
-      if (g == n_groups) tiles[n_groups++] = h.g_tile;
+      int g = h.g_half ? 0 : group(h.g_tile);
       if (h.g_form == 2) {
         if (b.precision == 1) b.any_rec32 = true;
         const int grp = 64 * gravity_split_ipt(b.precision, h.g_tile);
@@ -509,7 +531,23 @@ dem_status rebuild(Batch& b, hipStream_t st, dem_sim* errsim) {
         for (int tg = 0; tg < n_grp; ++tg)
           for (int sp = 0; sp < h.g_np; ++sp) gsg[g].push_back({p, tg, sp, 0});
       } else {
-        if (h.g_nt <= kGravSlots) {
+        if (h.g_half) {
+          // every pair of tiles in one block, or in two of half the targets each
+          if (halved) g = group(kHalvedTile / 2);
+          for (int i = 0; i < h.g_nt; ++i)
+            for (int j = i; j < h.g_nt; ++j) {
+              GravPair q{p, i * kHalvedTile, j * kHalvedTile, std::min((j + 1) * kHalvedTile, h.ns),
+                         2 * j, i == j ? -1 : 2 * i, kHalvedTile / grav_pair_waves(kHalvedTile), 0};
+              if (!halved) {
+                ghalf.push_back(q);
+                continue;
+              }
+              glg[g].push_back(q);
+              q.i0 += kHalvedTile / 2;
+              if (i != j) q.row_r += 1;
+              if (q.i0 < h.ns) glg[g].push_back(q);
+            }
+        } else if (h.g_nt <= kGravSlots) {
           auto row0 = [&](int t) { return t < h.g_m0 ? t : h.g_m0 + (t - h.g_m0) * h.g_segs; };
           for (int i = 0; i < h.g_nt; ++i)
             for (int j = i; j < h.g_nt; ++j) {
@@ -591,6 +629,8 @@ dem_status rebuild(Batch& b, hipStream_t st, dem_sim* errsim) {
     b.grav_tile[g] = tiles[g];
   }
   b.n_grav_groups = n_groups;
+  HIPCHK(errsim, upload(b, &b.gh, ghalf, st));
+  b.n_ghalf = (int)ghalf.size();
   b.gravity_first = b.any_tree || gravity_longer(b.precision, pairs, spheres);
   HIPCHK(errsim, upload(b, &b.seg_cells, sc, st));
   HIPCHK(errsim, upload(b, &b.item_cells, ic, st));
@@ -685,6 +725,7 @@ void enqueue_pass_marked(Batch& b, hipStream_t st, int mode, Mark mark, bool ove
   const bool fork = overlap && b.any_grav && b.side && staged;
   auto gravity = [&](hipStream_t s) {
     if (b.any_rec32) launch_gravity_records(s, b.d_table, b.wl_grav, b.n_grav_blk);
+    launch_gravity_whole(s, b.d_table, b.gh, b.n_ghalf, b.all_soft);
     for (int g = 0; g < b.n_grav_groups; ++g) {
       launch_gravity_pairs(s, b.d_table, b.gl[g], b.n_grav[g], b.precision, b.all_soft,
                            b.grav_tile[g]);
@@ -970,6 +1011,7 @@ dem_status alloc_pile(dem_sim* s, int64_t na, int64_t ns) {
   h.g_np = (int32_t)s->sz.g_np;
   h.g_m0 = (int32_t)s->sz.g_m0;
   h.g_segs = (int32_t)s->sz.g_segs;
+  h.g_half = (int32_t)s->sz.g_half;
   h.n_rblk = (int32_t)s->sz.n_rblk;
   h.box = s->prm.box[0];
   h.G = s->prm.G;

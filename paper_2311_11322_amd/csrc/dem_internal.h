@@ -96,6 +96,7 @@ struct PileDev {
   int32_t g_np;              // partial-sum rows: tiles x segments, super-tiles, or source splits
   int32_t g_m0;              // pairs of single tiles: tiles from g_m0 on are cut, as sources,
   int32_t g_segs;            // into g_segs segments (rows g_m0 + (J - g_m0) g_segs + s)
+  int32_t g_half;            // 1: as targets a tile J is two halves (reactions in rows 2J, 2J + 1)
   int32_t n_rblk;            // reconstruct blocks (bbox partials)
   int32_t n_periodic;        // cells per axis of a periodic pile
   int32_t member_scan;       // 1: reduction finds members by scanning all spheres
@@ -274,6 +275,9 @@ void launch_forces(hipStream_t st, const PileDev* piles, const WorkItem* wl, int
 void launch_gravity_records(hipStream_t st, const PileDev* piles, const WorkItem* wl, int nblk);
 void launch_gravity_pairs(hipStream_t st, const PileDev* piles, const GravPair* gp, int nitems,
                           int precision, bool softened, int tile);
+// Whole tiles as targets of the piles that are cut in halves (GravPlan::half; FP64).
+void launch_gravity_whole(hipStream_t st, const PileDev* piles, const GravPair* gp, int nitems,
+                          bool softened);
 // Piles of more than kGravSlots tiles: super-tiles of several tiles.
 void launch_gravity_tiles(hipStream_t st, const PileDev* piles, const GravItem* gl, int nitems,
                           int precision, bool softened, int tile);
@@ -289,10 +293,13 @@ void launch_gravity_combine(hipStream_t st, const PileDev* piles, const WorkItem
 int gravity_tiles(int precision, int* tiles);
 // How the exact sum of a pile in the pair form is cut into blocks: its tile (the
 // given one, or chosen by the number of spheres when tile is 0) and, for piles of
-// at most kGravSlots tiles, the segments into which tiles from m0 on are cut as sources.
+// at most kGravSlots tiles, the segments into which tiles from m0 on are cut as
+// sources, or (FP64) whether tiles of kHalvedTile may be taken as two halves as targets.
 struct GravPlan {
   int tile, segs, m0;
+  bool half;
 };
+constexpr int kHalvedTile = 512;
 // Waves of a block of the pair kernel, which share its sources, for a tile size.
 constexpr int grav_pair_waves(int tile) { return tile < 256 ? tile / 64 : 4; }
 GravPlan gravity_plan(int precision, int64_t ns, int tile);

@@ -75,13 +75,15 @@ __device__ __forceinline__ Src<T> relative(const Rec64& r, const double an[3]) {
 }
 
 // 64 sources, one per lane, led once around the wave past every lane's IPT
-// targets; with REACT each source's reaction sum comes back in (bx, by, bz).
-template <typename T, int IPT, bool SOFT, bool REACT>
+// targets; with REACT each source's reaction sum comes back in (bx, by, bz), one for
+// each of G groups of a lane's targets.
+template <typename T, int IPT, bool SOFT, bool REACT, int G = 1>
 __device__ __forceinline__ void ring(Src<T> s, const T (&xi)[IPT], const T (&yi)[IPT],
                                      const T (&zi)[IPT], const T (&ei)[IPT], const T (&mi)[IPT],
-                                     T (&ax)[IPT], T (&ay)[IPT], T (&az)[IPT], double c15, T& bx,
-                                     T& by, T& bz) {
-  bx = by = bz = 0;
+                                     T (&ax)[IPT], T (&ay)[IPT], T (&az)[IPT], double c15,
+                                     T (&bx)[G], T (&by)[G], T (&bz)[G]) {
+#pragma unroll
+  for (int h = 0; h < G; ++h) bx[h] = by[h] = bz[h] = 0;
   for (int step = 0; step < 64; ++step) {
 #pragma unroll
     for (int u = 0; u < IPT; ++u) {
@@ -97,9 +99,10 @@ __device__ __forceinline__ void ring(Src<T> s, const T (&xi)[IPT], const T (&yi)
       az[u] = fma(wi, dz, az[u]);
       if (REACT) {
         const T wj = mi[u] * c3;
-        bx = fma(wj, dx, bx);
-        by = fma(wj, dy, by);
-        bz = fma(wj, dz, bz);
+        constexpr int P = IPT / G;
+        bx[u / P] = fma(wj, dx, bx[u / P]);
+        by[u / P] = fma(wj, dy, by[u / P]);
+        bz[u / P] = fma(wj, dz, bz[u / P]);
       }
     }
     s.x = ror1(s.x);
@@ -108,9 +111,12 @@ __device__ __forceinline__ void ring(Src<T> s, const T (&xi)[IPT], const T (&yi)
     s.m = ror1(s.m);
     s.e = ror1(s.e);
     if (REACT) {
-      bx = ror1(bx);
-      by = ror1(by);
-      bz = ror1(bz);
+#pragma unroll
+      for (int h = 0; h < G; ++h) {
+        bx[h] = ror1(bx[h]);
+        by[h] = ror1(by[h]);
+        bz[h] = ror1(bz[h]);
+      }
     }
   }
 }
@@ -131,7 +137,11 @@ __device__ __forceinline__ void ring(Src<T> s, const T (&xi)[IPT], const T (&yi)
 // wave for a whole pair of 512 / one for 64 to 256 sources, a row each / so: 25 piles
 // of 16,000 spheres 2.59 / 2.77 / 2.59 ms in tiles of 512 (2.70 in the plan's 256), one
 // of 13,001 231 / 102 / 91 us, one of 124,958 6017 / 5999 / 6032 us.
-template <typename T, int IPT, bool SOFT>
+//
+// G = 2: the reactions from the two halves of the targets' tile in a row each, as two
+// blocks of half the targets store them, to the bit: a launch that has few blocks
+// takes the halves, a full one the whole tiles (rebuild in dem_host.hip).
+template <typename T, int IPT, bool SOFT, int G>
 __global__ __launch_bounds__(64 * grav_pair_waves(64 * IPT)) GRAV_WAVES(T, IPT) void k_grav_pairs(
     const PileDev* __restrict__ piles, const GravPair* __restrict__ gp) {
   constexpr int B = 64 * IPT, W = grav_pair_waves(64 * IPT);
@@ -177,16 +187,19 @@ __global__ __launch_bounds__(64 * grav_pair_waves(64 * IPT)) GRAV_WAVES(T, IPT) 
     Src<T> s = relative<T>(next, an);
     if (jx >= j1) s.m = (T)0;
     if (kAhead) next = rec[min(jx + 64, it.j1 - 1)];
-    T bx, by, bz;
+    T bx[G], by[G], bz[G];
     if (it.row_r < 0) {
-      ring<T, IPT, SOFT, false>(s, xi, yi, zi, ei, mi, ax, ay, az, c15, bx, by, bz);
+      ring<T, IPT, SOFT, false, G>(s, xi, yi, zi, ei, mi, ax, ay, az, c15, bx, by, bz);
     } else {
-      ring<T, IPT, SOFT, true>(s, xi, yi, zi, ei, mi, ax, ay, az, c15, bx, by, bz);
+      ring<T, IPT, SOFT, true, G>(s, xi, yi, zi, ei, mi, ax, ay, az, c15, bx, by, bz);
       if (jx < j1) {
-        T* q = part + (size_t)it.row_r * 3 * ns + jx;
-        q[0] = -bx;
-        q[ns] = -by;
-        q[2 * (size_t)ns] = -bz;
+#pragma unroll
+        for (int h = 0; h < G; ++h) {
+          T* q = part + (size_t)(it.row_r + h) * 3 * ns + jx;
+          q[0] = -bx[h];
+          q[ns] = -by[h];
+          q[2 * (size_t)ns] = -bz[h];
+        }
       }
     }
     if (!kAhead) next = rec[min(jx + 64, it.j1 - 1)];
@@ -259,12 +272,13 @@ __global__ __launch_bounds__(64) GRAV_WAVES(T, IPT) void k_grav_tiles(
         const int jx = jc + lane;
         Src<T> s = relative<T>(rec[min(jx, j1 - 1)], an);
         if (jx >= j1) s.m = (T)0;
-        T bx, by, bz;
+        T b[3][1];
+        T &bx = b[0][0], &by = b[1][0], &bz = b[2][0];
         if (J == I) {
-          ring<T, IPT, SOFT, false>(s, xi, yi, zi, ei, mi, ax, ay, az, c15, bx, by, bz);
+          ring<T, IPT, SOFT, false>(s, xi, yi, zi, ei, mi, ax, ay, az, c15, b[0], b[1], b[2]);
           continue;
         }
-        ring<T, IPT, SOFT, true>(s, xi, yi, zi, ei, mi, ax, ay, az, c15, bx, by, bz);
+        ring<T, IPT, SOFT, true>(s, xi, yi, zi, ei, mi, ax, ay, az, c15, b[0], b[1], b[2]);
         // add to the source's reaction sum over the tiles of SI so far (which
         // this same lane stored)
         if (jx < j1) {
@@ -400,9 +414,8 @@ __global__ __launch_bounds__(64) void k_grav_split(const PileDev* __restrict__ p
 }
 
 // Sum of the partials of slot k over its rows q0 <= q < q1, in row order, FP64.
-// The rows of a slot are every row below m0 (a tile each), the first row of each
-// of the b cut tiles before its own (the reaction of that tile's targets), and every
-// row after those.  Eight rows' loads are in flight.
+// The rows of a slot are every row below m0, then the first of segs rows b times,
+// and every row after those.  Eight rows' loads are in flight.
 template <typename T>
 __device__ __forceinline__ void sum_rows(const T* __restrict__ part, size_t ns, int k, int q0,
                                          int q1, int m0, int b, int segs, double g[3]) {
@@ -452,9 +465,13 @@ __global__ __launch_bounds__(kBlock) void k_grav_combine(const PileDev* __restri
   const int k = base + lane;
   double g[3] = {0.0, 0.0, 0.0};
   if (k < ns && st == 0) {
-    const int m0 = P.g_m0, segs = P.g_segs;
-    const int b = P.tree || segs == 1 ? 0 : max(0, k / P.g_tile - m0);
-    const int n = P.tree ? kTreeParts : P.g_np - b * (segs - 1);
+    // whole tiles below g_m0, the first row of each cut tile before the slot's own (the
+    // reaction of that tile's targets), and every row from its own tile on; halves:
+    // two reactions of each tile before its own, then one row per tile
+    const int t = P.tree || P.g_segs == 1 ? 0 : k / P.g_tile;
+    const int m0 = P.g_half ? 2 * t : P.g_m0, segs = P.g_segs;
+    const int b = P.g_half ? P.g_np : max(0, t - m0);
+    const int n = P.tree ? kTreeParts : (P.g_half ? P.g_nt + t : P.g_np - b * (segs - 1));
     const int q0 = n * wv / 4, q1 = n * (wv + 1) / 4;
     if (P.tree) sum_rows<double>(P.tpart, ns, k, q0, q1, n, 0, 1, g);
     else if (precision == 1) sum_rows<float>((const float*)P.gpart, ns, k, q0, q1, m0, b, segs, g);
@@ -512,13 +529,15 @@ int gravity_tiles(int precision, int* tiles) {
 // one compute unit's, and the launch lasts as long as the unit with the most.  Step
 // of one pile in us, FP64 by tiles of 128 / 192 / 256 / 512: 2,000 spheres 76 / 78 /
 // 81 / 119, 3,500 85 / 82 / 85 / 121, 6,000 98 / 101 / 100 / 124, 9,000 122 / 124 /
-// 116 / 127; by 256 / 512: 10,500 (231 blocks of 512, one round) 144 / 126, 13,001
-// 154 / 172, 16,000 184 / 214, 20,000 249 / 265; FP32: 2,000 75 / 76 / 76 / 108, 3,500
+// 116 / 127; by 256 / 512 whole / in halves as targets: 10,500 (231 blocks of 512, one
+// round) 144 / 126 / -, 11,500 154 / 173 / 149, 13,001 161 / 174 / 158, 16,000 191 /
+// 223 / 203, 20,000 - / 274 / 255; FP32: 2,000 75 / 76 / 76 / 108, 3,500
 // 81 / 79 / 80 / 111, 8,000 104 / 100 / 98 / 105; by 512 / 768 / 1024: 40,000 455 /
 // 491 / 562, 70,000 1208 / 1177 / 1257, 124,958 3491 / - / 3513.  An engine that fills
 // the chip takes any of them, the larger the better above some 4,000 spheres, because
-// of the rows: 25 piles of 16,000 spheres, 256 / 512: FP64 2928 / 2907 us, FP32 1941 /
-// 1650; 20 of 20,000 in FP64 by tiles of 512, cut in halves / not: 3515 / 3424.
+// of the rows: 256 piles of 500-20,000 in FP64, with 256 / halves / 512 above 11,264
+// spheres 7.12 / 7.00 / 6.91 ms, 25 piles of 16,000 in FP32, 256 / 512, 1.94 / 1.65;
+// 20 of 20,000 in FP64, halves / 512, 3.67 / 3.52, hence whole tiles past 18,432.
 //
 // A source tile is cut in segments (a row each) while that halves the one round of
 // blocks, or where a few blocks beyond one or two rounds would double or half as much
@@ -527,12 +546,17 @@ int gravity_tiles(int precision, int* tiles) {
 // quarters, end the launch evenly (124,958 spheres, FP32, gravity stage 3393 -> 3338
 // us).  A given tile keeps its size and is cut by the same rule.
 GravPlan gravity_plan(int precision, int64_t ns, int tile) {
-  GravPlan p{tile, 1, 0};
+  GravPlan p{tile, 1, 0, false};
   if (tile <= 0) {
     if (ns <= 2500) p.tile = 128;
     else if (ns <= 4200) p.tile = 192;
-    else if (precision == 0) p.tile = ns <= 9500 || (ns > 22 * 512 && ns <= 18432) ? 256 : 512;
+    else if (precision == 0) p.tile = ns <= 9500 ? 256 : 512;
     else p.tile = ns <= 8000 ? 256 : (ns <= 45000 ? 512 : (ns <= 98304 ? 768 : 1024));
+    if (precision == 0 && ns > 22 * kHalvedTile && ns <= 18432) {
+      p.half = true;
+      p.segs = 2;
+      return p;
+    }
   }
   constexpr int64_t kUnits = 256;
   const int64_t nt = (ns + p.tile - 1) / p.tile, pairs = nt * (nt + 1) / 2;
@@ -555,14 +579,14 @@ void launch_gravity_records(hipStream_t st, const PileDev* piles, const WorkItem
   hipLaunchKernelGGL(k_grav_records, dim3(nblk), dim3(kBlock), 0, st, piles, wl);
 }
 
-template <typename T, int IPT>
+template <typename T, int IPT, int G = 1>
 static void pairs_launch(hipStream_t st, const PileDev* piles, const GravPair* gp, int n,
                          bool soft) {
   if (soft)
-    hipLaunchKernelGGL((k_grav_pairs<T, IPT, true>), dim3(n), dim3(64 * grav_pair_waves(64 * IPT)), 0, st,
+    hipLaunchKernelGGL((k_grav_pairs<T, IPT, true, G>), dim3(n), dim3(64 * grav_pair_waves(64 * IPT)), 0, st,
                        piles, gp);
   else
-    hipLaunchKernelGGL((k_grav_pairs<T, IPT, false>), dim3(n), dim3(64 * grav_pair_waves(64 * IPT)), 0, st,
+    hipLaunchKernelGGL((k_grav_pairs<T, IPT, false, G>), dim3(n), dim3(64 * grav_pair_waves(64 * IPT)), 0, st,
                        piles, gp);
 }
 
@@ -583,6 +607,11 @@ void launch_gravity_pairs(hipStream_t st, const PileDev* piles, const GravPair* 
     else if (ipt == 4) pairs_launch<double, 4>(st, piles, gp, nitems, softened);
     else pairs_launch<double, 8>(st, piles, gp, nitems, softened);
   }
+}
+
+void launch_gravity_whole(hipStream_t st, const PileDev* piles, const GravPair* gp, int nitems,
+                          bool softened) {
+  if (nitems > 0) pairs_launch<double, kHalvedTile / 64, 2>(st, piles, gp, nitems, softened);
 }
 
 template <typename T, int IPT>

@@ -49,10 +49,11 @@ def _exact(n, soft, idx):
     return torch.cat(out).cpu().numpy()
 
 
-# tile 0: the plan's.  In FP32 12,000 and 16,000 are cut in halves, 15,361 and 18,000
-# are not; 9,700, 18,433 and 24,001 end on a tile of which some waves have no source
+# tile 0: the plan's.  In FP32 12,000 and 16,000 are cut in halves as sources, 15,361 and
+# 18,000 are not; in FP64 11,265 to 18,432 are cut in halves as targets (11,777: the last
+# has a half); 9,700, 18,433 and 24,001 end on a tile of which some waves have no source
 CASES = [(129, 0), (2500, 0), (2501, 0), (4200, 0), (4201, 0), (8000, 0), (8001, 0), (9500, 0),
-         (9700, 0), (11264, 0), (11265, 0), (12000, 0), (15361, 0), (16000, 0), (18000, 0),
+         (9700, 0), (11264, 0), (11265, 0), (11777, 0), (12000, 0), (15361, 0), (16000, 0), (18000, 0),
          (18432, 0), (18433, 0), (24001, 0), (45000, 0), (45001, 0), (98304, 0), (98305, 0),
          (70, -1), (513, -1), (1025, -1), (2600, -1), (5200, -1), (11400, -1)]
 
@@ -92,3 +93,30 @@ def test_cut_and_uncut_piles_in_one_engine(D, prec):
     for s, a in zip(sims, alone):
         b = s.read_state(fields)
         assert all(np.array_equal(a[k], b[k]) for k in fields)
+
+
+@pytest.mark.parametrize("n", [11265, 13001, 16000])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_whole_and_halved_blocks_give_the_same_bits(D, prec, n):
+    """A pile alone takes its tiles as targets in halves, in a launch that is full
+    without in whole tiles."""
+    print("[case] whole and halved blocks", prec, n, flush=True)
+    fields = ("agg_pos", "agg_vel", "sph_force")
+    a = _sim(D, n, prec)
+    a.step(2)
+    want = a.read_state(fields)
+    a.close()
+    eng = D.Engine(1 << 38)
+    sims = [_sim(D, n if k % 3 else 20000, prec) for k in range(36)]
+    for s in sims:
+        eng.attach(s)
+    assert eng.step(2) == D.DEM_OK
+    for k in (1, 35):
+        got = sims[k].read_state(fields)
+        assert all(np.array_equal(want[f], got[f]) for f in fields)
+    eng.detach(sims[1])
+    sims[1].step(1)
+    b = _sim(D, n, prec)
+    b.step(3)
+    x, y = b.read_state(fields), sims[1].read_state(fields)
+    assert all(np.array_equal(x[f], y[f]) for f in fields)
