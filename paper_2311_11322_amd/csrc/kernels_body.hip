@@ -333,7 +333,7 @@ __global__ __launch_bounds__(kBlock) void k_reduce(PileDev* __restrict__ piles,
     if (last) atomicExch(done, 0u);
   }
   __syncthreads();
-  if (last && threadIdx.x < 64) finish_one(P, threadIdx.x, mode, cp.dt);
+  if (last && threadIdx.x < 64) finish_one(P, threadIdx.x, mode, cp.dt, P.status != 0);
 }
 
 // One wave per pile: commit the step (flip the ping-pong halves) unless the
@@ -342,7 +342,7 @@ __global__ __launch_bounds__(kBlock) void k_reduce(PileDev* __restrict__ piles,
 __global__ __launch_bounds__(64) void k_finish(PileDev* __restrict__ piles, int mode, double dt) {
   PileDev& P = piles[blockIdx.x];
   if (P.fused) return;                       // k_fused finishes it
-  finish_one(P, threadIdx.x, mode, dt);
+  finish_one(P, threadIdx.x, mode, dt, P.status != 0);
 }
 
 __global__ void k_fill_u32(uint32_t* __restrict__ p, uint32_t value, int64_t n) {

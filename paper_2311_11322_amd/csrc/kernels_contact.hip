@@ -84,7 +84,7 @@ __global__ __launch_bounds__(NT, 5) void k_search(PileDev* __restrict__ piles,
   // big spheres: k_search_big.  The status may change meanwhile (another block
   // finds the lists full): a wave that reads a failure lists nothing, and the
   // block goes on to its barriers.
-  const bool active = k < P.ns - P.n_big && searching(P);    // uniform over the lane group
+  const bool active = k < P.ns - P.n_big && searching(P, P.status);   // uniform over the lane group
   uint32_t nup = 0, nlo = 0, i = 0;
   if (active) {
     i = P.sid[k].id;
@@ -138,7 +138,7 @@ __global__ __launch_bounds__(kBlock) void k_search_big(PileDev* __restrict__ pil
   __shared__ uint32_t fill[4];
   const WorkItem w = wl[blockIdx.x];
   PileDev& P = piles[w.pile];
-  search_big_one(P, w.base, threadIdx.x, kBlock, buf_up, buf_lo, fill);
+  search_big_one(P, w.base, threadIdx.x, kBlock, P.status, buf_up, buf_lo, fill);
 }
 
 }  // namespace

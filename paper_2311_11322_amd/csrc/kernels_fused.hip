@@ -99,7 +99,7 @@ __device__ void search_all(PileDev& P, SearchLds<kFusedLanes, kFusedThreads>& sh
   if (tid == 0) *P.runs = *total;
   stage_sync();
   for (int kb = 0; kb < P.n_big; ++kb) {
-    search_big_one(P, kb, tid, kFusedThreads, big_up, big_lo, big_fill);
+    search_big_one(P, kb, tid, kFusedThreads, tid == 0 ? status_of(P) : 0, big_up, big_lo, big_fill);
     stage_sync();                         // runs written, the LDS read
   }
 }
@@ -322,7 +322,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_fused(PileDev* __restrict__ p
         }
         stage_sync();
       }
-      if (tid < 64) finish_one(P, tid, mode, cp.dt);
+      if (tid < 64) finish_one(P, tid, mode, cp.dt, !ok);
     }
     if (step + 1 < steps) stage_sync();     // the entry as the end of the step left it
   }

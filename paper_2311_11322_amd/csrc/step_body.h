@@ -524,10 +524,10 @@ __device__ __forceinline__ void reduce_tail(const PileDev& P, int A, const doubl
 
 // Per pile, by one wave: commit the step (flip the ping-pong halves) unless the
 // pile failed during it, in which case its state stays at the failing step's
-// start and the step index is recorded; the perturber's reaction and kick.  The
-// status is read where atomics leave it: in k_fused the same launch set it.
-__device__ __forceinline__ void finish_one(PileDev& P, int lane, int mode, double dt) {
-  if (status_of(P) != 0) {
+// start and the step index is recorded; the perturber's reaction and kick.  failed:
+// the pile's status by the caller, as in k_fused the same launch set it by atomics.
+__device__ __forceinline__ void finish_one(PileDev& P, int lane, int mode, double dt, bool failed) {
+  if (failed) {
     if (lane == 0 && P.fail_step < 0) P.fail_step = P.step;
     return;
   }

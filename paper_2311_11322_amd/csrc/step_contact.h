@@ -330,11 +330,10 @@ __device__ __forceinline__ void store_runs(const PileDev& P, int k, uint32_t i, 
   put_run<st>(buf + (kRunLds - nlo) * st, nlo, lane, Lanes, P.lo_nbr + l0);
 }
 
-// Whether the pile's search goes on.  A failed pile's does not; but a stateless
-// search (given positions) whose lists are full goes on counting, so that it
-// reports how many contacts there are.
-__device__ __forceinline__ bool searching(const PileDev& P) {
-  const int st = status_of(P);
+// Whether the search of a pile of status st goes on.  A failed pile's does not; but
+// a stateless search (given positions) whose lists are full goes on counting, so that
+// it reports how many contacts there are.
+__device__ __forceinline__ bool searching(const PileDev& P, int st) {
   return st == 0 || (st == kStCapacity && (P.given || P.na == 0));
 }
 
@@ -355,17 +354,18 @@ __device__ __forceinline__ bool take_runs(PileDev& P, uint32_t nup, uint32_t nlo
 }
 
 // The kb-th big sphere of the pile (at slot ns - n_big + kb), searched by
-// nthreads threads of one block (tid the thread's index; LDS buf_up, buf_lo
-// of kBigRun entries and fill[4]; every thread of the block calls this):
+// nthreads threads of one block (tid the thread's index, st the first one's reading
+// of the status; LDS buf_up, buf_lo of kBigRun entries and fill[4]; every thread of the
+// block calls this):
 // they split the cells within reach of any other sphere and the big
 // spheres' cell, gather both runs in LDS, rank-sort them and store them.  A
 // run longer than kBigRun is counted, and a capacity failure.
 __device__ __forceinline__ void search_big_one(PileDev& P, int kb, int tid, int nthreads,
-                                               uint32_t* buf_up, uint32_t* buf_lo,
+                                               int st, uint32_t* buf_up, uint32_t* buf_lo,
                                                uint32_t* fill) {
   // one read of the status for the whole block (another block of this pile
   // may set it meanwhile), so that every thread takes the same path
-  if (tid == 0) fill[0] = searching(P) ? 0u : 1u;
+  if (tid == 0) fill[0] = searching(P, st) ? 0u : 1u;
   __syncthreads();
   const bool failed = fill[0] != 0u;
   __syncthreads();
