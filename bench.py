@@ -43,8 +43,10 @@ CONTACT_BYTES_PER_CONTACT = 64
 MEASURED_TRAFFIC = {
     # (precision, spheres, tile asked for (0: the library's choice), form of the exact sum):
     #     (bytes per launch, source_hash("kernels_gravity.hip"))
-    ("fp64", 124958, 512, 1): (2623.5e6, "efd60b0144299520"),
-    ("fp32", 124958, 1024, 1): (1703.8e6, "efd60b0144299520"),
+    ("fp64", 124958, 0, 1): (2355.8e6, "36b80f28d70b6585"),
+    ("fp32", 124958, 0, 1): (849.1e6, "36b80f28d70b6585"),
+    ("fp64", 124958, 0, 2): (187.3e6, "36b80f28d70b6585"),
+    ("fp64", 499845, 0, 1): (27371.1e6, "36b80f28d70b6585"),
 }
 
 

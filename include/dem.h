@@ -226,7 +226,7 @@ dem_status dem_find_contacts(const double* pos, const double* radius, const int3
                              int64_t n, const double* box, uint64_t* pairs_out, int64_t cap,
                              int64_t* n_out);
 
-/* Contact forces of given sphere states (test hook, so that a checker can
+/* Contact forces of given sphere states (test hook, so that a test can
  * evaluate the contact model on exactly the same FP64 input): one evaluation
  * of the contact part of a step -- search skipping pairs of one aggregate,
  * spring history carried from the given previous contacts, the contact force
