@@ -337,17 +337,17 @@ typedef struct {
                                   2 staged.  Same order and arithmetic, so the same
                                   results; different cost. */
     int32_t fused;             /* 0 automatic -- the whole step of the system in one
-                                  workgroup (one launch per step for a batch of such systems;
-                                  with gravity, two launches around the batched gravity
-                                  kernels) when it has at most 256 spheres; 1 always; 2 never
+                                  workgroup (one launch for up to 64 steps of a batch of such
+                                  systems; with gravity, two launches a step around the
+                                  batched gravity kernels) when it has at most 256 spheres; 1 always; 2 never
                                   (one launch per stage).  Never with tree gravity.  The same
                                   arithmetic per element; the centre of mass and bulk radius
                                   are summed in another order (spin-up, stop rule). */
     int32_t gravity_form;      /* form of the exact softened sum (Eq. 4): 0 automatic --
                                   pairs unless their partial sums would exceed 64 GiB;
                                   1 pairs: each unordered pair once, one partial sum per
-                                  sphere and tile (or half or quarter of a tile of a pile
-                                  of few), past 256 tiles on super-tiles of
+                                  sphere and tile (or half or quarter of one, where that
+                                  fills the chip), past 256 tiles on super-tiles of
                                   ceil(tiles / 256) tiles, one per super-tile (at most
                                   256 x 3 values per sphere); 2 per
                                   target: each ordered pair from its target's side, one
